@@ -923,8 +923,8 @@ size_t workspace_bytes(int64_t n, int op) {
         b += align_up(4 * un) * 2;                      // quotient counts, members
         b += align_up(8 * (un + 1));                    // member offsets
         b += align_up(8 * (size_t)scan_parts(n));       // scan partials
-        b += align_up(4 * un) + align_up(4);            // large coarse rows and their count
-        b += align_up(4 * (size_t)kGiantSlots * giant_words(n));  // giant rows' bitmaps
+        b += align_up(4 * un);                          // ranks of the members
+        b += align_up(4 * (size_t)kGiantShare * giant_words(n));  // giant rows' bitmaps
         b += align_up(4 * (size_t)kGiantMeta);
         b += align_up(un);                              // row classes
     }
@@ -970,9 +970,8 @@ bool carve(void *base, size_t bytes, int64_t n, int op, Workspace *ws) {
         ws->q.members = (int32_t *)take(4 * un);
         ws->q.moff = (int64_t *)take(8 * (un + 1));
         ws->q.part = (unsigned long long *)take(8 * (size_t)scan_parts(n));
-        ws->q.big = (int32_t *)take(4 * un);
-        ws->q.big_count = (uint32_t *)take(4);
-        ws->q.gbits = (uint32_t *)take(4 * (size_t)kGiantSlots * giant_words(n));
+        ws->q.rank = (int32_t *)take(4 * un);
+        ws->q.gbits = (uint32_t *)take(4 * (size_t)kGiantShare * giant_words(n));
         ws->q.gmeta = (uint32_t *)take(4 * (size_t)kGiantMeta);
         ws->q.cls = (uint8_t *)take(un);
     }
@@ -1539,13 +1538,39 @@ int aggregate_impl(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int32_t *a
     return collect_sweeps(ctx, launches, ws, s);
 }
 
+// The quotient's arrays of a coarsening workspace.  Everything before them
+// (tuples, worklists, labels: 38 bytes per vertex) holds nothing that is
+// needed once the aggregation has returned, and is the quotient's spare buffer
+// unless the caller has a larger one (`idle`, of idle_cap entries).
+QuotientWs quotient_ws(const Workspace &ws, int32_t *idle, int64_t idle_cap) {
+    QuotientWs q;
+    q.cnt = ws.q.cnt;
+    q.moff = ws.q.moff;
+    q.members = ws.q.members;
+    q.part = ws.q.part;
+    q.rank = ws.q.rank;
+    q.gbits = ws.q.gbits;
+    q.gmeta = ws.q.gmeta;
+    q.cls = ws.q.cls;
+    q.tmp = (int32_t *)ws.T;
+    q.tmp_cap = (int64_t)(((char *)ws.q.cnt - (char *)ws.T) / 4);
+    if (idle && idle_cap > q.tmp_cap) {
+        // from a 256-byte boundary on, as the workspace's arrays
+        const size_t skip = (align_up((size_t)(uintptr_t)idle) - (size_t)(uintptr_t)idle) / 4;
+        if (idle_cap - (int64_t)skip > q.tmp_cap) {
+            q.tmp = idle + skip;
+            q.tmp_cap = idle_cap - (int64_t)skip;
+        }
+    }
+    return q;
+}
+
 // Coarse graph of an aggregation into caller buffers; *nnz_out (host) gets
 // the coarse nnz.
 int quotient_impl(mis2_ctx *ctx, const mis2_graph *g, const int32_t *agg, int64_t n_agg,
                   int64_t *crow, int32_t *ccol, int64_t *nnz_out, const Workspace &ws,
-                  hipStream_t s) {
-    QuotientWs q{ws.q.cnt,   ws.q.moff,  ws.q.members, ws.q.part, ws.q.big,
-                 ws.q.big_count, ws.q.gbits, ws.q.gmeta, ws.q.cls};
+                  int32_t *idle, int64_t idle_cap, hipStream_t s) {
+    const QuotientWs q = quotient_ws(ws, idle, idle_cap);
     HIP_TRY(ctx, quotient_graph(g->row_ptr, g->col, g->n, g->nnz, agg, n_agg, crow, ccol, q, s));
     int64_t nnz = 0;
     HIP_TRY(ctx, hipMemcpyAsync(&ctx->pinned[0], crow + n_agg, sizeof(int64_t),
@@ -1615,7 +1640,7 @@ BatchArena carve_batch_arena(void *base, int32_t G, int64_t n, int64_t nnz) {
 
 int batch_level(mis2_ctx *ctx, const mis2_graph &cur, uint64_t seed, int64_t stop_below,
                 int32_t *agg_dst, const BatchArena &ar, int64_t *crow_next, int32_t *ccol_next,
-                BatchLevel *bl, hipStream_t s) {
+                int32_t *idle, int64_t idle_cap, BatchLevel *bl, hipStream_t s) {
     int rc;
     const int32_t cg = (int32_t)bl->voff.size() - 1;
     std::vector<uint32_t> gb(cg);
@@ -1674,8 +1699,7 @@ int batch_level(mis2_ctx *ctx, const mis2_graph &cur, uint64_t seed, int64_t sto
     bl->n_next = n_next;
     bl->nnz_next = 0;
     if (n_next > 0) {
-        QuotientWs q{ws.q.cnt,       ws.q.moff,  ws.q.members, ws.q.part, ws.q.big,
-                     ws.q.big_count, ws.q.gbits, ws.q.gmeta,   ws.q.cls};
+        const QuotientWs q = quotient_ws(ws, idle, idle_cap);
         HIP_TRY(ctx, quotient_graph(cur.row_ptr, cur.col, cur.n, cur.nnz, ar.map, n_next, crow_next,
                                     ccol_next, q, s));
         HIP_TRY(ctx, hipMemcpyAsync(&ctx->pinned[0], crow_next + n_next, sizeof(int64_t),
@@ -1743,7 +1767,8 @@ int mis2_quotient(mis2_ctx *ctx, const mis2_graph *g, const int32_t *agg_id, int
     Workspace ws;
     if ((rc = get_workspace(ctx, g, MIS2_OP_COARSEN, &ws))) return rc;
     if ((rc = maybe_validate(ctx, g, ws, s))) return rc;
-    return quotient_impl(ctx, g, agg_id, n_agg, coarse_row_ptr, coarse_col, coarse_nnz, ws, s);
+    return quotient_impl(ctx, g, agg_id, n_agg, coarse_row_ptr, coarse_col, coarse_nnz, ws, nullptr,
+                         0, s);
 }
 
 // mis2_galerkin: member counts, offsets, cursors and lists, scan partials
@@ -2056,7 +2081,8 @@ int mis2_cgs_setup(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int point,
         ws.lenc = (int32_t *)crow[1];
         if ((rc = aggregate_impl(ctx, g, seed, plan->cluster, &nc, nullptr, ws, s))) return rc;
         int64_t cnnz = 0;
-        if ((rc = quotient_impl(ctx, g, plan->cluster, nc, crow[0], ccol[0], &cnnz, ws, s)))
+        if ((rc = quotient_impl(ctx, g, plan->cluster, nc, crow[0], ccol[0], &cnnz, ws, ccol[1],
+                                g->nnz, s)))
             return rc;
         cg = mis2_graph{nc, cnnz, crow[0], ccol[0]};
     } else {
@@ -2195,8 +2221,11 @@ int mis2_coarsen(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int64_t stop
         *n_levels = lv;
         if (na == cur.n) break;  // no progress
         int64_t cnnz = 0;
+        // the buffer this level's graph came from, past its entries (level 0
+        // reads the caller's graph)
+        const int64_t used = lv == 1 ? 0 : cur.nnz;
         if ((rc = quotient_impl(ctx, &cur, agg_out + off, na, crow[lv & 1], ccol[lv & 1], &cnnz, ws,
-                                s)))
+                                ccol[(lv + 1) & 1] + used, g->nnz - used, s)))
             return rc;
         off += cur.n;
         cur.n = na;
@@ -2266,8 +2295,11 @@ int mis2_aggregate_batched(mis2_ctx *ctx, const mis2_graph *g, int32_t n_graphs,
                         (long long)agg_cap, lv);
         for (int32_t i = 0; i < cg; i++) bl.allow[i] = lv + 1 < max_levels;
         const int nx = (lv + 1) & 1;
+        // the buffer this level's union came from, past its entries (level 0
+        // reads the caller's)
+        const int64_t used = lv == 0 ? 0 : cur.nnz;
         if ((rc = batch_level(ctx, cur, seed, stop_below, agg_out + off, ar, ar.crow[nx],
-                              ar.ccol[nx], &bl, s)))
+                              ar.ccol[nx], ar.ccol[nx ^ 1] + used, g->nnz - used, &bl, s)))
             return rc;
         std::vector<int32_t> next_ids;
         for (int32_t i = 0; i < cg; i++) {

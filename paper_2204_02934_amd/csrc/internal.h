@@ -145,11 +145,10 @@ struct Workspace {
         int64_t *moff = nullptr;
         int32_t *members = nullptr;
         unsigned long long *part = nullptr;
-        int32_t *big = nullptr;
-        uint32_t *big_count = nullptr;
-        uint32_t *gbits = nullptr;   // [kGiantSlots * giant_words(n)]
+        int32_t *rank = nullptr;
+        uint32_t *gbits = nullptr;   // [kGiantShare * giant_words(n)]
         uint32_t *gmeta = nullptr;   // [kGiantMeta]
-        uint8_t *cls = nullptr;      // [n] which pass handles each coarse row
+        uint8_t *cls = nullptr;      // [n] which path handles each coarse row
     } q;
 };
 
@@ -508,10 +507,14 @@ hipError_t exclusive_scan_u32_i64(const uint32_t *in, int64_t n, int64_t *out,
 hipError_t launch_scan_tiles(uint32_t *blocksum, int64_t nb, uint32_t *d_total, hipStream_t s);
 
 // quotient.hip: coarse graph of an aggregation.
-// Coarse rows with more than kGiantCand candidates take one of kGiantSlots
-// bitmap slots (a bit per coarse id) filled by the whole grid.
-constexpr int kGiantSlots = 8;
-constexpr int64_t kGiantCand = 65536;
+// Coarse rows with more than kGiantCand candidates take one of up to
+// kGiantSlots bitmap slots (a bit per coarse id) filled by the whole grid; the
+// workspace holds kGiantShare bitmaps of n bits, which make more slots the
+// fewer coarse ids there are.  A workgroup takes some 5 us per 2048 candidates,
+// so a row of 65536 held up its whole launch.
+constexpr int kGiantSlots = 64;
+constexpr int kGiantShare = 8;
+constexpr int64_t kGiantCand = 16384;
 constexpr int kGiantMeta = 3 * kGiantSlots + 1;  // rows, smallest and largest ids, count
 inline size_t giant_words(int64_t n) { return (size_t)((n + 31) / 32); }
 struct QuotientWs {
@@ -519,12 +522,19 @@ struct QuotientWs {
     int64_t *moff;              // [n_agg + 1] member offsets
     int32_t *members;           // [n]
     unsigned long long *part;   // [scan_parts(n)]
-    int32_t *big;               // [n_agg] coarse rows left to whole workgroups
-    uint32_t *big_count;        // [1]
-    uint32_t *gbits;            // [kGiantSlots * giant_words(n_agg)] bitmaps of giant rows
+    int32_t *rank;              // [n] ranks of the members
+    uint32_t *gbits;            // [kGiantShare * giant_words(n)] bitmaps of giant rows
     uint32_t *gmeta;            // [kGiantMeta]
-    uint8_t *cls;               // [n_agg] the pass of each coarse row (small, middle, large)
+    uint8_t *cls;               // [n_agg] the path of each coarse row (0 first, 1 second, 2 the rest)
+    int32_t *tmp;               // spare buffer of tmp_cap entries (null: none)
+    int64_t tmp_cap;
 };
+// members[moff[a] .. moff[a + 1]) = the vertices of aggregate a in no
+// particular order, cnt[a] how many (vertices with agg < 0 are left out);
+// rank: [n] scratch, part: [scan_parts(n_agg)].
+hipError_t launch_member_lists(int64_t n, const int32_t *agg, int64_t n_agg, uint32_t *cnt,
+                               int64_t *moff, unsigned long long *part, int32_t *rank,
+                               int32_t *members, hipStream_t s);
 // nnz: stored entries of the fine graph (no coarse row has more candidates).
 hipError_t quotient_graph(const int64_t *row_ptr, const int32_t *col, int64_t n, int64_t nnz,
                           const int32_t *agg, int64_t n_agg, int64_t *crow, int32_t *ccol,
@@ -603,7 +613,7 @@ struct mis2_ctx;
 namespace mis2 {
 int batch_level(mis2_ctx *ctx, const mis2_graph &cur, uint64_t seed, int64_t stop_below,
                 int32_t *agg_dst, const BatchArena &ar, int64_t *crow_next, int32_t *ccol_next,
-                BatchLevel *bl, hipStream_t s);
+                int32_t *idle, int64_t idle_cap, BatchLevel *bl, hipStream_t s);
 }  // namespace mis2
 
 // Context (abi.hip).

@@ -9,18 +9,24 @@
 // for graphs that stop coarsening) and edges to it are dropped.
 //
 // Member lists are built by a counting sort (their order does not matter:
-// every coarse row is a sorted set).  Rows go to one of four paths by their
-// candidate count (the members' stored entries): up to kWSmall and up to
-// kWCap, one wavefront each (two passes; the first, with a small LDS hash
-// set, keeps many rows in flight and marks the rows it leaves to the
-// second); up to kGiantCand, one workgroup each; beyond, a bitmap slot that
-// the whole grid fills.  A wavefront puts the aggregate ids of the members'
-// neighbours into its LDS hash set and ranks the distinct ones; a workgroup
-// sorts them in LDS or sweeps windows of 32*kBitWords coarse ids with an LDS
-// bitmap, which emits ids in increasing order and, after the first window,
-// visits only the range the row's candidates span.  Every path deals the
-// members' entries out evenly over its lanes.  Each kernel runs twice: once
-// to count each row, once (after a prefix sum) to write it.
+// every coarse row is a sorted set).  A coarse row's candidates are its
+// members' stored entries; what it holds is their distinct aggregate ids, of
+// which there are few even where the candidates are many (a 27-point mesh's
+// aggregate has some 1000 candidates and 30 neighbours).  Rows go to one of
+// four paths by how many distinct ids they turn out to have: a small LDS hash
+// set per lane group (k_coarse_rows_group, several rows per wavefront where
+// aggregates are small), a 1024-slot set per wavefront (only where an LDS
+// bitmap cannot hold every coarse id), one workgroup, and for rows of more than
+// kGiantCand candidates a bitmap slot that the whole grid fills.  The first two rank the distinct ids; a workgroup sweeps the
+// coarse ids with an LDS bitmap (of as many bits as there are coarse ids, in
+// windows of 32*kBitWords where that is more), which emits them in increasing
+// order and, after the first window, visits only the range the row's
+// candidates span.  Every path deals the members' entries out evenly over its
+// lanes.  The first three write their rows to a spare buffer while they count
+// them, and after the prefix sum they are only copied; what the buffer has no
+// room for is gathered a second time and written then.
+#include <algorithm>
+
 #include "internal.h"
 #include "lanes.h"
 
@@ -28,12 +34,11 @@ namespace mis2 {
 
 namespace {
 
-constexpr int kQCap = 4096;                  // candidates sorted in LDS per coarse row
-constexpr int kBitWords = 12288;             // LDS bitmap words (48 KiB)
-constexpr int64_t kQWindow = 32 * (int64_t)kBitWords;  // coarse ids per bitmap window
+constexpr int kBitWords = 12288;             // most LDS bitmap words (48 KiB)
 constexpr int kWaves = kBlock / 64;
-constexpr int kWCap = 1024;                  // candidates of a row handled by one wavefront
-constexpr int kWSmall = 128;                 // rows a wavefront takes in the first pass
+constexpr int kWSlots = 1024;                // set of a wavefront row (second path)
+constexpr int kWLim = 768;                   // a row with as many distinct ids goes on
+constexpr uint32_t kWCand = 8192;            // or with more candidates
 constexpr int kWEdges = 8;                   // entries per lane loaded together
 
 __device__ __forceinline__ void wave_sync() {
@@ -42,19 +47,6 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Coarse rows with at most CAP candidates, one wavefront each.  kRowsMark:
-// every coarse row; the count pass marks in cls[a] whether row a has more
-// than CAP candidates (1) or not (0), and the fill pass skips the marked
-// rows.  kRowsMarked: the rows marked 1; the count pass marks 2 on those with
-// more than CAP candidates and lists them in next[] for the workgroup kernel.
-// kRowsList: every coarse row, listing those with more than CAP in next[].  The candidates go into a per-wavefront LDS hash set
-// (open addressing, CAP slots, so it never fills); each id that enters it is
-// also appended to a list.  The distinct ids are then ranked -- by counting,
-// each against all the others, when there are at most 64, else by a bitonic
-// sort in LDS -- and the set is emptied by clearing just their slots.  A
-// small CAP keeps the LDS per wavefront small, so that many rows are in
-// flight at once: the rows of a fine mesh's aggregates are a few dozen
-// candidates each.  FILL = false: ccnt[a]; FILL = true: ccol[crow[a] ...].
 template <int CAP>
 __device__ __forceinline__ uint32_t qhash(uint32_t c) {
     static_assert((CAP & (CAP - 1)) == 0 && CAP >= 64 && CAP <= 65536, "CAP: a power of two");
@@ -62,123 +54,337 @@ __device__ __forceinline__ uint32_t qhash(uint32_t c) {
     return (c * 2654435761u) >> (32 - bits);
 }
 
-// MODE: which rows a pass takes and what it does with the rows of more
-// than CAP candidates.
-enum { kRowsMark = 0, kRowsMarked = 1, kRowsList = 2 };
+// Column indices of the entries q0 .. q0 + U - 1 (the last entry again past
+// tot) of R rows numbered one after the other: off[r] the number of row r's
+// first entry, base[r] the column index of entry 0 counted back from it.  One
+// binary search finds the first entry's row; the others follow it, so a row
+// of U entries or more costs its lane two LDS reads, not a search per entry
+// (which kept these kernels bound by LDS reads).
+template <int R, int U, typename Off>
+__device__ __forceinline__ void walk_run(const Off *off, const int64_t *base, Off q0, Off tot,
+                                         int64_t (&at)[U]) {
+    int r = 0;  // the last row with off[r] <= q0 (it is not empty)
+#pragma unroll
+    for (int st = R / 2; st > 0; st >>= 1)
+        if (off[r + st] <= q0) r += st;
+    Off next = off[r + 1];
+    int64_t b = base[r];
+#pragma unroll
+    for (int k = 0; k < U; k++) {
+        const Off q = tot - q0 > (Off)k ? q0 + (Off)k : tot - 1;
+        while (q >= next) {  // tot is the last offset, so this ends
+            r++;
+            next = off[r + 1];
+            b = base[r];
+        }
+        at[k] = b + (int64_t)q;
+    }
+}
 
-template <bool FILL, int CAP, int MODE>
+// One row's candidates, put into an LDS hash set (open addressing) by a group
+// of G lanes; each id that enters is also appended to a list.  The members go
+// G at a time; their entries are numbered by a scan of the row lengths within
+// the group and dealt out evenly, U in a row per lane loaded together.  Most candidates repeat
+// an id the set already holds: a plain read of the slot comes before the
+// compare-and-swap.  Returns false when the row has LIM or more distinct ids
+// or more than MAXC candidates (the set is then only partly filled).
+template <int G, int CAP, int LIM>
+struct RowSet {
+    uint32_t tab[CAP];
+    uint32_t list[LIM + G];
+    int64_t base[G];     // column index of a member row's first entry, less its number
+    uint32_t off[G + 1];
+    uint32_t num;
+};
+
+template <int G>
+__device__ __forceinline__ uint32_t group_incl_scan(uint32_t x) {
+    if constexpr (G == 64) {
+        return wave_incl_scan(x);
+    } else {
+        static_assert(G == 16, "group_incl_scan: a DPP row or the wavefront");
+        x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);
+        x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);
+        x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);
+        x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);
+        return x;
+    }
+}
+
+template <int G, int CAP, int LIM, int U>
+__device__ __forceinline__ bool row_gather(RowSet<G, CAP, LIM> &S, int lane, int64_t a, int64_t m0,
+                                           int64_t m1, uint32_t maxc,
+                                           const int64_t *__restrict__ row_ptr,
+                                           const int32_t *__restrict__ col,
+                                           const int32_t *__restrict__ agg,
+                                           const int32_t *__restrict__ members) {
+    static_assert(LIM + G <= CAP, "every lane of the group may add an id past the limit");
+    constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+    volatile uint32_t *num = &S.num;
+    auto put = [&](int32_t cv) {
+        if (cv < 0 || (int64_t)cv == a) return;
+        const uint32_t key = (uint32_t)cv;
+        uint32_t h = qhash<CAP>(key);
+        for (;;) {  // at most LIM - 1 + G slots are ever taken, so this ends
+            uint32_t prev = S.tab[h];
+            if (prev == kEmpty) {
+                if (*num >= (uint32_t)LIM) break;  // over the limit already
+                prev = atomicCAS(&S.tab[h], kEmpty, key);
+                if (prev == kEmpty) {
+                    S.list[atomicAdd(&S.num, 1u)] = key;
+                    break;
+                }
+            }
+            if (prev == key) break;
+            h = (h + 1) & (CAP - 1);
+        }
+    };
+    uint32_t all = 0;
+    // a member of an aggregate with others has entries of its own
+    bool fits = m1 - m0 <= (int64_t)maxc;
+    for (int64_t c0 = m0; fits && c0 < m1; c0 += G) {
+        const int64_t i = c0 + lane;
+        int64_t rs = 0, d = 0;
+        if (i < m1) {
+            const int32_t v = members[i];
+            rs = row_ptr[v];
+            d = row_ptr[v + 1] - rs;
+        }
+        // each length clamped past the limit: the sums stay below 2^32
+        const uint32_t len = (uint32_t)min(d, (int64_t)maxc + 1);
+        const uint32_t incl = group_incl_scan<G>(len);
+        if (lane == 0) S.off[0] = 0u;
+        S.off[lane + 1] = incl;
+        S.base[lane] = rs - (int64_t)(incl - len);
+        wave_sync();
+        const uint32_t tot = S.off[G];
+        all += tot;
+        fits = all <= maxc && *num < (uint32_t)LIM;
+        if (fits) {
+            for (uint32_t c1 = 0; c1 < tot; c1 += (uint32_t)(G * U)) {
+                const uint32_t q0 = c1 + (uint32_t)(lane * U);
+                if (q0 < tot) {
+                    int64_t at[U];
+                    walk_run<G, U>(S.off, S.base, q0, tot, at);
+                    int32_t x[U];
+#pragma unroll
+                    for (int k = 0; k < U; k++) x[k] = col[at[k]];
+                    int32_t c[U];
+#pragma unroll
+                    for (int k = 0; k < U; k++) c[k] = agg[x[k]];
+#pragma unroll
+                    for (int k = 0; k < U; k++)
+                        if (q0 + (uint32_t)k < tot) put(c[k]);
+                }
+                // over the limit: the row goes on to the next path
+                if (c1 + (uint32_t)(G * U) < tot && *num >= (uint32_t)LIM) break;
+            }
+        }
+        wave_sync();  // the offsets are rewritten by the next chunk
+    }
+    return fits && *num < (uint32_t)LIM;
+}
+
+// Empties the set of a row: the slot of each listed id (its probe run holds
+// it exactly once; other lanes' clears only leave holes), or all of it.
+template <int G, int CAP, int LIM>
+__device__ __forceinline__ void row_clear(RowSet<G, CAP, LIM> &S, int lane, uint32_t m, bool whole) {
+    constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+    if (whole) {
+        for (int i = lane; i < CAP; i += G) S.tab[i] = kEmpty;
+    } else {
+        for (uint32_t i = (uint32_t)lane; i < m; i += (uint32_t)G) {
+            const uint32_t key = S.list[i];
+            uint32_t h = qhash<CAP>(key);
+            while (S.tab[h] != key) h = (h + 1) & (CAP - 1);
+            S.tab[h] = kEmpty;
+        }
+    }
+    wave_sync();
+    if (lane == 0) S.num = 0u;
+    wave_sync();
+}
+
+// The spare buffer that rows are written to while they are counted.  Its first
+// part has `per` entries for every member of a row; its second part takes the
+// rows that need more, wherever there is room: kSpareParts regions with a cursor each (one address for the whole
+// chip would serialise its atomics); a row's place, an index into the buffer,
+// is kept in the row's unused slot of the first part.
+constexpr int kSpareParts = 32;
+constexpr int kSpareLine = 32;  // words per cursor (one cache line)
+struct Spare {
+    int32_t *buf;       // [per * n] first part, then the cursors, then the regions
+    int64_t per;
+    uint32_t *cursor;   // [kSpareParts][kSpareLine], zero before the count pass
+    int64_t base;       // of region 0 in buf
+    uint32_t cap;       // entries of a region
+};
+
+// m entries for row a in region `part`: their index in buf, or -1 when the
+// region is full.  One thread calls it.
+__device__ __forceinline__ int64_t spare_take(const Spare &sp, uint32_t part, uint32_t m) {
+    part &= (uint32_t)(kSpareParts - 1);
+    uint32_t *c = sp.cursor + part * kSpareLine;
+    if (m > sp.cap || *(volatile uint32_t *)c > sp.cap - m) return -1;
+    const uint32_t at = atomicAdd(c, m);
+    return at <= sp.cap - m ? sp.base + (int64_t)part * sp.cap + at : -1;
+}
+
+// Notes the place of a row of class 3 with members from m0 on (per >= 2).
+__device__ __forceinline__ void spare_note(const Spare &sp, int64_t m0, int64_t at) {
+    sp.buf[m0 * sp.per] = (int32_t)(uint32_t)at;
+    sp.buf[m0 * sp.per + 1] = (int32_t)(at >> 32);
+}
+
+// Classes of coarse rows: where the row is after the count pass.
+constexpr uint8_t kInPlace = 0;  // first part of the spare buffer
+constexpr uint8_t kSecond = 1;   // the second path's, to be written
+constexpr uint8_t kBig = 2;      // a workgroup's or a giant row, to be written
+constexpr uint8_t kSpared = 3;   // second part of the spare buffer
+
+// First path: every coarse row, one group of G lanes each, its distinct ids
+// in a CAP-slot set (LIM - 1 of them at most, MAXC candidates).  What bounds
+// it is the chain of dependent loads of a row (member offsets, members, row
+// extents, columns, their labels) and the LDS steps after it, so rows in
+// flight count: 16 lanes per row and 128 slots where aggregates are small
+// (four rows per wavefront), a wavefront and 256 slots where a row has
+// hundreds of candidates.  Measured, counting and writing together, against one
+// wavefront per row with a set as large as its candidates (and a workgroup's
+// sort past 1024 of them), run twice: 2.5M rows of a 512-subdomain union
+// (level 0: 5 members, 40 candidates) 4.0 -> 0.87 ms; 14 000 rows of 40
+// members and 1000 candidates (27-point 83x71x97) 1.38 -> 0.06 ms.
+// ccnt[a], the ids in increasing order in the spare buffer and cls[a] (class 0
+// or 3); class `over` for a row it leaves to another path.
+template <int G, int CAP, int LIM, int U>
+__global__ __launch_bounds__(kBlock) void k_coarse_rows_group(
+    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+    const int32_t *__restrict__ agg, int64_t n_agg, const int64_t *__restrict__ moff,
+    const int32_t *__restrict__ members, uint32_t maxc, uint32_t *__restrict__ ccnt,
+    Spare sp, uint8_t *__restrict__ cls, uint8_t over) {
+    constexpr int kGroups = kBlock / G;
+    __shared__ RowSet<G, CAP, LIM> sets[kGroups];
+    const int grp = (int)threadIdx.x / G, lane = (int)threadIdx.x % G;
+    RowSet<G, CAP, LIM> &S = sets[grp];
+    row_clear(S, lane, 0u, true);
+    // each XCD takes one run of the rows of a step (the grid is a multiple of
+    // 8): neighbouring rows share columns and labels
+    const int64_t blk = (int64_t)(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    for (int64_t a = blk * kGroups + grp; a < n_agg; a += (int64_t)gridDim.x * kGroups) {
+        const int64_t m0 = moff[a], m1 = moff[a + 1];
+        const bool fits = row_gather<G, CAP, LIM, U>(S, lane, a, m0, m1, maxc, row_ptr, col, agg,
+                                                     members);
+        const uint32_t m = S.num;
+        int64_t at = m0 * sp.per;
+        if (fits && (int64_t)m > (m1 - m0) * sp.per) {
+            if (lane == 0) {
+                at = spare_take(sp, blockIdx.x, m);
+                S.base[0] = at;
+                if (at >= 0) spare_note(sp, m0, at);
+            }
+            wave_sync();
+            at = S.base[0];
+        }
+        const bool done = fits && at >= 0;
+        if (done) {
+            // rank each id by counting the smaller ones (ids are distinct)
+            int32_t *dst = sp.buf + at;
+            for (uint32_t i = (uint32_t)lane; i < m; i += (uint32_t)G) {
+                const uint32_t x = S.list[i];
+                uint32_t rank = 0;
+                for (uint32_t y = 0; y < m; y++) rank += S.list[y] < x ? 1u : 0u;
+                dst[rank] = (int32_t)x;
+            }
+        }
+        if (lane == 0) {
+            ccnt[a] = m;
+            cls[a] = !done ? over : at == m0 * sp.per ? kInPlace : kSpared;
+        }
+        row_clear(S, lane, m, !fits);
+    }
+}
+
+// The rows in the spare buffer to their place, 16 lanes each.
+__global__ __launch_bounds__(kBlock) void k_copy_rows(int64_t n_agg, const int64_t *__restrict__ moff,
+                                                      const int64_t *__restrict__ crow,
+                                                      const uint8_t *__restrict__ cls, Spare sp,
+                                                      int32_t *__restrict__ ccol) {
+    const int lane = (int)(threadIdx.x & 15u);
+    for (int64_t a = (int64_t)blockIdx.x * (kBlock / 16) + (threadIdx.x >> 4); a < n_agg;
+         a += (int64_t)gridDim.x * (kBlock / 16)) {
+        const int64_t d0 = crow[a], len = crow[a + 1] - d0;
+        const uint8_t k = cls[a];
+        if (len == 0 || (k != kInPlace && k != kSpared)) continue;
+        int64_t s0 = moff[a] * sp.per;
+        if (k == kSpared)
+            s0 = (int64_t)(uint32_t)sp.buf[s0] | (int64_t)((uint64_t)(uint32_t)sp.buf[s0 + 1] << 32);
+        for (int64_t i = lane; i < len; i += 16) ccol[d0 + i] = sp.buf[s0 + i];
+    }
+}
+
+// Second path, where there are more coarse ids than an LDS bitmap holds: the
+// rows of class 1, one wavefront each with a 1024-slot set.  (With fewer ids a
+// workgroup and a bitmap are faster: a set half full probes in long divergent
+// runs.  Level 0 of Chung-Lu 1M, 17 000 rows of 96 or more distinct ids: 800
+// us here.)  FILL = false: ccnt[a], and the row itself where the spare buffer
+// has room (class 3); class 2 to the rows with kWLim or more distinct ids or
+// more than kWCand candidates.  FILL = true: the rows still of class 1 to
+// ccol[crow[a] ...].  Up to 64 ids are ranked by
+// counting, more sorted in LDS.  Each wavefront reads 64 classes at a time,
+// so the rows of class 1 stay spread over all wavefronts.
+template <bool FILL>
 __global__ __launch_bounds__(kBlock) void k_coarse_rows_wave(
     const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
     const int32_t *__restrict__ agg, int64_t n_agg, const int64_t *__restrict__ moff,
     const int32_t *__restrict__ members, uint32_t *__restrict__ ccnt,
     const int64_t *__restrict__ crow, int32_t *__restrict__ ccol, uint8_t *__restrict__ cls,
-    int32_t *__restrict__ next, uint32_t *__restrict__ next_count) {
+    Spare sp) {
     constexpr uint32_t kEmpty = 0xFFFFFFFFu;
-    __shared__ uint32_t tabs[kWaves][CAP];
-    __shared__ uint32_t lists[kWaves][CAP];
-    __shared__ uint32_t nums[kWaves];
-    __shared__ uint32_t woffs[kWaves][65];
-    __shared__ int64_t wsts[kWaves][64];
-    const int wv = (int)(threadIdx.x >> 6);
-    uint32_t *tab = tabs[wv];
-    uint32_t *list = lists[wv];
-    const int lane = (int)(threadIdx.x & 63u);
+    __shared__ RowSet<64, kWSlots, kWLim> sets[kWaves];
+    const int wv = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63u);
+    RowSet<64, kWSlots, kWLim> &S = sets[wv];
     const int64_t nw = (int64_t)gridDim.x * kWaves;
-    for (int i = lane; i < CAP; i += 64) tab[i] = kEmpty;
-    if (lane == 0) nums[wv] = 0u;
-    wave_sync();
+    const int64_t w0 = (int64_t)blockIdx.x * kWaves + wv;
+    row_clear(S, lane, 0u, true);
     auto row = [&](const int64_t a) {
         const int64_t m0 = moff[a], m1 = moff[a + 1];
-        // candidates: stored entries of all members (each lane's part
-        // clamped: only "more than CAP" matters)
-        uint32_t cand = 0;
-        for (int64_t i = m0 + lane; i < m1; i += 64) {
-            const int32_t v = members[i];
-            const int64_t d = row_ptr[v + 1] - row_ptr[v];
-            cand = (uint32_t)min((int64_t)cand + d, (int64_t)1 << 24);
-        }
-        cand = group_sum<64>(cand);
-        if (!FILL && lane == 0) {
-            if (MODE == kRowsMark) {
-                cls[a] = cand > (uint32_t)CAP ? 1 : 0;
-            } else if (cand > (uint32_t)CAP) {
-                if (MODE == kRowsMarked) cls[a] = 2;
-                next[atomicAdd(next_count, 1u)] = (int32_t)a;
-            }
-        }
-        if (cand > (uint32_t)CAP) return;
-        // gather into the set: the members go 64 at a time; their entries
-        // are numbered by a wave scan of the row lengths and dealt out
-        // evenly, kWEdges per lane loaded together, each lane finding its
-        // row by binary search over the offsets
-        auto put = [&](int32_t cv) {
-            if (cv < 0 || (int64_t)cv == a) return;
-            const uint32_t key = (uint32_t)cv;
-            uint32_t h = qhash<CAP>(key);
-            for (;;) {  // the set has room for every candidate, so this ends
-                const uint32_t prev = atomicCAS(&tab[h], kEmpty, key);
-                if (prev == kEmpty) {
-                    list[atomicAdd(&nums[wv], 1u)] = key;
-                    break;
+        const bool done = row_gather<64, kWSlots, kWLim, kWEdges>(S, lane, a, m0, m1, kWCand,
+                                                                  row_ptr, col, agg, members);
+        const uint32_t m = S.num;
+        int32_t *dst = nullptr;
+        if (FILL) {
+            dst = ccol + crow[a];
+        } else {
+            int64_t at = -1;
+            if (lane == 0) {
+                ccnt[a] = m;
+                if (!done) {
+                    cls[a] = kBig;
+                } else if (m > 0) {
+                    at = spare_take(sp, (uint32_t)w0, m);
+                    if (at >= 0) {
+                        cls[a] = kSpared;
+                        spare_note(sp, m0, at);
+                    }
                 }
-                if (prev == key) break;
-                h = (h + 1) & (CAP - 1);
             }
-        };
-        uint32_t *woff = woffs[wv];
-        int64_t *wst = wsts[wv];
-        for (int64_t c0 = m0; c0 < m1; c0 += 64) {
-            const int64_t i = c0 + lane;
-            int64_t rs = 0;
-            uint32_t len = 0;  // a row of this path has at most CAP entries
-            if (i < m1) {
-                const int32_t v = members[i];
-                rs = row_ptr[v];
-                len = (uint32_t)(row_ptr[v + 1] - rs);
-            }
-            const uint32_t incl = wave_incl_scan(len);
-            const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-            woff[lane + 1] = incl;
-            wst[lane] = rs;
-            if (lane == 0) woff[0] = 0u;
-            wave_sync();
-            for (uint32_t q0 = (uint32_t)lane; q0 < tot; q0 += 64u * kWEdges) {
-                int32_t x[kWEdges];
-#pragma unroll
-                for (int k = 0; k < kWEdges; k++) {
-                    uint32_t q = q0 + 64u * (uint32_t)k;
-                    if (q >= tot) q = tot - 1;  // a valid entry; its result is not used
-                    int r = 0;  // the last row with woff[r] <= q (it is not empty)
-#pragma unroll
-                    for (int st = 32; st > 0; st >>= 1)
-                        if (woff[r + st] <= q) r += st;
-                    x[k] = col[wst[r] + (int64_t)(q - woff[r])];
-                }
-                int32_t c[kWEdges];
-#pragma unroll
-                for (int k = 0; k < kWEdges; k++) c[k] = agg[x[k]];
-#pragma unroll
-                for (int k = 0; k < kWEdges; k++)
-                    if (q0 + 64u * (uint32_t)k < tot) put(c[k]);
-            }
-            wave_sync();  // the offsets are rewritten by the next chunk
+            const int lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+            const int hi = __builtin_amdgcn_readfirstlane((int)(at >> 32));
+            if (hi >= 0) dst = sp.buf + (((int64_t)hi << 32) | (uint32_t)lo);
         }
-        wave_sync();
-        const uint32_t m = nums[wv];
-        if (m <= 64) {
-            // rank each id by counting the smaller ones (ids are distinct)
-            if (FILL && (uint32_t)lane < m) {
-                const uint32_t x = list[lane];
+        if (dst && m <= 64) {
+            if ((uint32_t)lane < m) {
+                const uint32_t x = S.list[lane];
                 uint32_t rank = 0;
-                for (uint32_t y = 0; y < m; y++) rank += list[y] < x ? 1u : 0u;
-                ccol[crow[a] + rank] = (int32_t)x;
+                for (uint32_t y = 0; y < m; y++) rank += S.list[y] < x ? 1u : 0u;
+                dst[rank] = (int32_t)x;
             }
-        } else if (FILL) {
-            // bitonic sort of a copy in the set's table, then the table
-            // is cleared whole
+        } else if (dst) {
+            // bitonic sort of a copy in the set's table, then the table is
+            // cleared whole
+            uint32_t *tab = S.tab;
             uint32_t P = 1;
             while (P < m) P <<= 1;
-            for (uint32_t i = lane; i < P; i += 64) tab[i] = i < m ? list[i] : kEmpty;
+            for (uint32_t i = lane; i < P; i += 64) tab[i] = i < m ? S.list[i] : kEmpty;
             wave_sync();
             for (uint32_t k = 2; k <= P; k <<= 1) {
                 for (uint32_t jj = k >> 1; jj > 0; jj >>= 1) {
@@ -196,66 +402,58 @@ __global__ __launch_bounds__(kBlock) void k_coarse_rows_wave(
                     wave_sync();
                 }
             }
-            for (uint32_t i = lane; i < m; i += 64) ccol[crow[a] + i] = (int32_t)tab[i];
+            for (uint32_t i = lane; i < m; i += 64) dst[i] = (int32_t)tab[i];
         }
         wave_sync();
-        // empty the set again
-        if (FILL && m > 64) {
-            for (int i = lane; i < CAP; i += 64) tab[i] = kEmpty;
-        } else {
-            // clear the slot of each distinct id (its probe run holds it
-            // exactly once; other lanes' clears only leave holes)
-            for (uint32_t i = lane; i < m; i += 64) {
-                const uint32_t key = list[i];
-                uint32_t h = qhash<CAP>(key);
-                while (tab[h] != key) h = (h + 1) & (CAP - 1);
-                tab[h] = kEmpty;
-            }
-        }
-        if (!FILL && lane == 0) ccnt[a] = m;
-        wave_sync();
-        if (lane == 0) nums[wv] = 0u;
-        wave_sync();
+        row_clear(S, lane, m, !done || (dst && m > 64));
     };
-    const int64_t w0 = (int64_t)blockIdx.x * kWaves + wv;
-    if (MODE != kRowsMarked) {
-        for (int64_t a = w0; a < n_agg; a += nw) row(a);
-    } else {
-        // the wavefront's rows w0, w0 + nw, ...: 64 marks read at once (2:
-        // marked by this kernel's count pass), so the marked rows stay
-        // spread over all wavefronts
-        for (int64_t j0 = 0; w0 + j0 * nw < n_agg; j0 += 64) {
-            const int64_t v = w0 + (j0 + lane) * nw;
-            const bool mine = v < n_agg && cls[v] >= 1;
-            uint64_t mask = __ballot(mine);
-            while (mask) {
-                const int r = __ffsll((unsigned long long)mask) - 1;
-                mask &= mask - 1;
-                row(w0 + (j0 + r) * nw);
-            }
+    for (int64_t j0 = 0; w0 + j0 * nw < n_agg; j0 += 64) {
+        const int64_t v = w0 + (j0 + lane) * nw;
+        const bool mine = v < n_agg && cls[v] == kSecond;
+        uint64_t mask = __ballot(mine);
+        while (mask) {
+            const int r = __ffsll((unsigned long long)mask) - 1;
+            mask &= mask - 1;
+            row(w0 + (j0 + r) * nw);
         }
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_member_count(int64_t n, const int32_t *__restrict__ agg,
-                                                         uint32_t *__restrict__ cnt) {
-    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
-         v += (int64_t)gridDim.x * kBlock) {
-        const int32_t a = agg[v];
-        if (a >= 0) atomicAdd(&cnt[a], 1u);
+// cnt[a] = members of aggregate a; rank[v] = v's place among them (in no
+// particular order).  Consecutive vertices often share their aggregate: the
+// first lane of each run of equal labels adds for the run, so one atomic
+// serves it, and the scatter below needs none (27-point 83x71x97, count and
+// scatter: 72 -> 11 us; 15M vertices of small cubes 860 -> 275 us).
+__global__ __launch_bounds__(kBlock) void k_member_rank(int64_t n, const int32_t *__restrict__ agg,
+                                                        uint32_t *__restrict__ cnt,
+                                                        int32_t *__restrict__ rank) {
+    const int lane = (int)(threadIdx.x & 63u);
+    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    // whole wavefronts stay in the loop together (the last chunk's tail lanes
+    // carry no aggregate)
+    for (int64_t v0 = (int64_t)blockIdx.x * kBlock + (threadIdx.x - lane); v0 < n; v0 += stride) {
+        const int64_t v = v0 + lane;
+        const int32_t a = v < n ? agg[v] : -1;
+        const int32_t prev = (int32_t)from_prev((uint32_t)a);
+        const uint64_t heads = __ballot(lane == 0 || a != prev);
+        const int start = 63 - __clzll((long long)(heads & (~0ull >> (63 - lane))));
+        const uint64_t later = lane == 63 ? 0ull : heads >> (lane + 1);
+        const int len = later ? __ffsll((unsigned long long)later) : 64 - lane;
+        uint32_t base = 0;
+        if (start == lane && a >= 0) base = atomicAdd(&cnt[a], (uint32_t)len);
+        base = (uint32_t)__shfl((int)base, start, 64);
+        if (v < n) rank[v] = (int32_t)(base + (uint32_t)(lane - start));
     }
 }
 
 __global__ __launch_bounds__(kBlock) void k_member_scatter(int64_t n, const int32_t *__restrict__ agg,
                                                            const int64_t *__restrict__ moff,
-                                                           uint32_t *__restrict__ cursor,
+                                                           const int32_t *__restrict__ rank,
                                                            int32_t *__restrict__ members) {
     for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
          v += (int64_t)gridDim.x * kBlock) {
         const int32_t a = agg[v];
-        if (a < 0) continue;
-        const uint32_t pos = atomicAdd(&cursor[a], 1u);
-        members[moff[a] + pos] = (int32_t)v;
+        if (a >= 0) members[moff[a] + rank[v]] = (int32_t)v;
     }
 }
 
@@ -296,14 +494,10 @@ __device__ __forceinline__ void block_minmax(int32_t *mn, int32_t *mx, int32_t *
 // Exclusive prefix of x over the workgroup in thread order; *total gets the
 // sum.  All threads must call it.
 __device__ __forceinline__ uint32_t block_excl(uint32_t x, uint32_t *scratch, uint32_t *total) {
-    const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x >> 6);
-    uint32_t incl = x;
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = (uint32_t)__shfl_up((int)incl, off, 64);
-        if (lane >= off) incl += y;
-    }
+    const int wave = (int)(threadIdx.x >> 6);
+    const uint32_t incl = wave_incl_scan(x);
     __syncthreads();
-    if (lane == 63) scratch[wave] = incl;
+    if ((threadIdx.x & 63u) == 63u) scratch[wave] = incl;
     __syncthreads();
     uint32_t before = 0, t = 0;
     for (int w = 0; w < kWaves; w++) {
@@ -314,11 +508,9 @@ __device__ __forceinline__ uint32_t block_excl(uint32_t x, uint32_t *scratch, ui
     return before + incl - x;
 }
 
-// Exclusive prefix of x over the workgroup in thread order (64-bit); *total
-// gets the sum.  All threads must call it.
-__device__ __forceinline__ unsigned long long block_excl64(unsigned long long x,
-                                                           unsigned long long *scratch,
-                                                           unsigned long long *total) {
+__device__ __forceinline__ unsigned long long block_excl(unsigned long long x,
+                                                         unsigned long long *scratch,
+                                                         unsigned long long *total) {
     const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x >> 6);
     unsigned long long incl = x;
     for (int off = 1; off < 64; off <<= 1) {
@@ -337,281 +529,310 @@ __device__ __forceinline__ unsigned long long block_excl64(unsigned long long x,
     return before + incl - x;
 }
 
-// LDS of walk_members: the entry offsets and row starts of one chunk of
-// kBlock members.
+// LDS of walk_members: the entry offsets of one chunk of kBlock members, and
+// each member row's start less its offset.  Off: 32 bits unless the graph has
+// 2^32 entries or more.
+template <typename Off>
 struct WalkLds {
-    unsigned long long off[kBlock + 1];
-    int64_t start[kBlock];
-    unsigned long long scan[kWaves];
+    Off off[kBlock + 1];
+    int64_t base[kBlock];
+    Off scan[kWaves];
 };
 
 // f(c) for the coarse id c = agg[col[j]] of every entry j of every member of
 // an aggregate (members[m0 .. m1)).  The members go in chunks of kBlock; the
 // chunk's entries are numbered through a prefix sum of the row lengths and
-// dealt out evenly, kWEdges per thread loaded together, each finding its
-// row by binary search over the offsets.  Rows of any length mix keep every
-// thread equally busy.  All threads must call it.
-template <typename F>
+// dealt out evenly, kWEdges in a row per thread loaded together.  Rows of any
+// length mix keep every thread equally busy.  Several workgroups can share
+// one chunk: `part` of `parts` takes every parts-th block of its entries.
+// All threads must call it.
+template <typename Off, typename F>
 __device__ __forceinline__ void walk_members(const int64_t *__restrict__ row_ptr,
                                              const int32_t *__restrict__ col,
                                              const int32_t *__restrict__ agg,
                                              const int32_t *__restrict__ members, int64_t m0,
-                                             int64_t m1, WalkLds &w, F f) {
+                                             int64_t m1, WalkLds<Off> &w, int part, int parts,
+                                             F f) {
     const int tid = (int)threadIdx.x;
     for (int64_t c0 = m0; c0 < m1; c0 += kBlock) {
         const int64_t i = c0 + tid;
         int64_t rs = 0;
-        unsigned long long len = 0;
+        Off len = 0;
         if (i < m1) {
             const int32_t v = members[i];
             rs = row_ptr[v];
-            len = (unsigned long long)(row_ptr[v + 1] - rs);
+            len = (Off)(row_ptr[v + 1] - rs);
         }
-        unsigned long long tot;
-        const unsigned long long ex = block_excl64(len, w.scan, &tot);
+        Off tot;
+        const Off ex = block_excl(len, w.scan, &tot);
         w.off[tid] = ex;
-        w.start[tid] = rs;
+        w.base[tid] = rs - (int64_t)ex;
         if (tid == 0) w.off[kBlock] = tot;
         __syncthreads();
-        for (unsigned long long q0 = tid; q0 < tot; q0 += (unsigned long long)kBlock * kWEdges) {
-            int32_t x[kWEdges];
+        for (Off c1 = (Off)part * (kBlock * kWEdges); c1 < tot;) {
+            const Off q0 = c1 + (Off)(tid * kWEdges);
+            if (q0 < tot && q0 >= c1) {
+                int64_t at[kWEdges];
+                walk_run<kBlock, kWEdges>(w.off, w.base, q0, tot, at);
+                int32_t x[kWEdges];
 #pragma unroll
-            for (int k = 0; k < kWEdges; k++) {
-                unsigned long long q = q0 + (unsigned long long)k * kBlock;
-                if (q >= tot) q = tot - 1;  // a valid entry; its result is not used
-                // the last row r with off[r] <= q (it is not empty: off[r + 1] > q)
-                int lo = 0, hi = kBlock;
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (w.off[mid] <= q) lo = mid;
-                    else hi = mid;
-                }
-                x[k] = col[w.start[lo] + (int64_t)(q - w.off[lo])];
+                for (int k = 0; k < kWEdges; k++) x[k] = col[at[k]];
+                int32_t c[kWEdges];
+#pragma unroll
+                for (int k = 0; k < kWEdges; k++) c[k] = agg[x[k]];
+#pragma unroll
+                for (int k = 0; k < kWEdges; k++)
+                    if (tot - q0 > (Off)k) f(c[k]);
             }
-            int32_t c[kWEdges];
-#pragma unroll
-            for (int k = 0; k < kWEdges; k++) c[k] = agg[x[k]];
-#pragma unroll
-            for (int k = 0; k < kWEdges; k++)
-                if (q0 + (unsigned long long)k * kBlock < tot) f(c[k]);
+            const Off step = (Off)(kBlock * kWEdges) * (Off)parts;
+            if (tot - c1 <= step) break;  // c1 does not wrap
+            c1 += step;
         }
         __syncthreads();  // the offsets are rewritten by the next chunk
     }
 }
 
-// FILL = false: ccnt[a] = number of distinct coarse neighbours of row a.
-// FILL = true:  ccol[crow[a] ...] = those neighbours in increasing order.
-// The listed (large) coarse rows big[0 .. *big_count), one workgroup each.
-template <bool FILL>
-__global__ __launch_bounds__(kBlock) void k_coarse_rows(const int64_t *__restrict__ row_ptr,
-                                                        const int32_t *__restrict__ col,
-                                                        const int32_t *__restrict__ agg,
-                                                        int64_t n_agg,
-                                                        const int64_t *__restrict__ moff,
-                                                        const int32_t *__restrict__ members,
-                                                        uint32_t *__restrict__ ccnt,
-                                                        const int64_t *__restrict__ crow,
-                                                        int32_t *__restrict__ ccol,
-                                                        const int32_t *__restrict__ big,
-                                                        const uint32_t *__restrict__ big_count,
-                                                        uint32_t *__restrict__ gmeta) {
-    static_assert(kBitWords >= kQCap, "the sort buffer is the bitmap");
-    __shared__ uint32_t buf[kBitWords];
+// The set bits of words [w0, w1) of buf, which stand for the ids from `id0`
+// on, in increasing order to dst (nullptr: only counted).  Every thread takes
+// a run of words, so one prefix sum numbers them all (runs of odd length:
+// their LDS reads spread over the banks).  All threads must call it.
+__device__ __forceinline__ uint32_t emit_bits(const uint32_t *buf, int w0, int w1, int64_t id0,
+                                              int32_t *dst, uint32_t *scan_s) {
+    const int run = ((w1 - w0 + kBlock - 1) / kBlock) | 1;
+    const int b = min(w1, w0 + (int)threadIdx.x * run), e = min(w1, b + run);
+    uint32_t cnt = 0;
+    for (int i = b; i < e; i++) cnt += (uint32_t)__popc(buf[i]);
+    uint32_t tot;
+    uint32_t pos = block_excl(cnt, scan_s, &tot);
+    if (dst) {
+        for (int i = b; i < e; i++) {
+            uint32_t word = buf[i];
+            while (word) {
+                const int bit = __ffs(word) - 1;
+                word &= word - 1;
+                dst[pos++] = (int32_t)(id0 + (int64_t)i * 32 + bit);
+            }
+        }
+    }
+    return tot;
+}
+
+// The rows of class 2, one workgroup each.  A workgroup owns the rows
+// blockIdx.x, blockIdx.x + gridDim.x, ... and reads kBlock of their classes at
+// a time.
+// The row's ids are collected in an LDS bitmap of `words` words (all coarse
+// ids, or kBitWords of them at a time); its size, and so the workgroups a
+// compute unit holds, follows the number of coarse ids.
+// FILL = false: ccnt[a], and the row itself where one window holds every
+// coarse id and the spare buffer has room (class 3).
+// FILL = true: the rows still of class 2 to ccol[crow[a] ...].
+template <bool FILL, typename Off>
+__global__ __launch_bounds__(kBlock) void k_coarse_rows(
+    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+    const int32_t *__restrict__ agg, int64_t n_agg, const int64_t *__restrict__ moff,
+    const int32_t *__restrict__ members, uint32_t *__restrict__ ccnt,
+    const int64_t *__restrict__ crow, int32_t *__restrict__ ccol, uint8_t *__restrict__ cls,
+    uint32_t *__restrict__ gmeta, uint32_t slots, int words, Spare sp) {
+    extern __shared__ uint32_t buf[];
     __shared__ unsigned long long red[kWaves];
     __shared__ uint32_t scan_s[kWaves];
-    __shared__ uint32_t fill_s;
-    __shared__ WalkLds walk;
+    __shared__ WalkLds<Off> walk;
     __shared__ int32_t range_s[2 * kWaves];
     __shared__ uint32_t giant_s;
+    __shared__ int64_t at_s;
     const int tid = (int)threadIdx.x;
-    const int64_t nbig = *big_count;
-    for (int64_t bi = blockIdx.x; bi < nbig; bi += gridDim.x) {
-        const int64_t a = big[bi];
+    const int64_t window = 32 * (int64_t)words;
+    auto row = [&](const int64_t a) {
         const int64_t m0 = moff[a], m1 = moff[a + 1];
-        unsigned long long cand = 0;
-        for (int64_t i = m0 + tid; i < m1; i += kBlock) {
-            const int32_t v = members[i];
-            cand += (unsigned long long)(row_ptr[v + 1] - row_ptr[v]);
-        }
-        cand = block_sum(cand, red);
-        if (gmeta && cand > (unsigned long long)kGiantCand) {
-            // a giant row: the count pass claims a bitmap slot for it (the
-            // slot kernels then count and write it); without a free slot it
-            // stays here
-            if (tid == 0) {
-                uint32_t taken = 0;
-                if (!FILL) {
-                    const uint32_t k = atomicAdd(&gmeta[3 * kGiantSlots], 1u);
-                    if (k < (uint32_t)kGiantSlots) {
-                        gmeta[k] = (uint32_t)a;
-                        taken = 1;
-                    }
-                } else {
-                    const uint32_t cnt = min(gmeta[3 * kGiantSlots], (uint32_t)kGiantSlots);
-                    for (uint32_t k = 0; k < cnt; k++) taken |= gmeta[k] == (uint32_t)a ? 1u : 0u;
-                }
-                giant_s = taken;
+        if (gmeta) {
+            unsigned long long cand = 0;
+            for (int64_t i = m0 + tid; i < m1; i += kBlock) {
+                const int32_t v = members[i];
+                cand += (unsigned long long)(row_ptr[v + 1] - row_ptr[v]);
             }
-            __syncthreads();
-            if (giant_s) continue;  // uniform; the next block_sum synchronises first
+            cand = block_sum(cand, red);
+            if (cand > (unsigned long long)kGiantCand) {
+                // a giant row: the count pass claims a bitmap slot for it (the
+                // slot kernels then count and write it); without a free slot
+                // it stays here
+                if (tid == 0) {
+                    uint32_t taken = 0;
+                    if (!FILL) {
+                        const uint32_t k = atomicAdd(&gmeta[3 * kGiantSlots], 1u);
+                        if (k < slots) {
+                            gmeta[k] = (uint32_t)a;
+                            taken = 1;
+                        }
+                    } else {
+                        const uint32_t cnt = min(gmeta[3 * kGiantSlots], slots);
+                        for (uint32_t k = 0; k < cnt; k++) taken |= gmeta[k] == (uint32_t)a ? 1u : 0u;
+                    }
+                    giant_s = taken;
+                }
+                __syncthreads();
+                if (giant_s) return;  // uniform; the next block_sum synchronises first
+            }
         }
-        uint32_t distinct = 0;
-        if (cand <= (unsigned long long)kQCap) {
-            // gather the candidate ids (self excluded) into LDS
-            if (tid == 0) fill_s = 0;
+        // bitmap windows over the coarse id space.  The first window also
+        // finds the smallest and largest candidate; later windows cover only
+        // that range, and each window emits only the words inside it.  In a
+        // disjoint union the candidates lie in the row's own graph, so a big
+        // row never sweeps the coarse ids of the other graphs.
+        uint32_t run = 0;
+        int64_t hi = n_agg;
+        int32_t tmin = INT32_MAX, tmax = -1;
+        bool first = true;
+        for (int64_t lo = 0; lo < hi;) {
+            for (int i = tid; i < words; i += kBlock) buf[i] = 0u;
             __syncthreads();
-            walk_members(row_ptr, col, agg, members, m0, m1, walk, [&](int32_t c) {
-                if (c >= 0 && (int64_t)c != a) buf[atomicAdd(&fill_s, 1u)] = (uint32_t)c;
+            walk_members(row_ptr, col, agg, members, m0, m1, walk, 0, 1, [&](int32_t c) {
+                if (c < 0 || (int64_t)c == a) return;
+                if (first) {
+                    tmin = min(tmin, c);
+                    tmax = max(tmax, c);
+                }
+                const int64_t o = (int64_t)c - lo;
+                if (o < 0 || o >= window) return;
+                const uint32_t bit = 1u << (o & 31);
+                if (!(buf[o >> 5] & bit)) atomicOr(&buf[o >> 5], bit);
             });
             __syncthreads();
-            const uint32_t m = fill_s;
-            uint32_t P = 1;
-            while (P < m) P <<= 1;
-            for (uint32_t i = m + tid; i < P; i += kBlock) buf[i] = 0xFFFFFFFFu;
-            __syncthreads();
-            // bitonic sort of buf[0..P)
-            for (uint32_t k = 2; k <= P; k <<= 1) {
-                for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-                    for (uint32_t i = tid; i < P; i += kBlock) {
-                        const uint32_t ixj = i ^ j;
-                        if (ixj > i) {
-                            const uint32_t x = buf[i], y = buf[ixj];
-                            const bool up = (i & k) == 0;
-                            if ((x > y) == up) {
-                                buf[i] = y;
-                                buf[ixj] = x;
+            if (first) {
+                block_minmax(&tmin, &tmax, range_s);
+                hi = (int64_t)tmax + 1;  // no candidate at all: tmax = -1 ends the sweep
+            }
+            const int64_t e_lo = max(lo, (int64_t)tmin);
+            const int64_t e_hi = min(lo + window, hi);
+            if (e_lo < e_hi) {
+                const int w0 = (int)((e_lo - lo) >> 5), w1 = (int)((e_hi - lo + 31) >> 5);
+                int32_t *dst = FILL ? ccol + crow[a] + run : nullptr;
+                uint32_t tot = 0;
+                if (!FILL) {
+                    // its size first, then a place for it
+                    tot = emit_bits(buf, w0, w1, lo, nullptr, scan_s);
+                    if (window >= n_agg) {
+                        if (tid == 0) {
+                            at_s = spare_take(sp, (uint32_t)blockIdx.x, tot);
+                            if (at_s >= 0) {
+                                cls[a] = kSpared;
+                                spare_note(sp, m0, at_s);
                             }
                         }
+                        __syncthreads();
+                        if (at_s >= 0) dst = sp.buf + at_s;
                     }
-                    __syncthreads();
                 }
-            }
-            // distinct values, in order
-            uint32_t run = 0;
-            for (uint32_t c0 = 0; c0 < m; c0 += kBlock) {
-                const uint32_t i = c0 + tid;
-                const bool first = i < m && (i == 0 || buf[i] != buf[i - 1]);
-                uint32_t tot;
-                const uint32_t pos = block_excl(first ? 1u : 0u, scan_s, &tot);
-                if (FILL && first) ccol[crow[a] + run + pos] = (int32_t)buf[i];
+                if (dst) tot = emit_bits(buf, w0, w1, lo, dst, scan_s);
                 run += tot;
             }
-            distinct = run;
-        } else {
-            // bitmap windows over the coarse id space
-            uint32_t run = 0;
-            // The first window also finds the smallest and largest candidate;
-            // later windows cover only that range, and each window emits
-            // only the words inside it.  In a disjoint union the candidates
-            // lie in the row's own graph, so a big row never sweeps the
-            // coarse ids of the other graphs.
-            int64_t hi = n_agg;
-            int32_t tmin = INT32_MAX, tmax = -1;
-            bool first = true;
-            for (int64_t lo = 0; lo < hi;) {
-                for (int i = tid; i < kBitWords; i += kBlock) buf[i] = 0u;
-                __syncthreads();
-                walk_members(row_ptr, col, agg, members, m0, m1, walk, [&](int32_t c) {
-                    if (c < 0 || (int64_t)c == a) return;
-                    if (first) {
-                        tmin = min(tmin, c);
-                        tmax = max(tmax, c);
-                    }
-                    const int64_t o = (int64_t)c - lo;
-                    if (o >= 0 && o < kQWindow) atomicOr(&buf[o >> 5], 1u << (o & 31));
-                });
-                __syncthreads();
-                if (first) {
-                    block_minmax(&tmin, &tmax, range_s);
-                    hi = (int64_t)tmax + 1;  // no candidate at all: tmax = -1 ends the sweep
-                }
-                // emit the set ids of this window in increasing order
-                const int64_t e_lo = max(lo, (int64_t)tmin);
-                const int64_t e_hi = min(lo + kQWindow, hi);
-                if (e_lo < e_hi) {
-                    const int w0 = (int)((e_lo - lo) >> 5), w1 = (int)((e_hi - lo + 31) >> 5);
-                    for (int c0 = w0; c0 < w1; c0 += kBlock) {
-                        const int wi = c0 + tid;
-                        const uint32_t word = wi < w1 ? buf[wi] : 0u;
-                        uint32_t tot;
-                        const uint32_t pos = block_excl((uint32_t)__popc(word), scan_s, &tot);
-                        if (FILL) {
-                            uint32_t wv = word, k = 0;
-                            while (wv) {
-                                const int bit = __ffs(wv) - 1;
-                                wv &= wv - 1;
-                                ccol[crow[a] + run + pos + k] =
-                                    (int32_t)(lo + (int64_t)wi * 32 + bit);
-                                k++;
-                            }
-                        }
-                        run += tot;
-                    }
-                }
-                __syncthreads();
-                int64_t next = lo + kQWindow;
-                if (first) {
-                    if ((int64_t)tmin > next) next = tmin;
-                    first = false;
-                }
-                lo = next;
+            __syncthreads();
+            int64_t next = lo + window;
+            if (first) {
+                if ((int64_t)tmin > next) next = tmin;
+                first = false;
             }
-            distinct = run;
+            lo = next;
         }
-        if (!FILL && tid == 0) ccnt[a] = distinct;
+        if (!FILL && tid == 0) ccnt[a] = run;
         __syncthreads();
+    };
+    __shared__ uint64_t marks[kWaves];
+    for (int64_t j0 = 0; (int64_t)blockIdx.x + j0 * gridDim.x < n_agg; j0 += kBlock) {
+        const int64_t v = (int64_t)blockIdx.x + (j0 + tid) * gridDim.x;
+        const uint64_t mine = __ballot(v < n_agg && cls[v] == kBig);
+        __syncthreads();  // the marks before are read, and no row changes its class yet
+        if ((tid & 63) == 0) marks[tid >> 6] = mine;
+        __syncthreads();
+        for (int w = 0; w < kWaves; w++) {
+            uint64_t mask = marks[w];
+            while (mask) {
+                const int r = __ffsll((unsigned long long)mask) - 1;
+                mask &= mask - 1;
+                row((int64_t)blockIdx.x + (j0 + w * 64 + r) * gridDim.x);
+            }
+        }
     }
 }
 
 // Giant rows, one bitmap slot each (gmeta: rows [0, S), smallest ids
-// [S, 2S), largest ids [2S, 3S), rows claimed [3S]).  Slot blockIdx.y; the
-// workgroups of a slot share its members in chunks of kBlock and set the bit
-// of every candidate (a plain read first skips bits already set: most
-// candidates of a giant row repeat).
+// [S, 2S), largest ids [2S, 3S), rows claimed [3S]).  Slots blockIdx.y,
+// blockIdx.y + gridDim.y, ...; the workgroups of a slot share its members in chunks of kBlock, kGiantParts
+// workgroups to a chunk (a chunk that holds hubs has a hundred times the
+// entries of another).  Where the
+// coarse ids fit an LDS bitmap (words > 0) a workgroup collects its share
+// there and adds its set words to the slot's once; else it sets every bit in
+// the slot (a plain read first skips bits it sees already set).  Most
+// candidates of a giant row repeat: a row of 2.3 million candidates held 6000
+// distinct ids, and setting each in global memory put every workgroup's
+// atomics on the same few lines.
+constexpr int kGiantParts = 8;
+template <typename Off>
 __global__ __launch_bounds__(kBlock) void k_giant_set(const int64_t *__restrict__ row_ptr,
                                                       const int32_t *__restrict__ col,
                                                       const int32_t *__restrict__ agg,
                                                       const int64_t *__restrict__ moff,
                                                       const int32_t *__restrict__ members,
-                                                      uint32_t *__restrict__ gbits, int64_t words,
-                                                      uint32_t *__restrict__ gmeta) {
-    __shared__ WalkLds walk;
+                                                      uint32_t *__restrict__ gbits, int64_t stride,
+                                                      uint32_t *__restrict__ gmeta, uint32_t slots,
+                                                      int words) {
+    extern __shared__ uint32_t buf[];
+    __shared__ WalkLds<Off> walk;
     __shared__ int32_t range_s[2 * kWaves];
-    const int slot = (int)blockIdx.y;
-    if ((uint32_t)slot >= min(gmeta[3 * kGiantSlots], (uint32_t)kGiantSlots)) return;
-    const int64_t a = gmeta[slot];
-    const int64_t m0 = moff[a], m1 = moff[a + 1];
-    uint32_t *bits = gbits + (int64_t)slot * words;
-    int32_t tmin = INT32_MAX, tmax = -1;
-    for (int64_t c0 = m0 + (int64_t)blockIdx.x * kBlock; c0 < m1;
-         c0 += (int64_t)gridDim.x * kBlock) {
-        walk_members(row_ptr, col, agg, members, c0, min(c0 + kBlock, m1), walk, [&](int32_t c) {
+    const int used = (int)min(gmeta[3 * kGiantSlots], slots);
+    const int part = (int)(blockIdx.x % kGiantParts);
+    for (int slot = (int)blockIdx.y; slot < used; slot += (int)gridDim.y) {
+        const int64_t a = gmeta[slot];
+        const int64_t m0 = moff[a], m1 = moff[a + 1];
+        if (m0 + (int64_t)(blockIdx.x / kGiantParts) * kBlock >= m1) continue;
+        uint32_t *bits = gbits + (int64_t)slot * stride;
+        for (int i = (int)threadIdx.x; i < words; i += kBlock) buf[i] = 0u;
+        __syncthreads();
+        int32_t tmin = INT32_MAX, tmax = -1;
+        auto set = [&](int32_t c, uint32_t *to) {
             if (c < 0 || (int64_t)c == a) return;
             tmin = min(tmin, c);
             tmax = max(tmax, c);
             const uint32_t bit = 1u << (c & 31);
-            if (!(bits[c >> 5] & bit)) atomicOr(&bits[c >> 5], bit);
-        });
-    }
-    block_minmax(&tmin, &tmax, range_s);
-    if (threadIdx.x == 0 && tmax >= 0) {
-        atomicMin((int32_t *)&gmeta[kGiantSlots + slot], tmin);
-        atomicMax((int32_t *)&gmeta[2 * kGiantSlots + slot], tmax);
+            if (!(to[c >> 5] & bit)) atomicOr(&to[c >> 5], bit);
+        };
+        for (int64_t c0 = m0 + (int64_t)(blockIdx.x / kGiantParts) * kBlock; c0 < m1;
+             c0 += (int64_t)(gridDim.x / kGiantParts) * kBlock) {
+            const int64_t c1 = min(c0 + kBlock, m1);
+            if (words)
+                walk_members(row_ptr, col, agg, members, c0, c1, walk, part, kGiantParts,
+                             [&](int32_t c) { set(c, buf); });
+            else
+                walk_members(row_ptr, col, agg, members, c0, c1, walk, part, kGiantParts,
+                             [&](int32_t c) { set(c, bits); });
+        }
+        block_minmax(&tmin, &tmax, range_s);
+        if (tmax >= 0) {
+            if (words)
+                for (int i = (tmin >> 5) + (int)threadIdx.x; i <= tmax >> 5; i += kBlock)
+                    if (buf[i]) atomicOr(&bits[i], buf[i]);
+            if (threadIdx.x == 0) {
+                atomicMin((int32_t *)&gmeta[kGiantSlots + slot], tmin);
+                atomicMax((int32_t *)&gmeta[2 * kGiantSlots + slot], tmax);
+            }
+        }
+        __syncthreads();  // the bitmap is cleared for the next slot
     }
 }
 
 // One workgroup per giant slot: FILL = false: ccnt[a] = the bits set;
-// FILL = true: their ids in increasing order to ccol[crow[a] ...].
+// FILL = true: their ids in increasing order to ccol[crow[a] ...].  Each
+// thread takes kRun words in a row, so a prefix sum covers kRun * kBlock.
 template <bool FILL>
 __global__ __launch_bounds__(kBlock) void k_giant_emit(const uint32_t *__restrict__ gbits,
                                                        int64_t words,
                                                        const uint32_t *__restrict__ gmeta,
-                                                       uint32_t *__restrict__ ccnt,
+                                                       uint32_t slots, uint32_t *__restrict__ ccnt,
                                                        const int64_t *__restrict__ crow,
                                                        int32_t *__restrict__ ccol) {
+    constexpr int kRun = 8;
     __shared__ uint32_t scan_s[kWaves];
     const int slot = (int)blockIdx.x;
-    if ((uint32_t)slot >= min(gmeta[3 * kGiantSlots], (uint32_t)kGiantSlots)) return;
+    if ((uint32_t)slot >= min(gmeta[3 * kGiantSlots], slots)) return;
     const int64_t a = gmeta[slot];
     const int32_t lo = (int32_t)gmeta[kGiantSlots + slot];
     const int32_t hi = (int32_t)gmeta[2 * kGiantSlots + slot];
@@ -619,18 +840,27 @@ __global__ __launch_bounds__(kBlock) void k_giant_emit(const uint32_t *__restric
     uint32_t run = 0;
     if (hi >= 0) {
         const int64_t w0 = lo >> 5, w1 = ((int64_t)hi >> 5) + 1;
-        for (int64_t c0 = w0; c0 < w1; c0 += kBlock) {
-            const int64_t wi = c0 + (int64_t)threadIdx.x;
-            const uint32_t word = wi < w1 ? bits[wi] : 0u;
+        for (int64_t c0 = w0; c0 < w1; c0 += kBlock * kRun) {
+            const int64_t wi = c0 + (int64_t)threadIdx.x * kRun;
+            uint32_t word[kRun], cnt = 0;
+#pragma unroll
+            for (int k = 0; k < kRun; k++) {
+                word[k] = bits[min(wi + k, w1 - 1)];
+                if (wi + k >= w1) word[k] = 0u;
+                cnt += (uint32_t)__popc(word[k]);
+            }
             uint32_t tot;
-            const uint32_t pos = block_excl((uint32_t)__popc(word), scan_s, &tot);
+            const uint32_t pos = block_excl(cnt, scan_s, &tot);
             if (FILL) {
-                uint32_t wv = word, k = 0;
-                while (wv) {
-                    const int bit = __ffs(wv) - 1;
-                    wv &= wv - 1;
-                    ccol[crow[a] + run + pos + k] = (int32_t)(wi * 32 + bit);
-                    k++;
+                int32_t *dst = ccol + crow[a] + run + pos;
+#pragma unroll
+                for (int k = 0; k < kRun; k++) {
+                    uint32_t wv = word[k];
+                    while (wv) {
+                        const int bit = __ffs(wv) - 1;
+                        wv &= wv - 1;
+                        *dst++ = (int32_t)((wi + k) * 32 + bit);
+                    }
                 }
             }
             run += tot;
@@ -640,8 +870,9 @@ __global__ __launch_bounds__(kBlock) void k_giant_emit(const uint32_t *__restric
 }
 
 // gmeta before a count pass: no rows, empty ranges.
-__global__ void k_giant_init(uint32_t *__restrict__ gmeta) {
+__global__ __launch_bounds__(kBlock) void k_giant_init(uint32_t *__restrict__ gmeta) {
     const int i = (int)threadIdx.x;
+    static_assert(kGiantMeta <= kBlock, "one thread per word");
     if (i < kGiantMeta)
         gmeta[i] = (i >= kGiantSlots && i < 2 * kGiantSlots) ? (uint32_t)INT32_MAX
                    : (i >= 2 * kGiantSlots && i < 3 * kGiantSlots) ? 0xFFFFFFFFu
@@ -657,83 +888,119 @@ int grid_for(int64_t work, int per_block, int cap) {
 
 }  // namespace
 
+hipError_t launch_member_lists(int64_t n, const int32_t *agg, int64_t n_agg, uint32_t *cnt,
+                               int64_t *moff, unsigned long long *part, int32_t *rank,
+                               int32_t *members, hipStream_t s) {
+    hipError_t e;
+    if ((e = launch_fill_u32(cnt, 0u, n_agg, s)) != hipSuccess) return e;
+    const int blocks = grid_for(n, kBlock, 8192);
+    if (n > 0)
+        hipLaunchKernelGGL(k_member_rank, dim3(blocks), dim3(kBlock), 0, s, n, agg, cnt, rank);
+    if ((e = exclusive_scan_u32_i64(cnt, n_agg, moff, part, s)) != hipSuccess) return e;
+    if (n > 0)
+        hipLaunchKernelGGL(k_member_scatter, dim3(blocks), dim3(kBlock), 0, s, n, agg,
+                           (const int64_t *)moff, (const int32_t *)rank, members);
+    return hipGetLastError();
+}
+
 hipError_t quotient_graph(const int64_t *row_ptr, const int32_t *col, int64_t n, int64_t nnz,
                           const int32_t *agg, int64_t n_agg, int64_t *crow, int32_t *ccol,
                           const QuotientWs &q, hipStream_t s) {
     hipError_t e;
-    if ((e = launch_fill_u32(q.cnt, 0u, n_agg, s)) != hipSuccess) return e;
-    if (n > 0)
-        hipLaunchKernelGGL(k_member_count, dim3(grid_for(n, kBlock, 8192)), dim3(kBlock), 0, s, n,
-                           agg, q.cnt);
-    if ((e = exclusive_scan_u32_i64(q.cnt, n_agg, q.moff, q.part, s)) != hipSuccess) return e;
-    if ((e = launch_fill_u32(q.cnt, 0u, n_agg, s)) != hipSuccess) return e;
-    if (n > 0)
-        hipLaunchKernelGGL(k_member_scatter, dim3(grid_for(n, kBlock, 8192)), dim3(kBlock), 0, s,
-                           n, agg, q.moff, q.cnt, q.members);
-    const int wblocks = grid_for(n_agg, kWaves, 8192);
-    const int bblocks = 1024;
+    if ((e = launch_member_lists(n, agg, n_agg, q.cnt, q.moff, q.part, q.rank, q.members, s)) !=
+        hipSuccess)
+        return e;
     // no coarse row has more candidates than the fine graph has entries
     const bool giant = nnz > kGiantCand && n_agg > 0;
     const int64_t words = (int64_t)giant_words(n_agg);
     uint32_t *gmeta = giant ? q.gmeta : nullptr;
-    if ((e = launch_fill_u32(q.big_count, 0u, 1, s)) != hipSuccess) return e;
-    if (giant) {
-        hipLaunchKernelGGL(k_giant_init, dim3(1), dim3(64), 0, s, q.gmeta);
-        if ((e = launch_fill_u32(q.gbits, 0u, kGiantSlots * words, s)) != hipSuccess) return e;
+    // as many bitmap slots as the workspace's bits for n ids make
+    const uint32_t slots = (uint32_t)std::min<int64_t>(
+        kGiantSlots, kGiantShare * (int64_t)giant_words(n) / std::max<int64_t>(words, 1));
+    // 16 lanes per row up to 256 candidates a row on average, else 64
+    const bool narrow = nnz <= 256 * n_agg;
+    const uint32_t maxc = narrow ? 512u : 16384u;
+    const int gblocks = (grid_for(n_agg, kBlock / (narrow ? 16 : 64), 4096) + 7) / 8 * 8;
+    const int wblocks = grid_for(n_agg, kWaves, 8192);
+    const int bblocks = grid_for(n_agg, 1, 2048);  // about what is resident at once
+    const bool hashed = words > kBitWords;         // second path between the first and a workgroup
+    // the spare buffer holds 9 or more entries a vertex; nearly all aggregates
+    // of a mesh have at most 6 neighbours a member
+    Spare sp;
+    sp.buf = q.tmp;
+    sp.per = 6;
+    const int64_t rest = (n * sp.per + 63) / 64 * 64;  // the cursors begin a cache line
+    sp.cursor = (uint32_t *)(q.tmp + rest);
+    sp.base = rest + kSpareParts * kSpareLine;
+    sp.cap = (uint32_t)std::min<int64_t>(std::max<int64_t>(q.tmp_cap - sp.base, 0) / kSpareParts,
+                                         (int64_t)1 << 26);
+    // the LDS bitmap of a workgroup: all coarse ids if they fit
+    const int bwords = (int)std::min<int64_t>(words, kBitWords);
+    const bool wide = nnz > 0xFFFFFFFFll;
+    {
+        FillSpans f;
+        f.add(sp.cursor, 0u, kSpareParts * kSpareLine);
+        if (giant) f.add(q.gbits, 0u, (int64_t)slots * words);
+        if ((e = launch_fill_spans(f, s)) != hipSuccess) return e;
     }
-    // two wavefront passes (rows of up to kWSmall candidates first) when
-    // rows are small on average and many; else one
-    const bool two = n_agg >= 16384 && nnz <= (int64_t)kWSmall * 2 * n_agg;
+    if (giant) hipLaunchKernelGGL(k_giant_init, dim3(1), dim3(kBlock), 0, s, q.gmeta);
+    auto group = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(gblocks), dim3(kBlock), 0, s, row_ptr, col, agg, n_agg,
+                           q.moff, q.members, maxc, q.cnt, sp, q.cls,
+                           hashed ? kSecond : kBig);
+    };
+    auto big = [&](auto kernel, const int64_t *rows, int32_t *cols) {
+        hipLaunchKernelGGL(kernel, dim3(bblocks), dim3(kBlock), 4 * (size_t)bwords, s, row_ptr, col,
+                           agg, n_agg, q.moff, q.members, q.cnt, rows, cols, q.cls, gmeta, slots,
+                           bwords, sp);
+    };
     if (n_agg > 0) {
-        if (two) {
-            hipLaunchKernelGGL((k_coarse_rows_wave<false, kWSmall, kRowsMark>), dim3(wblocks),
-                               dim3(kBlock), 0, s, row_ptr, col, agg, n_agg, q.moff, q.members,
-                               q.cnt, (const int64_t *)nullptr, (int32_t *)nullptr, q.cls, q.big,
-                               q.big_count);
-            hipLaunchKernelGGL((k_coarse_rows_wave<false, kWCap, kRowsMarked>), dim3(wblocks),
-                               dim3(kBlock), 0, s, row_ptr, col, agg, n_agg, q.moff, q.members,
-                               q.cnt, (const int64_t *)nullptr, (int32_t *)nullptr, q.cls, q.big,
-                               q.big_count);
-        } else {
-            hipLaunchKernelGGL((k_coarse_rows_wave<false, kWCap, kRowsList>), dim3(wblocks),
-                               dim3(kBlock), 0, s, row_ptr, col, agg, n_agg, q.moff, q.members,
-                               q.cnt, (const int64_t *)nullptr, (int32_t *)nullptr, q.cls, q.big,
-                               q.big_count);
-        }
-        hipLaunchKernelGGL(k_coarse_rows<false>, dim3(bblocks), dim3(kBlock), 0, s, row_ptr, col,
-                           agg, n_agg, q.moff, q.members, q.cnt, (const int64_t *)nullptr,
-                           (int32_t *)nullptr, (const int32_t *)q.big,
-                           (const uint32_t *)q.big_count, gmeta);
+        if (narrow)
+            group(k_coarse_rows_group<16, 128, 96, 4>);
+        else
+            group(k_coarse_rows_group<64, 256, 160, 8>);
+        if (hashed)
+            hipLaunchKernelGGL(k_coarse_rows_wave<false>, dim3(wblocks), dim3(kBlock), 0, s,
+                               row_ptr, col, agg, n_agg, q.moff, q.members, q.cnt,
+                               (const int64_t *)nullptr, (int32_t *)nullptr, q.cls, sp);
+        if (wide)
+            big(k_coarse_rows<false, unsigned long long>, nullptr, nullptr);
+        else
+            big(k_coarse_rows<false, uint32_t>, nullptr, nullptr);
     }
     if (giant) {
-        hipLaunchKernelGGL(k_giant_set, dim3(256, kGiantSlots), dim3(kBlock), 0, s, row_ptr, col,
-                           agg, q.moff, q.members, q.gbits, words, q.gmeta);
-        hipLaunchKernelGGL(k_giant_emit<false>, dim3(kGiantSlots), dim3(kBlock), 0, s,
-                           (const uint32_t *)q.gbits, words, (const uint32_t *)q.gmeta, q.cnt,
+        const int gwords = words <= kBitWords ? (int)words : 0;
+        auto set = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(512, 8), dim3(kBlock), 4 * (size_t)gwords, s,
+                               row_ptr, col, agg, q.moff, q.members, q.gbits, words, q.gmeta, slots,
+                               gwords);
+        };
+        if (wide)
+            set(k_giant_set<unsigned long long>);
+        else
+            set(k_giant_set<uint32_t>);
+        hipLaunchKernelGGL(k_giant_emit<false>, dim3(slots), dim3(kBlock), 0, s,
+                           (const uint32_t *)q.gbits, words, (const uint32_t *)q.gmeta, slots, q.cnt,
                            (const int64_t *)nullptr, (int32_t *)nullptr);
     }
     if ((e = exclusive_scan_u32_i64(q.cnt, n_agg, crow, q.part, s)) != hipSuccess) return e;
     if (n_agg > 0) {
-        if (two) {
-            hipLaunchKernelGGL((k_coarse_rows_wave<true, kWSmall, kRowsMark>), dim3(wblocks),
-                               dim3(kBlock), 0, s, row_ptr, col, agg, n_agg, q.moff, q.members,
-                               q.cnt, crow, ccol, q.cls, q.big, q.big_count);
-            hipLaunchKernelGGL((k_coarse_rows_wave<true, kWCap, kRowsMarked>), dim3(wblocks),
-                               dim3(kBlock), 0, s, row_ptr, col, agg, n_agg, q.moff, q.members,
-                               q.cnt, crow, ccol, q.cls, q.big, q.big_count);
-        } else {
-            hipLaunchKernelGGL((k_coarse_rows_wave<true, kWCap, kRowsList>), dim3(wblocks),
-                               dim3(kBlock), 0, s, row_ptr, col, agg, n_agg, q.moff, q.members,
-                               q.cnt, crow, ccol, q.cls, q.big, q.big_count);
-        }
-        hipLaunchKernelGGL(k_coarse_rows<true>, dim3(bblocks), dim3(kBlock), 0, s, row_ptr, col,
-                           agg, n_agg, q.moff, q.members, q.cnt, crow, ccol,
-                           (const int32_t *)q.big, (const uint32_t *)q.big_count, gmeta);
+        hipLaunchKernelGGL(k_copy_rows, dim3(grid_for(n_agg, kBlock / 16, 8192)), dim3(kBlock), 0,
+                           s, n_agg, q.moff, (const int64_t *)crow, (const uint8_t *)q.cls, sp,
+                           ccol);
+        if (hashed)
+            hipLaunchKernelGGL(k_coarse_rows_wave<true>, dim3(wblocks), dim3(kBlock), 0, s, row_ptr,
+                               col, agg, n_agg, q.moff, q.members, q.cnt, (const int64_t *)crow,
+                               ccol, q.cls, sp);
+        if (wide)
+            big(k_coarse_rows<true, unsigned long long>, crow, ccol);
+        else
+            big(k_coarse_rows<true, uint32_t>, crow, ccol);
     }
     if (giant)
-        hipLaunchKernelGGL(k_giant_emit<true>, dim3(kGiantSlots), dim3(kBlock), 0, s,
-                           (const uint32_t *)q.gbits, words, (const uint32_t *)q.gmeta, q.cnt, crow,
-                           ccol);
+        hipLaunchKernelGGL(k_giant_emit<true>, dim3(slots), dim3(kBlock), 0, s,
+                           (const uint32_t *)q.gbits, words, (const uint32_t *)q.gmeta, slots, q.cnt,
+                           crow, ccol);
     return hipGetLastError();
 }
 

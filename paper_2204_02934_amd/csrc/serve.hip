@@ -214,7 +214,7 @@ int mis2_server_step(mis2_server *s, void *stream, int32_t *n_pending) {
     mis2_graph cur{s->n_u, s->nnz_u, rp, cl};
     const int nx = s->cur ^ 1;
     int rc = batch_level(ctx, cur, s->seed, s->stop_below, s->agg_scratch, s->ar, s->ar.crow[nx],
-                         s->ar.ccol[nx], &bl, st);
+                         s->ar.ccol[nx], cl + s->nnz_u, s->ecap - s->nnz_u, &bl, st);
     if (rc) return rc;
     // 3. labels out, finished jobs off, coarse graphs on
     std::vector<int32_t> next;
