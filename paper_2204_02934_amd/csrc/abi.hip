@@ -1771,11 +1771,11 @@ int mis2_quotient(mis2_ctx *ctx, const mis2_graph *g, const int32_t *agg_id, int
                          0, s);
 }
 
-// mis2_galerkin: member counts, offsets, cursors and lists, scan partials
+// mis2_galerkin: member counts, offsets, ranks and lists, scan partials
 // and a flag word; at least what validating the fine graph needs.
 static size_t galerkin_bytes(int64_t n, int64_t n_agg) {
     const size_t ua = (size_t)n_agg;
-    const size_t own = 2 * align_up(4 * ua) + align_up(8 * (ua + 1)) + align_up(4 * (size_t)n) +
+    const size_t own = align_up(4 * ua) + align_up(8 * (ua + 1)) + 2 * align_up(4 * (size_t)n) +
                        align_up(8 * (size_t)scan_parts(n_agg)) + align_up(256);
     return std::max(own, workspace_bytes(n, MIS2_OP_MIS2));
 }
@@ -1811,8 +1811,8 @@ int mis2_galerkin(mis2_ctx *ctx, const mis2_graph *g, const double *val, const d
         return (void *)r;
     };
     uint32_t *cnt = (uint32_t *)take(4 * (size_t)na);
-    uint32_t *cursor = (uint32_t *)take(4 * (size_t)na);
     int64_t *moff = (int64_t *)take(8 * ((size_t)na + 1));
+    int32_t *rank = (int32_t *)take(4 * (size_t)n);
     int32_t *members = (int32_t *)take(4 * (size_t)n);
     unsigned long long *part = (unsigned long long *)take(8 * (size_t)scan_parts(na));
     uint32_t *flag = (uint32_t *)take(256);
@@ -1832,11 +1832,8 @@ int mis2_galerkin(mis2_ctx *ctx, const mis2_graph *g, const double *val, const d
     if (ctx->pinned[0] & 1u) return fail(ctx, MIS2_EINVAL, "aggregate id outside [0, %lld)", (long long)na);
     if (ctx->pinned[0] & 2u) return fail(ctx, MIS2_EINVAL, "coarse column outside [0, %lld)", (long long)na);
     // members of each aggregate by increasing id
-    HIP_TRY(ctx, launch_fill_u32(cnt, 0u, na, s));
-    HIP_TRY(ctx, launch_count_of(n, agg, cnt, s));
-    HIP_TRY(ctx, exclusive_scan_u32_i64(cnt, na, moff, part, s));
-    HIP_TRY(ctx, launch_fill_u32(cursor, 0u, na, s));
-    HIP_TRY(ctx, launch_sorted_members(n, agg, na, moff, cursor, members, s));
+    HIP_TRY(ctx, launch_member_lists(n, agg, na, cnt, moff, part, rank, members, s));
+    HIP_TRY(ctx, launch_sort_members(na, moff, members, s));
     HIP_TRY(ctx, launch_galerkin(g->row_ptr, g->col, val, diag, agg, na, moff, members,
                                  coarse->row_ptr, coarse->col, coarse_val, coarse_diag, flag,
                                  g->nnz, s));
@@ -2060,11 +2057,10 @@ int mis2_cgs_setup(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int point,
         ccol[i] = (int32_t *)take(4 * (size_t)g->nnz);
     }
     const size_t un = (size_t)n;
-    uint32_t *pr = (uint32_t *)take(4 * un);
-    int32_t *cround = (int32_t *)take(4 * un);
+    unsigned long long *st = (unsigned long long *)take(8 * un);
     uint32_t *cnt = (uint32_t *)take(4 * un);
     int64_t *moff = (int64_t *)take(8 * (un + 1));
-    uint32_t *cursor = (uint32_t *)take(4 * un);
+    uint32_t *wcnt = (uint32_t *)take(4 * un);
     int32_t *members = (int32_t *)take(4 * un);
     int32_t *corder = (int32_t *)take(4 * un);
     uint32_t *ssz = (uint32_t *)take(4 * un);
@@ -2088,42 +2084,62 @@ int mis2_cgs_setup(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int point,
     } else {
         HIP_TRY(ctx, launch_iota(n, plan->cluster, s));
     }
-    // Jones-Plassmann colouring of cg; every round colours at least the
-    // smallest uncoloured tuple, so at most nc rounds
-    HIP_TRY(ctx, launch_jp_init(nc, tuple_params(nc, seed, 0), pr, cround, plan->cluster_color, s));
-    HIP_TRY(ctx, launch_fill_u32(scal, 0u, 64, s));
-    for (int r = 0;; r++) {
-        if (r > nc) return fail(ctx, MIS2_EINTERNAL, "colouring made no progress");
-        HIP_TRY(ctx, launch_fill_u32(scal, 0u, 1, s));
-        HIP_TRY(ctx, launch_jp_round(nc, cg.row_ptr, cg.col, pr, cround, plan->cluster_color, r,
-                                     scal, scal + 1, s));
-        HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, scal, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    // Jones-Plassmann colouring of cg; every launch colours at least the
+    // smallest uncoloured tuple, so at most nc launches.  A few are queued
+    // between two looks at what is left (one that finds nothing left is short)
+    HIP_TRY(ctx, launch_jp_init(nc, tuple_params(nc, seed, 0), st, s));
+    constexpr int kJpQueued = 4;
+    uint32_t *const maxc = scal + kJpQueued;
+    for (int64_t r = 0;; r += kJpQueued) {
+        if (r > nc + kJpQueued) return fail(ctx, MIS2_EINTERNAL, "colouring made no progress");
+        HIP_TRY(ctx, launch_fill_u32(scal, 0u, r == 0 ? 64 : kJpQueued, s));
+        for (int k = 0; k < kJpQueued; k++)
+            HIP_TRY(ctx, launch_jp_pass(nc, cg.row_ptr, cg.col, st, plan->cluster_color, members,
+                                        wcnt, r + k == 0, scal + k, maxc, s));
+        HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, scal, (kJpQueued + 1) * sizeof(uint32_t),
+                                    hipMemcpyDeviceToHost, s));
         HIP_TRY(ctx, hipStreamSynchronize(s));
-        if (ctx->pinned[0] == 0) break;
+        if (ctx->pinned[kJpQueued - 1] == 0) break;
     }
-    const int32_t n_colors = (int32_t)ctx->pinned[1] + 1;
-    // rows of each cluster in increasing id
-    HIP_TRY(ctx, launch_fill_u32(cnt, 0u, nc, s));
-    HIP_TRY(ctx, launch_count_of(n, plan->cluster, cnt, s));
-    HIP_TRY(ctx, exclusive_scan_u32_i64(cnt, nc, moff, part, s));
-    HIP_TRY(ctx, launch_fill_u32(cursor, 0u, nc, s));
-    HIP_TRY(ctx, launch_sorted_members(n, plan->cluster, nc, moff, cursor, members, s));
-    // clusters by colour, then id
-    std::vector<uint32_t> h((size_t)n_colors);
-    HIP_TRY(ctx, launch_fill_u32(hist, 0u, n_colors, s));
-    HIP_TRY(ctx, launch_color_hist(nc, plan->cluster_color, n_colors, hist, s));
-    HIP_TRY(ctx, hipMemcpyAsync(h.data(), hist, 4 * (size_t)n_colors, hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
-    for (int32_t c = 0; c < n_colors; c++) plan->color_off[c + 1] = plan->color_off[c] + h[c];
-    if (plan->color_off[n_colors] != nc)
-        return fail(ctx, MIS2_EINTERNAL, "colour histogram does not add up");
-    for (int32_t c = 0; c < n_colors; c++)
-        HIP_TRY(ctx, compact_u32_eq((const uint32_t *)plan->cluster_color, (uint32_t)c, nc,
-                                    corder + plan->color_off[c], scal + 2, blocksum, s));
-    HIP_TRY(ctx, launch_gather_sizes(nc, corder, cnt, ssz, s));
-    HIP_TRY(ctx, exclusive_scan_u32_i64(ssz, nc, plan->cluster_off, part, s));
-    HIP_TRY(ctx, launch_place_rows(nc, corder, moff, members, plan->cluster_off, plan->rows, s));
-    HIP_TRY(ctx, launch_scatter_pos(n, plan->rows, plan->pos, s));
+    const int32_t n_colors = (int32_t)ctx->pinned[kJpQueued] + 1;
+    // clusters by colour, then id (a point plan's clusters are its rows)
+    int32_t *const order = point ? plan->rows : corder;
+    const int64_t counts = color_sort_counts(nc, n_colors);
+    if (counts > 0) {
+        // counts <= n: it is n_colors for one tile, else at most n / 32 + 64
+        int64_t *const first = crow[1];
+        HIP_TRY(ctx, launch_color_sort(nc, plan->cluster_color, n_colors, hist, moff, part, order,
+                                       first, s));
+        HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, first, 8 * (size_t)n_colors,
+                                    hipMemcpyDeviceToHost, s));
+        HIP_TRY(ctx, hipStreamSynchronize(s));
+        memcpy(plan->color_off, ctx->pinned, 8 * (size_t)n_colors);
+        plan->color_off[n_colors] = nc;
+    } else {
+        std::vector<uint32_t> h((size_t)n_colors);
+        HIP_TRY(ctx, launch_fill_u32(hist, 0u, n_colors, s));
+        HIP_TRY(ctx, launch_color_hist(nc, plan->cluster_color, n_colors, hist, s));
+        HIP_TRY(ctx, hipMemcpyAsync(h.data(), hist, 4 * (size_t)n_colors, hipMemcpyDeviceToHost, s));
+        HIP_TRY(ctx, hipStreamSynchronize(s));
+        for (int32_t c = 0; c < n_colors; c++) plan->color_off[c + 1] = plan->color_off[c] + h[c];
+        if (plan->color_off[n_colors] != nc)
+            return fail(ctx, MIS2_EINTERNAL, "colour histogram does not add up");
+        for (int32_t c = 0; c < n_colors; c++)
+            HIP_TRY(ctx, compact_u32_eq((const uint32_t *)plan->cluster_color, (uint32_t)c, nc,
+                                        order + plan->color_off[c], scal + 2, blocksum, s));
+    }
+    if (point) {
+        HIP_TRY(ctx, launch_point_plan(n, plan->rows, plan->pos, plan->cluster_off, s));
+    } else {
+        // rows of each cluster in increasing id, then the clusters in order
+        HIP_TRY(ctx, launch_member_lists(n, plan->cluster, nc, cnt, moff, part, (int32_t *)ssz,
+                                         members, s));
+        HIP_TRY(ctx, launch_sort_members(nc, moff, members, s));
+        HIP_TRY(ctx, launch_gather_sizes(nc, corder, cnt, ssz, s));
+        HIP_TRY(ctx, exclusive_scan_u32_i64(ssz, nc, plan->cluster_off, part, s));
+        HIP_TRY(ctx, launch_place_rows(nc, corder, moff, members, plan->cluster_off, plan->rows, s));
+        HIP_TRY(ctx, launch_scatter_pos(n, plan->rows, plan->pos, s));
+    }
     HIP_TRY(ctx, hipStreamSynchronize(s));
     plan->n_clusters = nc;
     plan->n_colors = n_colors;

@@ -9,11 +9,13 @@
 // sequential sweep in the same order.
 //
 // Colouring (the paper takes it from other work): Jones-Plassmann with fixed
-// priorities, the packed tuple of h(seed, 0, v) (Sections V-A, V-C).  Each
-// round every uncoloured vertex whose tuple is below those of its uncoloured
-// neighbours takes the smallest colour no coloured neighbour has.  Two
-// vertices picked in one round are never adjacent (each would be below the
-// other), so a round reads only colours fixed in earlier rounds.
+// priorities, the packed tuple of h(seed, 0, v) (Sections V-A, V-C): every
+// uncoloured vertex whose tuple is below those of its uncoloured neighbours
+// takes the smallest colour no coloured neighbour has.  A vertex is coloured
+// only after all its neighbours of lower tuple and before all those of higher
+// tuple, so its colour is the smallest one its lower neighbours leave: the
+// result is that of colouring the vertices one by one in tuple order, whatever
+// subset of the ready ones a pass happens to colour.
 #include "internal.h"
 #include "lanes.h"
 
@@ -21,76 +23,176 @@ namespace mis2 {
 
 namespace {
 
-__global__ __launch_bounds__(kBlock) void k_jp_init(int64_t n, TupleParams tp,
-                                                    uint32_t *__restrict__ pr,
-                                                    int32_t *__restrict__ cround,
-                                                    int32_t *__restrict__ color) {
-    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
-         v += (int64_t)gridDim.x * kBlock) {
-        pr[v] = make_tuple(tp, (uint32_t)v);
-        cround[v] = -1;
-        color[v] = -1;
-    }
+// State of a vertex: its tuple in the low word, its colour (-1: none yet) in
+// the high one.
+__device__ __forceinline__ unsigned long long jp_state(uint32_t tuple, int32_t color) {
+    return (unsigned long long)tuple | ((unsigned long long)(uint32_t)color << 32);
 }
 
-// Round r.  cround[w] is the round w was coloured in (-1: not yet); a
-// neighbour coloured in this very round reads as -1 or r, both "uncoloured
-// when the round started", and its colour is never read.  *d_left gets the
-// vertices still uncoloured after the round, *d_maxc the largest colour.
-__global__ __launch_bounds__(kBlock) void k_jp_round(int64_t n, const int64_t *__restrict__ row_ptr,
-                                                     const int32_t *__restrict__ col,
-                                                     const uint32_t *__restrict__ pr,
-                                                     int32_t *cround, int32_t *color, int r,
-                                                     uint32_t *__restrict__ d_left,
-                                                     uint32_t *__restrict__ d_maxc) {
-    __shared__ uint32_t s_left, s_max;
-    if (threadIdx.x == 0) {
-        s_left = 0;
-        s_max = 0;
-    }
-    __syncthreads();
-    uint32_t left = 0;
+__global__ __launch_bounds__(kBlock) void k_jp_init(int64_t n, TupleParams tp,
+                                                    unsigned long long *__restrict__ st) {
     for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
-         v += (int64_t)gridDim.x * kBlock) {
-        if (cround[v] != -1) continue;
-        const int64_t s = row_ptr[v], e = row_ptr[v + 1];
-        const uint32_t pv = pr[v];
-        bool local_min = true;
-        for (int64_t j = s; j < e; j++) {
-            const int32_t w = col[j];
-            const int32_t cw = cround[w];
-            if ((cw == -1 || cw == r) && pr[w] < pv) local_min = false;
-        }
-        if (!local_min) {
-            left++;
-            continue;
-        }
-        // smallest colour not on a neighbour coloured in an earlier round,
-        // 64 colours at a time; stored inside the loop
-        for (int32_t base = 0;; base += 64) {
+         v += (int64_t)gridDim.x * kBlock)
+        st[v] = jp_state(make_tuple(tp, (uint32_t)v), -1);
+}
+
+constexpr int kJpLoads = 8;  // entries of a row loaded together
+
+// kJpPasses passes over the uncoloured vertices.  Wavefront w owns the
+// vertices [w * seg, (w + 1) * seg) and keeps those still uncoloured, in
+// order, in list[w * seg ...] and their number in cnt[w] (first launch: all of
+// them).  One lane per vertex; a neighbour's state is one 8-byte load, so a
+// vertex either sees its colour and tuple together or finds it uncoloured
+// and waits.  The loads and stores of states are relaxed atomics: they see
+// what other workgroups coloured a moment ago (those of the same XCD share
+// its L2, and each XCD owns one run of vertices), so one launch colours
+// several links of a chain of neighbours; a colour missed is seen by the next
+// launch.  *left = 1 when a vertex stays uncoloured, *maxc is raised to the
+// largest colour given.
+// One launch per round over every vertex, with the round of each neighbour
+// and then its tuple loaded entry by entry, took 1.72 ms (21 launches of 82 us)
+// on the 7-point 100^3 grid.
+constexpr int kJpPasses = 4;
+__global__ __launch_bounds__(kBlock) void k_jp_pass(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                    const int32_t *__restrict__ col,
+                                                    unsigned long long *st,
+                                                    int32_t *__restrict__ color, int32_t *list,
+                                                    uint32_t *__restrict__ cnt, int64_t seg,
+                                                    int first, uint32_t *__restrict__ left,
+                                                    uint32_t *__restrict__ maxc) {
+    const int lane = (int)(threadIdx.x & 63u);
+    const int64_t blk = (int64_t)(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const int64_t w = blk * (kBlock / 64) + (threadIdx.x >> 6);
+    const int64_t base = w * seg;
+    int64_t m = first ? max((int64_t)0, min(seg, n - base)) : (int64_t)cnt[w];
+    int32_t best = -1;
+    for (int pass = 0; pass < kJpPasses && m > 0; pass++) {
+        int64_t out = 0;
+        for (int64_t i0 = 0; i0 < m; i0 += 64) {
+            const bool mine = i0 + lane < m;
+            const int64_t at = base + (mine ? i0 + lane : i0);
+            const int64_t v = first && pass == 0 ? at : (int64_t)list[at];
+            const int64_t s = row_ptr[v], e = row_ptr[v + 1];
+            const uint32_t pv = (uint32_t)st[v];
+            bool wait = !mine;
             uint64_t used = 0;
-            for (int64_t j = s; j < e; j++) {
-                const int32_t w = col[j];
-                const int32_t cw = cround[w];
-                if (cw >= 0 && cw < r) {
-                    const int32_t c = color[w] - base;
+            for (int64_t j = s; j < e && !wait; j += kJpLoads) {
+                int32_t x[kJpLoads];
+#pragma unroll
+                for (int k = 0; k < kJpLoads; k++) x[k] = col[min(j + k, e - 1)];
+                unsigned long long y[kJpLoads];
+#pragma unroll
+                for (int k = 0; k < kJpLoads; k++)
+                    y[k] = __hip_atomic_load(&st[x[k]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int k = 0; k < kJpLoads; k++) {
+                    const int32_t c = (int32_t)(y[k] >> 32);
+                    if (c < 0 && (uint32_t)y[k] < pv) wait = true;
                     if (c >= 0 && c < 64) used |= 1ull << c;
                 }
             }
-            if (used != ~0ull) {
-                const int32_t c = base + __ffsll((unsigned long long)~used) - 1;
+            if (!wait) {
+                // every neighbour of lower tuple is coloured, for good
+                int32_t c = used != ~0ull ? __ffsll((unsigned long long)~used) - 1 : 64;
+                for (int32_t b0 = 64; c == b0; b0 += 64) {  // all 64 colours before b0 taken
+                    uint64_t u = 0;
+                    for (int64_t j = s; j < e; j++) {
+                        const int32_t d =
+                            (int32_t)(__hip_atomic_load(&st[col[j]], __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT) >> 32) - b0;
+                        if (d >= 0 && d < 64) u |= 1ull << d;
+                    }
+                    c = u != ~0ull ? b0 + __ffsll((unsigned long long)~u) - 1 : b0 + 64;
+                }
+                __hip_atomic_store(&st[v], jp_state(pv, c), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
                 color[v] = c;
-                cround[v] = r;
-                atomicMax(&s_max, (uint32_t)c);
-                break;
+                best = max(best, c);
             }
+            const uint64_t keep = __ballot(mine && wait);
+            if (mine && wait)
+                list[base + out + __popcll(keep & (lane ? ~0ull >> (64 - lane) : 0ull))] = (int32_t)v;
+            out += __popcll(keep);
+        }
+        m = out;
+        // this wavefront's list is read back by other lanes
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    }
+    if (lane == 0) {
+        cnt[w] = (uint32_t)m;
+        if (m > 0) *left = 1u;
+    }
+    best = (int32_t)group_max<64>((uint32_t)(best + 1)) - 1;
+    if (lane == 0 && best > (int32_t) * (volatile uint32_t *)maxc) atomicMax(maxc, (uint32_t)best);
+}
+
+// Ids in order of colour, then id: a counting sort.  cnt[c * tiles + t] = the
+// ids of colour c in tile t of kColorTile ids; after a prefix sum over it,
+// pos has where each run goes.
+constexpr int kColorTile = 2048;
+constexpr int kSortColors = 64;  // most colours
+__global__ __launch_bounds__(kBlock) void k_color_count(int64_t n, const int32_t *__restrict__ color,
+                                                        int32_t n_colors, int64_t tiles,
+                                                        uint32_t *__restrict__ cnt) {
+    __shared__ uint32_t h[kSortColors];
+    if (threadIdx.x < kSortColors) h[threadIdx.x] = 0u;
+    __syncthreads();
+    const int64_t t = blockIdx.x, e = min(n, (t + 1) * kColorTile);
+    for (int64_t v = t * kColorTile + threadIdx.x; v < e; v += kBlock) atomicAdd(&h[color[v]], 1u);
+    __syncthreads();
+    if ((int)threadIdx.x < n_colors) cnt[(int64_t)threadIdx.x * tiles + t] = h[threadIdx.x];
+}
+
+// Each wavefront takes a quarter of the tile, 64 ids at a time; its lanes of
+// one colour are numbered by a ballot.  first[c] = where colour c begins.
+__global__ __launch_bounds__(kBlock) void k_color_scatter(int64_t n, const int32_t *__restrict__ color,
+                                                          int32_t n_colors, int64_t tiles,
+                                                          const int64_t *__restrict__ pos,
+                                                          int32_t *__restrict__ out,
+                                                          int64_t *__restrict__ first) {
+    constexpr int kW = kBlock / 64, kPart = kColorTile / kW;
+    __shared__ uint32_t h[kW][kSortColors];
+    __shared__ int64_t at[kW][kSortColors];
+    const int lane = (int)(threadIdx.x & 63u), wv = (int)(threadIdx.x >> 6);
+    const int64_t t = blockIdx.x;
+    const int64_t b = t * kColorTile + (int64_t)wv * kPart, e = min(n, b + kPart);
+    h[wv][lane] = 0u;
+    __syncthreads();
+    for (int64_t v = b + lane; v < e; v += 64) atomicAdd(&h[wv][color[v]], 1u);
+    __syncthreads();
+    if (lane < n_colors) {
+        int64_t o = pos[(int64_t)lane * tiles + t];
+        if (t == 0 && wv == 0) first[lane] = o;
+        for (int k = 0; k < wv; k++) o += h[k][lane];
+        at[wv][lane] = o;
+    }
+    __syncthreads();
+    for (int64_t v0 = b; v0 < e; v0 += 64) {
+        const int64_t v = v0 + lane;
+        const int32_t c = v < e ? color[v] : -1;
+        uint64_t todo = __ballot(c >= 0);
+        while (todo) {
+            const int l = __ffsll((unsigned long long)todo) - 1;
+            const int32_t cl = __builtin_amdgcn_readlane(c, l);
+            const uint64_t same = __ballot(c == cl);
+            const int64_t o = at[wv][cl];
+            if (c == cl) out[o + __popcll(same & (lane ? ~0ull >> (64 - lane) : 0ull))] = (int32_t)v;
+            __builtin_amdgcn_wave_barrier();  // o is read before it moves on
+            if (lane == 0) at[wv][cl] = o + __popcll(same);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            todo &= ~same;
         }
     }
-    if (left) atomicAdd(&s_left, left);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        if (s_left) atomicAdd(d_left, s_left);
-        atomicMax(d_maxc, s_max);
+}
+
+// The point plan: rows[k] (in order of colour) is the k-th cluster.
+__global__ __launch_bounds__(kBlock) void k_point_plan(int64_t n, const int32_t *__restrict__ rows,
+                                                       int32_t *__restrict__ pos,
+                                                       int64_t *__restrict__ cluster_off) {
+    for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k <= n;
+         k += (int64_t)gridDim.x * kBlock) {
+        cluster_off[k] = k;
+        if (k < n) pos[rows[k]] = (int32_t)k;
     }
 }
 
@@ -135,12 +237,14 @@ __global__ __launch_bounds__(kBlock) void k_scatter_members(int64_t n,
     }
 }
 
-constexpr int64_t kSmallCluster = 64;
+constexpr int kSortRegs = 8;  // members per lane
+constexpr int64_t kSmallCluster = 64 * kSortRegs;
 
-// Each cluster of 2 .. kSmallCluster members: one wavefront, one member per
-// lane; a member's place is the number of smaller ones (ids are distinct),
-// counted across the lanes.  Every lane has its member in a register before
-// any is written back.
+// Each cluster of 2 .. kSmallCluster members: one wavefront, up to kSortRegs
+// members per lane; a member's place is the number of smaller ones (ids are
+// distinct), counted across the lanes.  Every member is in a register before
+// any is written back.  (Clusters past 64 members sorted by a workgroup in
+// global memory cost some 50 us each: a network of 28 passes and more.)
 __global__ __launch_bounds__(kBlock) void k_sort_small(int64_t nc, const int64_t *__restrict__ moff,
                                                        int32_t *__restrict__ members) {
     const int lane = threadIdx.x & 63;
@@ -148,38 +252,73 @@ __global__ __launch_bounds__(kBlock) void k_sort_small(int64_t nc, const int64_t
     if (a >= nc) return;
     const int64_t s = moff[a], m = moff[a + 1] - s;
     if (m < 2 || m > kSmallCluster) return;
-    const int32_t x = lane < m ? members[s + lane] : 0x7fffffff;
-    int rank = 0;
-    for (int w = 0; w < (int)m; w++) rank += __builtin_amdgcn_readlane(x, w) < x;
-    if (lane < m) members[s + rank] = x;
+    if (m <= 64) {
+        const int32_t x = lane < m ? members[s + lane] : 0x7fffffff;
+        int rank = 0;
+        for (int w = 0; w < (int)m; w++) rank += __builtin_amdgcn_readlane(x, w) < x;
+        if (lane < m) members[s + rank] = x;
+        return;
+    }
+    int32_t x[kSortRegs];
+    int rank[kSortRegs];
+#pragma unroll
+    for (int k = 0; k < kSortRegs; k++) {
+        x[k] = k * 64 + lane < m ? members[s + k * 64 + lane] : 0x7fffffff;
+        rank[k] = 0;
+    }
+#pragma unroll
+    for (int q = 0; q < kSortRegs; q++) {
+        const int mq = (int)m - q * 64 < 64 ? (int)m - q * 64 : 64;
+        for (int w = 0; w < mq; w++) {
+            const int32_t y = __builtin_amdgcn_readlane(x[q], w);
+#pragma unroll
+            for (int k = 0; k < kSortRegs; k++) rank[k] += y < x[k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kSortRegs; k++)
+        if (k * 64 + lane < m) members[s + rank[k]] = x[k];
 }
 
 // Each larger cluster: one workgroup sorts it in place with a bitonic
 // network on the next power of two, positions past the end reading as +inf.
 // The network's first step of every merge compares i with i ^ (k - 1) and
 // the later ones i with i ^ j, always the smaller value to the lower index,
-// so no real value ever moves past the end.
+// so no real value ever moves past the end.  A workgroup reads the sizes of
+// kBlock clusters at once and sorts the few large ones among them (reading
+// them one after the other took 31 us on 14 000 clusters, 249 us on a million
+// without a large one).
 __global__ __launch_bounds__(kBlock) void k_sort_large(int64_t nc, const int64_t *__restrict__ moff,
                                                        int32_t *__restrict__ members) {
-    for (int64_t a = blockIdx.x; a < nc; a += gridDim.x) {
-        const int64_t s = moff[a], size = moff[a + 1] - s;
-        if (size <= kSmallCluster) continue;
-        int64_t P = 1;
-        while (P < size) P <<= 1;
-        int32_t *m = members + s;
-        for (int64_t k = 2; k <= P; k <<= 1) {
-            for (int64_t j = k >> 1; j > 0; j >>= 1) {
-                for (int64_t i = threadIdx.x; i < P; i += kBlock) {
-                    const int64_t p = (j == (k >> 1)) ? (i ^ (k - 1)) : (i ^ j);
-                    if (p > i && p < size) {
-                        const int32_t x = m[i], y = m[p];
-                        if (x > y) {
-                            m[i] = y;
-                            m[p] = x;
+    __shared__ uint64_t large[kBlock / 64];
+    for (int64_t a0 = (int64_t)blockIdx.x * kBlock; a0 < nc; a0 += (int64_t)gridDim.x * kBlock) {
+        const int64_t own = a0 + threadIdx.x;
+        const uint64_t mine = __ballot(own < nc && moff[own + 1] - moff[own] > kSmallCluster);
+        __syncthreads();
+        if ((threadIdx.x & 63u) == 0) large[threadIdx.x >> 6] = mine;
+        __syncthreads();
+        for (int w = 0; w < kBlock / 64; w++) {
+            for (uint64_t mask = large[w]; mask; mask &= mask - 1) {
+                const int64_t a = a0 + w * 64 + __ffsll((unsigned long long)mask) - 1;
+                const int64_t s = moff[a], size = moff[a + 1] - s;
+                int64_t P = 1;
+                while (P < size) P <<= 1;
+                int32_t *m = members + s;
+                for (int64_t k = 2; k <= P; k <<= 1) {
+                    for (int64_t j = k >> 1; j > 0; j >>= 1) {
+                        for (int64_t i = threadIdx.x; i < P; i += kBlock) {
+                            const int64_t p = (j == (k >> 1)) ? (i ^ (k - 1)) : (i ^ j);
+                            if (p > i && p < size) {
+                                const int32_t x = m[i], y = m[p];
+                                if (x > y) {
+                                    m[i] = y;
+                                    m[p] = x;
+                                }
+                            }
                         }
+                        __syncthreads();
                     }
                 }
-                __syncthreads();
             }
         }
     }
@@ -533,20 +672,50 @@ int grid_of(int64_t work, int cap) {
 
 }  // namespace
 
-hipError_t launch_jp_init(int64_t n, const TupleParams &tp, uint32_t *pr, int32_t *cround,
-                          int32_t *color, hipStream_t s) {
+hipError_t launch_jp_init(int64_t n, const TupleParams &tp, unsigned long long *st,
+                          hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_jp_init, dim3(grid_of(n, 8192)), dim3(kBlock), 0, s, n, tp, pr, cround,
-                       color);
+    hipLaunchKernelGGL(k_jp_init, dim3(grid_of(n, 8192)), dim3(kBlock), 0, s, n, tp, st);
     return hipGetLastError();
 }
 
-hipError_t launch_jp_round(int64_t n, const int64_t *row_ptr, const int32_t *col,
-                           const uint32_t *pr, int32_t *cround, int32_t *color, int r,
-                           uint32_t *d_left, uint32_t *d_maxc, hipStream_t s) {
+hipError_t launch_jp_pass(int64_t n, const int64_t *row_ptr, const int32_t *col,
+                          unsigned long long *st, int32_t *color, int32_t *list, uint32_t *cnt,
+                          bool first, uint32_t *left, uint32_t *maxc, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_jp_round, dim3(grid_of(n, 4096)), dim3(kBlock), 0, s, n, row_ptr, col,
-                       pr, cround, color, r, d_left, d_maxc);
+    // wavefronts of at least 64 vertices, a multiple of 8 workgroups (one run
+    // of them per XCD), all resident at once
+    int64_t blocks = (n + 4 * kBlock - 1) / (4 * kBlock);
+    blocks = std::max<int64_t>(8, std::min<int64_t>((blocks + 7) / 8 * 8, 2048));
+    const int64_t waves = blocks * (kBlock / 64);
+    hipLaunchKernelGGL(k_jp_pass, dim3((unsigned)blocks), dim3(kBlock), 0, s, n, row_ptr, col, st,
+                       color, list, cnt, (n + waves - 1) / waves, first ? 1 : 0, left, maxc);
+    return hipGetLastError();
+}
+
+int64_t color_sort_counts(int64_t n, int32_t n_colors) {
+    return n_colors <= kSortColors ? (n + kColorTile - 1) / kColorTile * n_colors : 0;
+}
+
+hipError_t launch_color_sort(int64_t n, const int32_t *color, int32_t n_colors, uint32_t *cnt,
+                             int64_t *pos, unsigned long long *part, int32_t *out, int64_t *first,
+                             hipStream_t s) {
+    const int64_t tiles = (n + kColorTile - 1) / kColorTile;
+    if (n <= 0 || n_colors > kSortColors || tiles > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_color_count, dim3((unsigned)tiles), dim3(kBlock), 0, s, n, color, n_colors,
+                       tiles, cnt);
+    const hipError_t e = exclusive_scan_u32_i64(cnt, tiles * n_colors, pos, part, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_color_scatter, dim3((unsigned)tiles), dim3(kBlock), 0, s, n, color,
+                       n_colors, tiles, (const int64_t *)pos, out, first);
+    return hipGetLastError();
+}
+
+hipError_t launch_point_plan(int64_t n, const int32_t *rows, int32_t *pos, int64_t *cluster_off,
+                             hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_point_plan, dim3(grid_of(n + 1, 8192)), dim3(kBlock), 0, s, n, rows, pos,
+                       cluster_off);
     return hipGetLastError();
 }
 
@@ -571,19 +740,24 @@ hipError_t launch_color_hist(int64_t n, const int32_t *color, int32_t n_colors, 
     return hipGetLastError();
 }
 
+hipError_t launch_sort_members(int64_t nc, const int64_t *moff, int32_t *members, hipStream_t s) {
+    if (nc <= 0) return hipSuccess;
+    const int64_t sblocks = (nc + kBlock / 64 - 1) / (kBlock / 64);
+    if (sblocks > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_sort_small, dim3((unsigned)sblocks), dim3(kBlock), 0, s, nc, moff,
+                       members);
+    hipLaunchKernelGGL(k_sort_large, dim3(grid_of(nc, 1024)), dim3(kBlock), 0, s, nc, moff,
+                       members);
+    return hipGetLastError();
+}
+
 hipError_t launch_sorted_members(int64_t n, const int32_t *cluster, int64_t nc,
                                  const int64_t *moff, uint32_t *cursor, int32_t *members,
                                  hipStream_t s) {
     if (n <= 0 || nc <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_scatter_members, dim3(grid_of(n, 8192)), dim3(kBlock), 0, s, n, cluster,
                        moff, cursor, members);
-    const int64_t sblocks = (nc + kBlock / 64 - 1) / (kBlock / 64);
-    if (sblocks > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_sort_small, dim3((unsigned)sblocks), dim3(kBlock), 0, s, nc, moff,
-                       members);
-    hipLaunchKernelGGL(k_sort_large, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(nc, 1024))),
-                       dim3(kBlock), 0, s, nc, moff, members);
-    return hipGetLastError();
+    return launch_sort_members(nc, moff, members, s);
 }
 
 hipError_t launch_gather_sizes(int64_t nk, const int32_t *order, const uint32_t *cnt,

@@ -363,15 +363,31 @@ hipError_t launch_c_values(int64_t n_agg, int64_t c_nnz, const int64_t *moff,
                            const int64_t *aptr, const int32_t *acol, const double *aval,
                            const int64_t *crow, const int32_t *ccol, double *cval, hipStream_t s);
 // cgs.hip: Algorithm 4 (cluster multicolor Gauss-Seidel).
-hipError_t launch_jp_init(int64_t n, const TupleParams &tp, uint32_t *pr, int32_t *cround,
-                          int32_t *color, hipStream_t s);
-hipError_t launch_jp_round(int64_t n, const int64_t *row_ptr, const int32_t *col,
-                           const uint32_t *pr, int32_t *cround, int32_t *color, int r,
-                           uint32_t *d_left, uint32_t *d_maxc, hipStream_t s);
+// st: [n] states (tuple, colour).  A pass colours what it can; list and cnt
+// ([n] each, but cnt at least 32) carry the uncoloured vertices from launch to
+// launch, *left (zero before it) is set when some remain, *maxc keeps the
+// largest colour.
+hipError_t launch_jp_init(int64_t n, const TupleParams &tp, unsigned long long *st,
+                          hipStream_t s);
+hipError_t launch_jp_pass(int64_t n, const int64_t *row_ptr, const int32_t *col,
+                          unsigned long long *st, int32_t *color, int32_t *list, uint32_t *cnt,
+                          bool first, uint32_t *left, uint32_t *maxc, hipStream_t s);
+// out = the ids 0 .. n - 1 by colour, then id; first[c] = where colour c
+// begins.  cnt / pos: color_sort_counts(n, n_colors) (+ 1) entries, at most n
+// (+ 1); 0 says that there are too many colours for it.
+int64_t color_sort_counts(int64_t n, int32_t n_colors);
+hipError_t launch_color_sort(int64_t n, const int32_t *color, int32_t n_colors, uint32_t *cnt,
+                             int64_t *pos, unsigned long long *part, int32_t *out, int64_t *first,
+                             hipStream_t s);
+// A point plan's pos and cluster_off from its rows.
+hipError_t launch_point_plan(int64_t n, const int32_t *rows, int32_t *pos, int64_t *cluster_off,
+                             hipStream_t s);
 hipError_t launch_iota(int64_t n, int32_t *out, hipStream_t s);
 hipError_t launch_count_of(int64_t n, const int32_t *key, uint32_t *cnt, hipStream_t s);
 hipError_t launch_color_hist(int64_t n, const int32_t *color, int32_t n_colors, uint32_t *hist,
                              hipStream_t s);
+// The members of each cluster in increasing id, in place.
+hipError_t launch_sort_members(int64_t nc, const int64_t *moff, int32_t *members, hipStream_t s);
 // members[moff[a] .. moff[a+1]) = the rows of cluster a in increasing id
 // (cursor zero on entry).
 hipError_t launch_sorted_members(int64_t n, const int32_t *cluster, int64_t nc,
