@@ -333,9 +333,8 @@ RoundsArgs round_args(const mis2_ctx *ctx, const mis2_graph *g, uint64_t seed,
 }
 
 // long_rows: for an unmasked run, out: 1 if round 0 met rows longer than the
-// cooperative threshold, 0 if not (or if the run ended before round 1
-// started); for a masked run, in: the value of the unmasked run of the same
-// graph.  Refresh Column compacts (launch modes 1 then 2) only when it is 1.
+// cooperative threshold, 0 if not, -1 if the run did not say; for a masked run,
+// in: the value of the unmasked run of the same graph.  Refresh Column compacts (launch modes 1 then 2) only when it is 1.
 // The ablation kernels' configuration (null: the production kernels).
 struct AblRun {
     bool unpacked = false;  // three-field tuples
@@ -384,7 +383,7 @@ int run_rounds(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Workspac
     // rounds ahead.
     if (!filled) HIP_TRY(ctx, launch_fill_spans(round_fills(g, ws, masked), s));
     if (ctx->plan.persistent && !abl) {
-        if (!masked) *long_rows = 0;
+        if (!masked) *long_rows = -1;
         int rc = run_rounds_persistent(ctx, g, seed, ws, gm, masked, phase, s, iters_out, launches,
                                        lanes);
         if (rc != kFallBack) return rc;
@@ -466,7 +465,7 @@ int run_rounds(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Workspac
                                              coop_threshold(lanes), rt_host,
                                              ctx->alive_host + 2 + phase, s, lt.e0, lt.e1));
                     launches->push_back(lt);
-                    if (!masked) *long_rows = longs > 0 ? 1 : 0;
+                    if (!masked) *long_rows = longs;
                     // the tail stamps its rounds' phases in the round table
                     ctx->stamps_valid[phase] = 1;
                     *iters_out = round;
@@ -536,7 +535,7 @@ int run_rounds(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Workspac
         if (idle > kProgressTimeoutS)
             return fail(ctx, MIS2_EHIP, "no MIS-2 round started for %.0f s", idle);
     }
-    if (!masked) *long_rows = longs > 0 ? 1 : 0;
+    if (!masked) *long_rows = longs;
     ctx->stamps_valid[phase] = 0;
     *iters_out = round;  // rounds issued; parse_trace gives the count after the sync
     return queue_trace(ctx, ws, phase, round, s, true);
@@ -1513,18 +1512,21 @@ int aggregate_impl(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int32_t *a
     p3_io.n = n;
     p3_io.seg = gm.seg;
     p3_io.S = gm.S;
-    SegIO long_io = p3_io;
-    long_io.wl_in = ws.wl1[1];
-    long_io.cnt_in = ws.cnt1[1];
-    long_io.wl_out = nullptr;
-    long_io.cnt_out = nullptr;
+    SegIO mid_io = p3_io;
+    mid_io.wl_in = ws.wl1[1];
+    mid_io.cnt_in = ws.cnt1[1];
+    mid_io.wl_out = ws.wl1[0];  // rows longer still, for the third
+    mid_io.cnt_out = ws.cnt1[0];
     // phase 3 keeps rows of up to 8 chunks of L entries in registers and
     // hands longer ones to a one-row-per-wavefront pass: 4 lanes at least,
     // or every 27-point row would be long (27-point 100^3 aggregation with
     // 1 lane: 1.7 ms, with 4: 0.78 ms)
     const int p3_lanes = std::max(4, group_lanes(lanes_for(ctx, g)));
+    // phase 1 has seen every row: none past the cooperative threshold, or any
+    const int64_t max_row = long_rows == 0 && lanes_for(ctx, g) > 0
+                                ? coop_threshold(lanes_for(ctx, g)) : INT64_MAX;
     HIP_TRY(ctx, launch_phase3(p3_lanes, gm.blocks, g->row_ptr, g->col, ws.label,
-                               ws.aggsize, p3_io, long_io, agg_id, sc + kS_Err, s));
+                               ws.aggsize, p3_io, mid_io, max_row, agg_id, sc + kS_Err, s));
 
     HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, sc, 8 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));

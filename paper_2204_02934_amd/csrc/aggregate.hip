@@ -314,7 +314,7 @@ __device__ __forceinline__ void p3_count(const int32_t (&a)[K], const int32_t (&
 // One group of L lanes per unaggregated row of the wavefront's segment.  Rows
 // of at most K chunks of L entries are counted in registers; longer rows are
 // listed, in order, in the wavefront's segment of io.wl_out for
-// k_phase3_long.  The group's best candidate is reduced with the candidate
+// k_phase3_mid.  The group's best candidate is reduced with the candidate
 // order above.
 template <int L>
 __global__ __launch_bounds__(kBlock) void k_phase3(const int64_t *__restrict__ row_ptr,
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(kBlock) void k_phase3(const int64_t *__restrict__ r
             e = row_ptr[v + 1];
         }
         const bool is_long = e - s > (int64_t)K * L;
-        const int64_t es = is_long ? s : e;  // long rows are left to k_phase3_long
+        const int64_t es = is_long ? s : e;  // long rows are left to k_phase3_mid
         const int64_t wmax = group_max64<64>((es - s + L - 1) / L);
         int bc = 0, bs = 0x7FFFFFFF, ba = 0x7FFFFFFF;
         if (wmax > 0) {
@@ -377,24 +377,122 @@ __global__ __launch_bounds__(kBlock) void k_phase3(const int64_t *__restrict__ r
     if (lane == 0) io.cnt_out[w] = kept;
 }
 
-// Long unaggregated rows, one at a time per wavefront: the couplings are
-// counted in an LDS hash map (aggregate id -> count) of cap slots, cap the
-// power of two >= 2 * len between 64 and kP3Slots, so that clearing and
-// reading the map cost in proportion to the row (every row of up to
-// kP3Slots entries fits: it has at most len distinct ids); then the
-// wavefront reduces its entries with the candidate order.  Rows longer than
-// kP3Slots count each label against the whole row, 64 labels at a time.
-// The grid is small enough to be resident at once (the map takes 64 KiB per
-// workgroup): wavefront w takes the list segments w, w + W, w + 2W, ... (W
-// wavefronts in the grid), reading 64 segment sizes in one load.  Measured on
-// gfx950 (Chung-Lu 4M, 22 791 rows of 33-291 entries): one wavefront per
-// segment with the whole 2048-slot map for every row took 288 us.
-constexpr int kP3Slots = 2048;
-constexpr int kP3LongBlocks = 512;  // 2 resident workgroups on each of 256 compute units
-
-__device__ __forceinline__ void p3_reduce(int &bc, int &bs, int &ba) {
-    p3_group_best<64>(bc, bs, ba);
+// Rows of up to kP3Mid entries, one wavefront each, K entries per lane in
+// registers.  A row couples to few aggregates (a 27-point row of three
+// unknowns: 80 entries, some 6 aggregates), so they are counted one by one: the
+// first lane not yet counted names its label, and ballots count it among all
+// K * 64 entries.  Returns (scalars) the best candidate in the order above.
+constexpr int kP3Mid = 512;
+template <int K>
+__device__ __forceinline__ void p3_mid_row(const int32_t *__restrict__ col,
+                                           const int32_t *__restrict__ label,
+                                           const int32_t *__restrict__ aggsize, int64_t s, int len,
+                                           int &bc, int &bs, int &ba) {
+    const int lane = (int)(threadIdx.x & 63u);
+    int32_t a[K], sz[K];
+#pragma unroll
+    for (int k = 0; k < K; k++) a[k] = col[s + min(k * 64 + lane, len - 1)];
+#pragma unroll
+    for (int k = 0; k < K; k++) a[k] = label[a[k]];
+    uint64_t left[K];
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        if (k * 64 + lane >= len) a[k] = kPad;
+        left[k] = __ballot(a[k] >= 0);
+        sz[k] = aggsize[a[k] >= 0 ? a[k] : 0];
+    }
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        while (left[k]) {
+            const int l = __ffsll((unsigned long long)left[k]) - 1;
+            const int32_t y = __builtin_amdgcn_readlane(a[k], l);
+            const int ysz = __builtin_amdgcn_readlane(sz[k], l);
+            int c = 0;
+#pragma unroll
+            for (int q = k; q < K; q++) {
+                const uint64_t eq = __ballot(a[q] == y);
+                c += __popcll(eq);
+                left[q] &= ~eq;
+            }
+            if (better(c, ysz, y, bc, bs, ba)) {
+                bc = c;
+                bs = ysz;
+                ba = y;
+            }
+        }
+    }
 }
+
+// The rows k_phase3 listed: those of up to kP3Mid entries here, longer ones
+// listed again, in order, for k_phase3_long.  `share` wavefronts take one
+// segment's rows between them, so the device is full where segments are few.
+// It is bound by each row's chain of loads (columns, labels, sizes); without
+// LDS eight wavefronts per SIMD hide it.  Elasticity 60^3 (rows of 80): an LDS
+// hash map per wavefront, 16 KiB and so two per SIMD, took 285 us.
+__global__ __launch_bounds__(kBlock) void k_phase3_mid(const int64_t *__restrict__ row_ptr,
+                                                       const int32_t *__restrict__ col,
+                                                       const int32_t *__restrict__ label,
+                                                       const int32_t *__restrict__ aggsize,
+                                                       SegIO io, int share,
+                                                       int32_t *__restrict__ agg_out,
+                                                       uint32_t *__restrict__ err) {
+    const int lane = (int)(threadIdx.x & 63u);
+    const int64_t id = wave_id();
+    const int64_t w = id / share;
+    const int part = (int)(id % share);
+    if (w >= io.S) return;
+    const int64_t count = io.cnt_in[w], sbase = w * io.seg;
+    uint32_t kept = 0;
+    for (int64_t i0 = 0; i0 < count; i0 += 64) {
+        const bool valid = i0 + lane < count;
+        const int32_t v = valid ? io.wl_in[sbase + i0 + lane] : 0;
+        const int64_t s = row_ptr[v], d = row_ptr[v + 1] - s;
+        const bool longer = valid && d > kP3Mid;
+        const int len = (int)min(d, (int64_t)kP3Mid);
+        const uint64_t again = __ballot(longer);
+        if (part == 0) {
+            if (longer) io.wl_out[sbase + kept + (uint32_t)__popcll(again & lanes_below(lane))] = v;
+            kept += (uint32_t)__popcll(again);
+        }
+        uint64_t todo = __ballot(valid && !longer && lane % share == part);
+        while (todo) {
+            const int l = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1;
+            const int32_t vr = __builtin_amdgcn_readlane(v, l);
+            const int lr = __builtin_amdgcn_readlane(len, l);
+            const int64_t sr =
+                (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(s >> 32), l) << 32) |
+                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)s, l));
+            int bc = 0, bs = 0x7FFFFFFF, ba = 0x7FFFFFFF;
+            if (lr <= 64)
+                p3_mid_row<1>(col, label, aggsize, sr, lr, bc, bs, ba);
+            else if (lr <= 128)
+                p3_mid_row<2>(col, label, aggsize, sr, lr, bc, bs, ba);
+            else
+                p3_mid_row<kP3Mid / 64>(col, label, aggsize, sr, lr, bc, bs, ba);
+            if (lane == 0) {
+                if (bc > 0)
+                    agg_out[vr] = ba;
+                else
+                    atomicOr(err, 1u);
+            }
+        }
+    }
+    if (part == 0 && lane == 0) io.cnt_out[w] = kept;
+}
+
+// Rows of more than kP3Mid entries, one workgroup each: the couplings are
+// counted in an LDS hash map (aggregate id -> count) of kP3Slots slots, of the
+// ids in one of `parts` classes of a hash at a time, parts chosen so that a
+// class is expected to fill half the map; a class that does not fit restarts
+// the row with twice the classes.  The workgroup then reduces the entries with
+// the candidate order.  (One wavefront that compared every label with
+// the whole row took 3.7 ms for one launch on a coarse level of Chung-Lu 1M,
+// rows of some 6000 entries.)  The grid is resident at once (64 KiB per
+// workgroup): workgroup w takes the segments w, w + W, ..., reading kBlock
+// sizes in one load.
+constexpr int kP3Slots = 8192;
+constexpr int kP3LongBlocks = 512;  // 2 resident workgroups on each of 256 compute units
 
 __global__ __launch_bounds__(kBlock) void k_phase3_long(const int64_t *__restrict__ row_ptr,
                                                         const int32_t *__restrict__ col,
@@ -403,100 +501,113 @@ __global__ __launch_bounds__(kBlock) void k_phase3_long(const int64_t *__restric
                                                         SegIO io, int32_t *__restrict__ agg_out,
                                                         uint32_t *__restrict__ err) {
     constexpr uint32_t kEmpty = 0xFFFFFFFFu;
-    __shared__ uint32_t keys_s[kBlock / 64][kP3Slots];
-    __shared__ uint32_t cnts_s[kBlock / 64][kP3Slots];
-    uint32_t *keys = keys_s[threadIdx.x >> 6];
-    uint32_t *cnts = cnts_s[threadIdx.x >> 6];
-    const int lane = (int)(threadIdx.x & 63u);
-    const int64_t W = (int64_t)gridDim.x * (kBlock / 64);
-    const int64_t w = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-    for (int64_t w0 = w; w0 < io.S; w0 += 64 * W) {
-        const int64_t mine = w0 + (int64_t)lane * W;  // the segment this lane reads the size of
-        const uint32_t my_count = mine < io.S ? io.cnt_in[mine] : 0u;
-        uint64_t todo = __ballot(my_count != 0u);
-        while (todo) {
-            const int j = __ffsll((unsigned long long)todo) - 1;
-            todo &= todo - 1;
-            const int64_t count = __shfl((int)my_count, j, 64);
-            const int64_t sbase = (w0 + (int64_t)j * W) * io.seg;
-            for (int64_t i = 0; i < count; i++) {
-                const int32_t v = io.wl_in[sbase + i];
-                const int64_t s = row_ptr[v], e = row_ptr[v + 1];
-                int bc = 0, bs = 0x7FFFFFFF, ba = 0x7FFFFFFF;
-                if (e - s <= kP3Slots) {
-                    int lg = 6;
-                    while ((int64_t)1 << lg < 2 * (e - s) && lg < 11) lg++;
-                    const uint32_t cap = 1u << lg;
-                    for (uint32_t k = (uint32_t)lane; k < cap; k += 64) {
-                        keys[k] = kEmpty;
-                        cnts[k] = 0u;
-                    }
-                    wave_lds_sync();
-                    for (int64_t j0 = s; j0 < e; j0 += 64 * kCoopLoads) {
-                        int32_t x[kCoopLoads];
+    constexpr int kBits = __builtin_ctz(kP3Slots), kWv = kBlock / 64;
+    constexpr uint32_t kMost = kP3Slots * 3 / 4;  // ids in the map; each thread may add one more
+    static_assert(kMost + kBlock < kP3Slots, "a probe always ends at an empty slot");
+    __shared__ uint32_t keys[kP3Slots], cnts[kP3Slots];
+    __shared__ uint32_t num;
+    __shared__ uint64_t marks[kWv];
+    __shared__ uint32_t counts[kBlock];
+    __shared__ int best[kWv][3];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    volatile uint32_t *vnum = &num;
+    auto row = [&](const int32_t v) {
+        const int64_t s = row_ptr[v], e = row_ptr[v + 1];
+        int bc = 0, bs = 0x7FFFFFFF, ba = 0x7FFFFFFF;
+        // (a class value is shared by some 128 ids, so doubling comes to an end)
+        uint32_t parts = (uint32_t)((e - s + kP3Slots / 2 - 1) / (kP3Slots / 2));
+        for (uint32_t p = 0; p < parts;) {
+            for (int k = tid; k < kP3Slots; k += kBlock) {
+                keys[k] = kEmpty;
+                cnts[k] = 0u;
+            }
+            if (tid == 0) num = 0u;
+            __syncthreads();
+            for (int64_t j0 = s; j0 < e; j0 += kBlock * kCoopLoads) {
+                int32_t a[kCoopLoads];
 #pragma unroll
-                        for (int k = 0; k < kCoopLoads; k++) {
-                            const int64_t jj = j0 + (int64_t)k * 64 + lane;
-                            x[k] = col[jj < e ? jj : s];
-                        }
-                        int32_t a[kCoopLoads];
+                for (int k = 0; k < kCoopLoads; k++) a[k] = col[min(j0 + k * kBlock + tid, e - 1)];
 #pragma unroll
-                        for (int k = 0; k < kCoopLoads; k++) a[k] = label[x[k]];
+                for (int k = 0; k < kCoopLoads; k++) a[k] = label[a[k]];
 #pragma unroll
-                        for (int k = 0; k < kCoopLoads; k++) {
-                            if (j0 + (int64_t)k * 64 + lane < e && a[k] >= 0) {
-                                const uint32_t key = (uint32_t)a[k];
-                                uint32_t h = (key * 2654435761u) >> (32 - lg);
-                                for (;;) {  // the map has a slot for every entry of the row
-                                    const uint32_t prev = atomicCAS(&keys[h], kEmpty, key);
-                                    if (prev == kEmpty || prev == key) break;
-                                    h = (h + 1) & (cap - 1);
-                                }
-                                atomicAdd(&cnts[h], 1u);
-                            }
+                for (int k = 0; k < kCoopLoads; k++) {
+                    if (j0 + k * kBlock + tid >= e || a[k] < 0) continue;
+                    const uint32_t key = (uint32_t)a[k], h0 = key * 2654435761u;
+                    // the class by other bits than the slot
+                    if (((h0 & 0xFFFFu) ^ (key >> 7)) % parts != p) continue;
+                    uint32_t h = h0 >> (32 - kBits);
+                    for (;;) {
+                        uint32_t prev = keys[h];
+                        if (prev == kEmpty) {
+                            if (*vnum > kMost) break;  // too full: the row restarts
+                            prev = atomicCAS(&keys[h], kEmpty, key);
+                            if (prev == kEmpty) atomicAdd(&num, 1u);
                         }
-                    }
-                    wave_lds_sync();
-                    for (uint32_t k = (uint32_t)lane; k < cap; k += 64) {
-                        const uint32_t key = keys[k];
-                        if (key != kEmpty) {
-                            const int c = (int)cnts[k], sz = aggsize[key];
-                            if (better(c, sz, (int)key, bc, bs, ba)) {
-                                bc = c;
-                                bs = sz;
-                                ba = (int)key;
-                            }
+                        if (prev == kEmpty || prev == key) {
+                            atomicAdd(&cnts[h], 1u);
+                            break;
                         }
-                    }
-                    wave_lds_sync();
-                } else {
-                    for (int64_t c1 = s; c1 < e; c1 += 64) {
-                        const int64_t jj = c1 + lane;
-                        const int32_t a = jj < e ? label[col[jj]] : kPad;
-                        int cnt = 0;
-                        for (int64_t c2 = s; c2 < e; c2 += 64) {
-                            const int64_t j2 = c2 + lane;
-                            const int32_t a2 = j2 < e ? label[col[j2]] : kPad;
-                            for (int t = 0; t < 64; t++)
-                                cnt += (__builtin_amdgcn_readlane(a2, t) == a);
-                        }
-                        if (a >= 0) {
-                            const int sz = aggsize[a];
-                            if (better(cnt, sz, a, bc, bs, ba)) {
-                                bc = cnt;
-                                bs = sz;
-                                ba = a;
-                            }
-                        }
+                        h = (h + 1) & (kP3Slots - 1);
                     }
                 }
-                p3_reduce(bc, bs, ba);
-                if (lane == 0) {
-                    if (bc > 0)
-                        agg_out[v] = ba;
-                    else
-                        atomicOr(err, 1u);
+            }
+            __syncthreads();
+            const bool full = *vnum > kMost;
+            if (!full)
+                for (int k = tid; k < kP3Slots; k += kBlock) {
+                    const uint32_t key = keys[k];
+                    if (key == kEmpty) continue;
+                    const int c = (int)cnts[k], sz = aggsize[key];
+                    if (better(c, sz, (int)key, bc, bs, ba)) {
+                        bc = c;
+                        bs = sz;
+                        ba = (int)key;
+                    }
                 }
+            __syncthreads();  // the map is cleared next
+            if (full) {
+                parts *= 2;  // the candidates seen so far stay: they are whole counts
+                p = 0;
+            } else {
+                p++;
+            }
+        }
+        p3_group_best<64>(bc, bs, ba);
+        if (lane == 0) {
+            best[wv][0] = bc;
+            best[wv][1] = bs;
+            best[wv][2] = ba;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            for (int q = 1; q < kWv; q++)
+                if (better(best[q][0], best[q][1], best[q][2], bc, bs, ba)) {
+                    bc = best[q][0];
+                    bs = best[q][1];
+                    ba = best[q][2];
+                }
+            if (bc > 0)
+                agg_out[v] = ba;
+            else
+                atomicOr(err, 1u);
+        }
+        __syncthreads();
+    };
+    const int64_t W = gridDim.x;
+    for (int64_t w0 = blockIdx.x; w0 < io.S; w0 += kBlock * W) {
+        const int64_t mine = w0 + tid * W;
+        const uint32_t c = mine < io.S ? io.cnt_in[mine] : 0u;
+        const uint64_t any = __ballot(c != 0u);
+        __syncthreads();
+        counts[tid] = c;
+        if (lane == 0) marks[wv] = any;
+        __syncthreads();
+        for (int q = 0; q < kWv; q++) {
+            for (uint64_t todo = marks[q]; todo; todo &= todo - 1) {
+                const int j = q * 64 + __ffsll((unsigned long long)todo) - 1;
+                const uint32_t count = counts[j];
+                const int64_t sbase = (w0 + (int64_t)j * W) * io.seg;
+                for (uint32_t i = 0; i < count; i++) row(io.wl_in[sbase + i]);
             }
         }
     }
@@ -668,11 +779,25 @@ hipError_t launch_join_min(int lanes, int blocks, const int64_t *row_ptr, const 
 
 hipError_t launch_phase3(int lanes, int blocks, const int64_t *row_ptr, const int32_t *col,
                          const int32_t *label, const int32_t *aggsize, const SegIO &io,
-                         const SegIO &io_long, int32_t *agg_out, uint32_t *err, hipStream_t s) {
+                         const SegIO &io_mid, int64_t max_row, int32_t *agg_out, uint32_t *err,
+                         hipStream_t s) {
     MIS2_P3_DISPATCH(lanes, dim3(blocks), dim3(kBlock), 0, s, row_ptr, col, label, aggsize, io,
                      agg_out, err);
-    hipLaunchKernelGGL(k_phase3_long, dim3(std::min(blocks, kP3LongBlocks)), dim3(kBlock), 0, s,
-                       row_ptr, col, label, aggsize, io_long, agg_out, err);
+    if (max_row > 32) {  // k_phase3 keeps up to 32 entries whatever its lanes
+        // about 8 wavefronts per SIMD (of 1024)
+        const int share = (int)std::max<int64_t>(1, std::min<int64_t>(8, 8192 / io_mid.S));
+        hipLaunchKernelGGL(k_phase3_mid, dim3((unsigned)(blocks * share)), dim3(kBlock), 0, s,
+                           row_ptr, col, label, aggsize, io_mid, share, agg_out, err);
+    }
+    if (max_row > kP3Mid) {
+        SegIO io_long = io_mid;
+        io_long.wl_in = io_mid.wl_out;
+        io_long.cnt_in = io_mid.cnt_out;
+        io_long.wl_out = nullptr;
+        io_long.cnt_out = nullptr;
+        hipLaunchKernelGGL(k_phase3_long, dim3(std::min(blocks * 4, kP3LongBlocks)), dim3(kBlock),
+                           0, s, row_ptr, col, label, aggsize, io_long, agg_out, err);
+    }
     return hipGetLastError();
 }
 

@@ -580,17 +580,20 @@ hipError_t launch_accept_phase2(int64_t n, const int64_t *row_ptr, const int32_t
 hipError_t launch_list_unlabelled(int blocks, int64_t n, const int32_t *label, int32_t *copy_to,
                                   const SegIO &io,
                                   hipStream_t s);
-// io: the unaggregated rows (wl_in / cnt_in) and the list of long rows it
-// leaves (wl_out / cnt_out); io_long: that list as input.
 // Algorithm 2's second loop over the unaggregated vertices listed in io
 // (wl_in / cnt_in): agg_out[v] = the smallest first-loop label among v's
 // neighbours; bit 1 of *err if there is none.
 hipError_t launch_join_min(int lanes, int blocks, const int64_t *row_ptr, const int32_t *col,
                            const int32_t *label, const SegIO &io, int32_t *agg_out,
                            uint32_t *err, hipStream_t s);
+// io: the unaggregated rows (wl_in / cnt_in) and the list of longer rows it
+// leaves (wl_out / cnt_out); io_mid: that list as input, and a list for the
+// rows it leaves.  max_row: no row of the graph is longer (kernels that would
+// find nothing are not launched).
 hipError_t launch_phase3(int lanes, int blocks, const int64_t *row_ptr, const int32_t *col,
                          const int32_t *label, const int32_t *aggsize, const SegIO &io,
-                         const SegIO &io_long, int32_t *agg_out, uint32_t *err, hipStream_t s);
+                         const SegIO &io_mid, int64_t max_row, int32_t *agg_out, uint32_t *err,
+                         hipStream_t s);
 
 // Batched coarsening (abi.hip).  The arena is the caller's workspace: the
 // coarsening workspace of the union, two coarse-union CSR buffers, the
