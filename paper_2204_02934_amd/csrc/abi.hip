@@ -863,6 +863,55 @@ int apply_plan(mis2_ctx *ctx, const mis2_graph *g, const Workspace &ws, hipStrea
     return MIS2_OK;
 }
 
+// Whether a graph takes the one-workgroup form: it fits, nothing about the
+// launches was asked for (an explicit plan, the fixed degree rule, per-sweep
+// timing or accounting), and so their records need not be made.
+bool takes_small(const mis2_ctx *ctx, const mis2_graph *g) {
+    return small_fits(g->n, g->nnz) && ctx->autotune && !ctx->profile && !ctx->account &&
+           ctx->plan.lanes == 0 && ctx->plan.blocks == 0 && !ctx->plan.persistent &&
+           ctx->plan.compact && ctx->plan.tail < 0 && ctx->plan.ahead == 0;
+}
+
+// Its launch and the synchronisation after it; the phases' rounds are recorded
+// as those of a tail launch that runs from round 0 on.
+int run_small(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, uint8_t *status, int32_t *agg,
+              uint8_t *roots, int32_t *list1, int32_t *list2, uint32_t *scalars, hipStream_t s,
+              std::vector<Launch> *launches) {
+    const TupleParams tp = tparams(ctx, g->n, seed, 0);
+    SmallArgs a;
+    a.row_ptr = g->row_ptr;
+    a.col = g->col;
+    a.n = g->n;
+    a.nnz = g->nnz;
+    a.seed = seed;
+    a.pmask = tp.pmask;
+    a.b = tp.b;
+    a.batch = ctx->batch;
+    a.status = status;
+    a.agg = agg;
+    a.roots = roots;
+    a.list1 = list1;
+    a.list2 = list2;
+    a.scalars = scalars;
+    a.host = ctx->pinned;
+    a.end_host = ctx->alive_host + 2;
+    for (int k = 0; k < 2; k++) {
+        a.rt_host[k] = ctx->pinned_rt + (size_t)k * (kTraceCap + 2) * kRoundStride;
+        __atomic_store_n(ctx->alive_host + 2 + k, 0ull, __ATOMIC_RELEASE);
+    }
+    HIP_TRY(ctx, launch_small(a, agg != nullptr, s));
+    HIP_TRY(ctx, hipStreamSynchronize(s));
+    for (int k = 0; k < (agg ? 2 : 1); k++) {
+        ctx->tail_used[k] = 1;
+        ctx->stamps_valid[k] = 0;
+        const int rounds = parse_trace(ctx, k);
+        if (rounds + 2 >= kTraceCap)
+            return fail(ctx, MIS2_EINTERNAL, "more than %d rounds", kTraceCap - 2);
+        launches->push_back(Launch{3, k, 0, lanes_for(ctx, g), nullptr, nullptr});
+    }
+    return MIS2_OK;
+}
+
 // Restores the context's plan at the end of a call and records the one used.
 struct PlanScope {
     mis2_ctx *ctx;
@@ -1181,6 +1230,14 @@ int mis2_run(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, uint8_t *status,
 
     ctx->events_used = 0;
     std::vector<Launch> launches;
+    if (takes_small(ctx, g)) {
+        if ((rc = run_small(ctx, g, seed, status, nullptr, nullptr, nullptr, nullptr, nullptr, s,
+                            &launches)))
+            return rc;
+        if (n_roots) *n_roots = __atomic_load_n(ctx->pinned + kS_Roots, __ATOMIC_ACQUIRE);
+        if (n_iters) *n_iters = (int32_t)(ctx->trace[0].size() / 2);
+        return collect_sweeps(ctx, launches, ws, s);
+    }
     const Geometry gm = geometry(ctx, g->n, lanes_for(ctx, g));
     HIP_TRY(ctx, launch_init_tuples(tparams(ctx, g->n, seed, 0), g->n, ws.T,
                                     round_fills(g, ws, false), s));
@@ -1455,6 +1512,22 @@ int aggregate_impl(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int32_t *a
     ps.armed = true;
     ctx->events_used = 0;
     std::vector<Launch> launches;
+    if (takes_small(ctx, g)) {
+        int32_t *const list2 = ws.wl1[0];
+        if ((rc = run_small(ctx, g, seed, nullptr, agg_id, roots, P1 ? ws.list : nullptr,
+                            P1 ? list2 : nullptr, P1 ? sc : nullptr, s, &launches)))
+            return rc;
+        if (P1) {
+            HIP_TRY(ctx, launch_graph_bounds(ws.list, sc + kS_Count1, ctx->batch.voff, ctx->batch.G,
+                                             P1, s));
+            HIP_TRY(ctx, launch_graph_bounds(list2, sc + kS_Count2, ctx->batch.voff, ctx->batch.G,
+                                             P2, s));
+        }
+        if (ctx->pinned[kS_Err])
+            return fail(ctx, MIS2_EINTERNAL, "phase-3 vertex without an aggregated neighbour");
+        if (n_agg) *n_agg = (int64_t)ctx->pinned[kS_Count1] + (int64_t)ctx->pinned[kS_Count2];
+        return collect_sweeps(ctx, launches, ws, s);
+    }
     const Geometry gm = geometry(ctx, n, lanes_for(ctx, g));
 
     // Phase 1: MIS-2 of G; roots numbered by increasing id, each labelled with

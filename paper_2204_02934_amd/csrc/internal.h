@@ -567,6 +567,27 @@ hipError_t launch_gather_i64(const int64_t *src, const int64_t *idx, int64_t cou
                              hipStream_t s);
 hipError_t launch_graph_ids(int64_t n, const BatchInfo &bt, int32_t *gid, hipStream_t s);
 
+// small.hip: Algorithm 1 (agg false: status) or Algorithm 3 (agg true) of a
+// graph that small_fits, in one launch.
+struct SmallArgs {
+    const int64_t *row_ptr;
+    const int32_t *col;
+    int64_t n, nnz;
+    uint64_t seed, pmask;
+    uint32_t b;
+    BatchInfo batch;
+    uint8_t *status;              // [n], agg false
+    int32_t *agg;                 // [n], agg true
+    uint8_t *roots;               // [n] or null
+    int32_t *list1, *list2;       // the roots of phases 1 and 2 in order, or null
+    uint32_t *scalars;            // device: kS_Count1 and kS_Count2, or null
+    uint32_t *host;               // host-pinned scalars
+    uint32_t *rt_host[2];         // host-pinned round tables
+    unsigned long long *end_host; // host-pinned [2]: rounds of each run plus one
+};
+bool small_fits(int64_t n, int64_t nnz);
+hipError_t launch_small(const SmallArgs &a, bool agg, hipStream_t s);
+
 // aggregate.hip
 hipError_t launch_label_roots(int64_t n, const int64_t *row_ptr, const int32_t *col,
                               const int32_t *roots, const uint32_t *d_count,
