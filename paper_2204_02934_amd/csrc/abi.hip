@@ -1924,7 +1924,7 @@ int mis2_galerkin(mis2_ctx *ctx, const mis2_graph *g, const double *val, const d
 namespace {
 struct SmoothedWs {
     uint8_t *cls;  // [max(n, n_agg)] rows left to the large-set structure pass
-    uint32_t *size, *cnt, *cursor, *flag;
+    uint32_t *size, *cnt, *col_cnt, *flag;
     unsigned long long *part;
     int64_t *apptr, *moff;
     int32_t *prow_of, *members, *apcol;
@@ -1955,7 +1955,7 @@ SmoothedWs carve_smoothed(void *base, int64_t n, int64_t n_agg, int64_t p_nnz, i
     w.cls = (uint8_t *)take(std::max(un, ua));
     w.size = (uint32_t *)take(4 * ua);
     w.cnt = (uint32_t *)take(4 * std::max(un, ua));
-    w.cursor = (uint32_t *)take(4 * ua);
+    w.col_cnt = (uint32_t *)take(4 * ua);
     w.flag = (uint32_t *)take(64);
     w.part = (unsigned long long *)take(8 * (size_t)scan_parts(std::max<int64_t>(n, n_agg)));
     w.apptr = (int64_t *)take(8 * (un + 1));
@@ -2018,13 +2018,27 @@ int mis2_smoothed(mis2_ctx *ctx, const mis2_graph *g, const double *val, const d
         return fail(ctx, MIS2_EINVAL, "mis2_smoothed: aggregate id outside [0, n_agg)");
     HIP_TRY(ctx, launch_fill_u32(w.size, 0u, n_agg, s));
     HIP_TRY(ctx, launch_count_of(n, agg, w.size, s));
-    // P: structure (count, offsets, columns), then values
-    HIP_TRY(ctx, launch_smoothed_sym(0, false, n, g->row_ptr, g->col, agg, nullptr, nullptr,
-                                     nullptr, nullptr, nullptr, w.cnt, nullptr, nullptr,
-                                     w.flag + 1, w.cls, s));
-    HIP_TRY(ctx, exclusive_scan_u32_i64(w.cnt, n, prow, w.part, s));
+    // P: structure (count, offsets, columns), then values.  The count pass
+    // leaves the rows in the value array, idle until then, if that holds a
+    // graph's entries and one more per row
+    int32_t *const spare = pval && p_cap / 2 >= (n + g->nnz + 3) / 4 ? (int32_t *)pval : nullptr;
+    // counts the rows of a product, scans the counts into `ptr`, and reads the
+    // total and the flags back; once more where rows are left to the last pass
+    auto count = [&](int kind, int64_t rows, const int64_t *sptr, const int32_t *scol, int64_t *ptr,
+                     uint32_t *flag, int32_t *spare, int64_t *total) -> int {
+        for (int later = 0; later < 2; later++) {
+            HIP_TRY(ctx, launch_smoothed_sym(kind, false, rows, g->nnz, g->row_ptr, g->col, agg, sptr,
+                                             scol, w.moff, w.members, w.prow_of, w.cnt, nullptr,
+                                             nullptr, flag, w.cls, spare, later != 0, s));
+            HIP_TRY(ctx, exclusive_scan_u32_i64(w.cnt, rows, ptr, w.part, s));
+            const int rc2 = read_total(ctx, ptr + rows, flag, total, &flags, s);
+            if (rc2 || !(flags & kSymLarge)) return rc2;
+        }
+        return MIS2_OK;
+    };
     int64_t pn = 0;
-    if ((rc = read_total(ctx, prow + n, w.flag + 1, &pn, &flags, s))) return rc;
+    if ((rc = count(0, n, nullptr, nullptr, prow, w.flag + 1, spare, &pn))) return rc;
+    const uint32_t p_flags = flags;  // a P row past the limit is one of A P as well
     *p_nnz = pn;
     if (pn > (int64_t)0x7FFFFFFF)
         return fail(ctx, MIS2_EINVAL, "mis2_smoothed: P has more than 2^31 - 1 entries");
@@ -2037,18 +2051,19 @@ int mis2_smoothed(mis2_ctx *ctx, const mis2_graph *g, const double *val, const d
         return fail(ctx, MIS2_ENOSPACE, "mis2_smoothed: workspace of %zu bytes needed", need);
     }
     w = carve_smoothed(ctx->ws, n, n_agg, pn, 0);
-    HIP_TRY(ctx, launch_smoothed_sym(0, true, n, g->row_ptr, g->col, agg, nullptr, nullptr,
-                                     nullptr, nullptr, nullptr, nullptr, prow, pcol, w.flag + 1, w.cls,
-                                     s));
+    if (spare)
+        HIP_TRY(ctx, launch_p_copy(n, g->row_ptr, spare, prow, pcol, s));
+    else
+        for (int later = 0; later < (p_flags & kSymLarge ? 2 : 1); later++)
+            HIP_TRY(ctx, launch_smoothed_sym(0, true, n, g->nnz, g->row_ptr, g->col, agg, nullptr,
+                                             nullptr, nullptr, nullptr, nullptr, nullptr, prow, pcol,
+                                             w.flag + 1, w.cls, nullptr, later != 0, s));
     HIP_TRY(ctx, launch_p_values(n, pn, g->row_ptr, g->col, val, diag, agg, w.size, omega, prow,
                                  pcol, pval, w.prow_of, s));
     // AP = A P
-    HIP_TRY(ctx, launch_smoothed_sym(1, false, n, g->row_ptr, g->col, agg, prow, pcol, nullptr,
-                                     nullptr, nullptr, w.cnt, nullptr, nullptr, w.flag + 1, w.cls, s));
-    HIP_TRY(ctx, exclusive_scan_u32_i64(w.cnt, n, w.apptr, w.part, s));
     int64_t apn = 0;
-    if ((rc = read_total(ctx, w.apptr + n, w.flag + 1, &apn, &flags, s))) return rc;
-    if (flags & 1u)
+    if ((rc = count(1, n, prow, pcol, w.apptr, w.flag + 2, nullptr, &apn))) return rc;
+    if ((p_flags | flags) & kSymBad)
         return fail(ctx, MIS2_ENOSPACE, "mis2_smoothed: a row of A P has more than 2048 columns");
     need = smoothed_bytes(n, n_agg, pn, apn);
     if (ctx->ws_bytes < need) {
@@ -2056,35 +2071,27 @@ int mis2_smoothed(mis2_ctx *ctx, const mis2_graph *g, const double *val, const d
         return fail(ctx, MIS2_ENOSPACE, "mis2_smoothed: workspace of %zu bytes needed", need);
     }
     w = carve_smoothed(ctx->ws, n, n_agg, pn, apn);
-    HIP_TRY(ctx, launch_smoothed_sym(1, true, n, g->row_ptr, g->col, agg, prow, pcol, nullptr,
-                                     nullptr, nullptr, nullptr, w.apptr, w.apcol, w.flag + 1, w.cls, s));
-    HIP_TRY(ctx, launch_ap_values(n, apn, g->row_ptr, g->col, val, diag, prow, pcol, pval,
-                                  w.apptr, w.apcol, w.apval, s));
-    // R_a: the P entries of column a in increasing order (hence increasing row)
-    HIP_TRY(ctx, launch_fill_u32(w.cnt, 0u, n_agg, s));
-    HIP_TRY(ctx, launch_count_of(pn, pcol, w.cnt, s));
-    HIP_TRY(ctx, exclusive_scan_u32_i64(w.cnt, n_agg, w.moff, w.part, s));
-    HIP_TRY(ctx, launch_fill_u32(w.cursor, 0u, n_agg, s));
-    HIP_TRY(ctx, launch_sorted_members(pn, pcol, n_agg, w.moff, w.cursor, w.members, s));
+    // R_a: the P entries of column a in increasing order (hence increasing
+    // row); the ranks go where AP's values (at least as many) come later
+    int32_t *const rank = (int32_t *)w.apval;
+    HIP_TRY(ctx, launch_column_rank(pn, pcol, n_agg, w.col_cnt, rank, s));
+    HIP_TRY(ctx, exclusive_scan_u32_i64(w.col_cnt, n_agg, w.moff, w.part, s));
+    HIP_TRY(ctx, launch_column_scatter(pn, pcol, w.moff, rank, w.members, s));
+    HIP_TRY(ctx, launch_sort_members(n_agg, w.moff, w.members, s));
+    HIP_TRY(ctx, launch_ap_fill(n, g->row_ptr, g->col, val, diag, prow, pcol, pval, w.apptr, w.apcol,
+                                w.apval, w.cls, flags, s));
     // Ac = P^T (A P)
-    HIP_TRY(ctx, launch_smoothed_sym(2, false, n_agg, g->row_ptr, g->col, agg, w.apptr, w.apcol,
-                                     w.moff, w.members, w.prow_of, w.cnt, nullptr, nullptr,
-                                     w.flag + 1, w.cls, s));
-    HIP_TRY(ctx, exclusive_scan_u32_i64(w.cnt, n_agg, crow, w.part, s));
     int64_t cn = 0;
-    if ((rc = read_total(ctx, crow + n_agg, w.flag + 1, &cn, &flags, s))) return rc;
-    if (flags & 1u)
+    if ((rc = count(2, n_agg, w.apptr, w.apcol, crow, w.flag + 3, nullptr, &cn))) return rc;
+    if (flags & kSymBad)
         return fail(ctx, MIS2_ENOSPACE,
                     "mis2_smoothed: a row of the coarse operator has more than 2048 columns");
     *c_nnz = cn;
     if (cn > c_cap || (cn > 0 && (!ccol || !cval)))
         return fail(ctx, MIS2_ENOSPACE, "mis2_smoothed: the coarse operator has %lld entries, "
                     "room for %lld", (long long)cn, (long long)c_cap);
-    HIP_TRY(ctx, launch_smoothed_sym(2, true, n_agg, g->row_ptr, g->col, agg, w.apptr, w.apcol,
-                                     w.moff, w.members, w.prow_of, nullptr, crow, ccol,
-                                     w.flag + 1, w.cls, s));
-    HIP_TRY(ctx, launch_c_values(n_agg, cn, w.moff, w.members, w.prow_of, pval, w.apptr, w.apcol,
-                                 w.apval, crow, ccol, cval, s));
+    HIP_TRY(ctx, launch_c_fill(n_agg, w.moff, w.members, w.prow_of, pval, w.apptr, w.apcol, w.apval,
+                               crow, ccol, cval, w.cls, flags, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
     return MIS2_OK;
 }

@@ -202,11 +202,21 @@ __global__ __launch_bounds__(kBlock) void k_iota(int64_t n, int32_t *__restrict_
         out[v] = (int32_t)v;
 }
 
+// cnt[k] += the keys equal to k; one atomic for a run of equal keys.
 __global__ __launch_bounds__(kBlock) void k_count_of(int64_t n, const int32_t *__restrict__ key,
                                                      uint32_t *__restrict__ cnt) {
-    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
-         v += (int64_t)gridDim.x * kBlock)
-        atomicAdd(&cnt[key[v]], 1u);
+    const int lane = (int)(threadIdx.x & 63u);
+    // whole wavefronts stay in the loop together
+    for (int64_t v0 = (int64_t)blockIdx.x * kBlock + (threadIdx.x - lane); v0 < n;
+         v0 += (int64_t)gridDim.x * kBlock) {
+        const int64_t v = v0 + lane;
+        const int32_t k = v < n ? key[v] : -1;
+        const int32_t prev = (int32_t)from_prev((uint32_t)k);
+        const uint64_t heads = __ballot(lane == 0 || k != prev);
+        const uint64_t later = lane == 63 ? 0ull : heads >> (lane + 1);
+        const int len = later ? __ffsll((unsigned long long)later) : 64 - lane;
+        if ((heads >> lane & 1u) && k >= 0) atomicAdd(&cnt[k], (uint32_t)len);
+    }
 }
 
 // Colour histogram through a workgroup-local table (colours < kHistBins).
@@ -224,21 +234,33 @@ __global__ __launch_bounds__(kBlock) void k_color_hist(int64_t n, const int32_t 
         if (h[k]) atomicAdd(&hist[k], h[k]);
 }
 
-// members of cluster a at [moff[a], moff[a+1]) in any order.
-__global__ __launch_bounds__(kBlock) void k_scatter_members(int64_t n,
-                                                            const int32_t *__restrict__ cluster,
-                                                            const int64_t *__restrict__ moff,
-                                                            uint32_t *__restrict__ cursor,
-                                                            int32_t *__restrict__ members) {
-    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
-         v += (int64_t)gridDim.x * kBlock) {
-        const int32_t a = cluster[v];
-        members[moff[a] + atomicAdd(&cursor[a], 1u)] = (int32_t)v;
-    }
-}
-
 constexpr int kSortRegs = 8;  // members per lane
 constexpr int64_t kSmallCluster = 64 * kSortRegs;
+
+// K members per lane of m in all.
+template <int K>
+__device__ __forceinline__ void sort_regs(int m, int32_t *members) {
+    const int lane = threadIdx.x & 63;
+    int32_t x[K];
+    int rank[K];
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        x[k] = k * 64 + lane < m ? members[k * 64 + lane] : 0x7fffffff;
+        rank[k] = 0;
+    }
+#pragma unroll
+    for (int q = 0; q < K; q++) {
+        const int mq = m - q * 64 < 64 ? m - q * 64 : 64;
+        for (int w = 0; w < mq; w++) {
+            const int32_t y = __builtin_amdgcn_readlane(x[q], w);
+#pragma unroll
+            for (int k = 0; k < K; k++) rank[k] += y < x[k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < K; k++)
+        if (k * 64 + lane < m) members[rank[k]] = x[k];
+}
 
 // Each cluster of 2 .. kSmallCluster members: one wavefront, up to kSortRegs
 // members per lane; a member's place is the number of smaller ones (ids are
@@ -259,41 +281,52 @@ __global__ __launch_bounds__(kBlock) void k_sort_small(int64_t nc, const int64_t
         if (lane < m) members[s + rank] = x;
         return;
     }
-    int32_t x[kSortRegs];
-    int rank[kSortRegs];
-#pragma unroll
-    for (int k = 0; k < kSortRegs; k++) {
-        x[k] = k * 64 + lane < m ? members[s + k * 64 + lane] : 0x7fffffff;
-        rank[k] = 0;
-    }
-#pragma unroll
-    for (int q = 0; q < kSortRegs; q++) {
-        const int mq = (int)m - q * 64 < 64 ? (int)m - q * 64 : 64;
-        for (int w = 0; w < mq; w++) {
-            const int32_t y = __builtin_amdgcn_readlane(x[q], w);
-#pragma unroll
-            for (int k = 0; k < kSortRegs; k++) rank[k] += y < x[k];
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < kSortRegs; k++)
-        if (k * 64 + lane < m) members[s + rank[k]] = x[k];
+    if (m <= 128)
+        sort_regs<2>((int)m, members + s);
+    else
+        sort_regs<kSortRegs>((int)m, members + s);
 }
 
-// Each larger cluster: one workgroup sorts it in place with a bitonic
-// network on the next power of two, positions past the end reading as +inf.
-// The network's first step of every merge compares i with i ^ (k - 1) and
-// the later ones i with i ^ j, always the smaller value to the lower index,
-// so no real value ever moves past the end.  A workgroup reads the sizes of
-// kBlock clusters at once and sorts the few large ones among them (reading
-// them one after the other took 31 us on 14 000 clusters, 249 us on a million
-// without a large one).
+// Each larger cluster: one workgroup sorts it with a bitonic network on the
+// next power of two, positions past the end reading as +inf, in LDS up to
+// kSortLds members, else in place.  The network's first step of every merge
+// compares i with i ^ (k - 1) and the later ones i with i ^ j, always the
+// smaller value to the lower index, so no real value ever moves past the end.
+// A workgroup owns a run of clusters, reads kBlock of their sizes at once and
+// sorts the large ones among them (reading them one after the other took 31 us
+// on 14 000 clusters, 249 us on a million without a large one).
+constexpr int kSortLds = 4096;
+
+template <typename M>
+__device__ __forceinline__ void sort_network(M m, int64_t size) {
+    int64_t P = 1;
+    while (P < size) P <<= 1;
+    for (int64_t k = 2; k <= P; k <<= 1) {
+        for (int64_t j = k >> 1; j > 0; j >>= 1) {
+            for (int64_t i = threadIdx.x; i < P; i += kBlock) {
+                const int64_t p = (j == (k >> 1)) ? (i ^ (k - 1)) : (i ^ j);
+                if (p > i && p < size) {
+                    const int32_t x = m[i], y = m[p];
+                    if (x > y) {
+                        m[i] = y;
+                        m[p] = x;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void k_sort_large(int64_t nc, const int64_t *__restrict__ moff,
                                                        int32_t *__restrict__ members) {
     __shared__ uint64_t large[kBlock / 64];
-    for (int64_t a0 = (int64_t)blockIdx.x * kBlock; a0 < nc; a0 += (int64_t)gridDim.x * kBlock) {
+    __shared__ int32_t buf[kSortLds];
+    const int64_t run = (nc + gridDim.x - 1) / gridDim.x;
+    const int64_t last = min(nc, (blockIdx.x + 1) * run);
+    for (int64_t a0 = blockIdx.x * run; a0 < last; a0 += kBlock) {
         const int64_t own = a0 + threadIdx.x;
-        const uint64_t mine = __ballot(own < nc && moff[own + 1] - moff[own] > kSmallCluster);
+        const uint64_t mine = __ballot(own < last && moff[own + 1] - moff[own] > kSmallCluster);
         __syncthreads();
         if ((threadIdx.x & 63u) == 0) large[threadIdx.x >> 6] = mine;
         __syncthreads();
@@ -301,24 +334,15 @@ __global__ __launch_bounds__(kBlock) void k_sort_large(int64_t nc, const int64_t
             for (uint64_t mask = large[w]; mask; mask &= mask - 1) {
                 const int64_t a = a0 + w * 64 + __ffsll((unsigned long long)mask) - 1;
                 const int64_t s = moff[a], size = moff[a + 1] - s;
-                int64_t P = 1;
-                while (P < size) P <<= 1;
-                int32_t *m = members + s;
-                for (int64_t k = 2; k <= P; k <<= 1) {
-                    for (int64_t j = k >> 1; j > 0; j >>= 1) {
-                        for (int64_t i = threadIdx.x; i < P; i += kBlock) {
-                            const int64_t p = (j == (k >> 1)) ? (i ^ (k - 1)) : (i ^ j);
-                            if (p > i && p < size) {
-                                const int32_t x = m[i], y = m[p];
-                                if (x > y) {
-                                    m[i] = y;
-                                    m[p] = x;
-                                }
-                            }
-                        }
-                        __syncthreads();
-                    }
+                if (size > kSortLds) {
+                    sort_network(members + s, size);
+                    continue;
                 }
+                for (int64_t i = threadIdx.x; i < size; i += kBlock) buf[i] = members[s + i];
+                __syncthreads();
+                sort_network(&buf[0], size);
+                for (int64_t i = threadIdx.x; i < size; i += kBlock) members[s + i] = buf[i];
+                __syncthreads();
             }
         }
     }
@@ -746,18 +770,9 @@ hipError_t launch_sort_members(int64_t nc, const int64_t *moff, int32_t *members
     if (sblocks > 0x7fffffff) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_sort_small, dim3((unsigned)sblocks), dim3(kBlock), 0, s, nc, moff,
                        members);
-    hipLaunchKernelGGL(k_sort_large, dim3(grid_of(nc, 1024)), dim3(kBlock), 0, s, nc, moff,
-                       members);
+    hipLaunchKernelGGL(k_sort_large, dim3((unsigned)std::min<int64_t>(nc, 1024)), dim3(kBlock), 0,
+                       s, nc, moff, members);
     return hipGetLastError();
-}
-
-hipError_t launch_sorted_members(int64_t n, const int32_t *cluster, int64_t nc,
-                                 const int64_t *moff, uint32_t *cursor, int32_t *members,
-                                 hipStream_t s) {
-    if (n <= 0 || nc <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scatter_members, dim3(grid_of(n, 8192)), dim3(kBlock), 0, s, n, cluster,
-                       moff, cursor, members);
-    return launch_sort_members(nc, moff, members, s);
 }
 
 hipError_t launch_gather_sizes(int64_t nk, const int32_t *order, const uint32_t *cnt,

@@ -340,28 +340,46 @@ hipError_t launch_rounds(int lanes, int blocks, const int64_t *row_ptr, const in
                          uint32_t *T, uint32_t *M, const RoundsArgs &a, hipStream_t s);
 // e0 / e1 (may be null): events stamped by the launch itself at the kernel's
 // start and end.
+constexpr uint32_t kSymBad = 1, kSymMid = 2, kSymLarge = 4;
 // smoothed.hip: smoothed aggregation.  kind 0: P rows (sources N[i], one
 // aggregate each), 1: AP rows (P rows of N[i]), 2: coarse rows (AP rows of
 // the rows holding P[i][a]); count pass (fill == false) writes count[r] and
-// sets *err |= 1 for a row of more than 2048 distinct columns; fill pass
-// writes the ascending columns at out_ptr[r].
-hipError_t launch_smoothed_sym(int kind, bool fill, int64_t rows, const int64_t *row_ptr,
+// sets flags in *err: kSymMid when a row was left to the second of three
+// passes, kSymLarge when one is left to the third (count[r] = 0 so far: the
+// caller launches again with later = true), kSymBad for a row of more than 2048
+// distinct columns; fill pass
+// (kind 0; the others have fills of their own below) writes the ascending
+// columns at out_ptr[r].  nnz: entries of the graph.
+// spare (kind 0, count pass; may be null): n + nnz entries that receive row r
+// at row_ptr[r] + r, from where launch_p_copy takes it in place of a fill pass.
+hipError_t launch_smoothed_sym(int kind, bool fill, int64_t rows, int64_t nnz, const int64_t *row_ptr,
                                const int32_t *col, const int32_t *agg, const int64_t *sptr,
                                const int32_t *scol, const int64_t *moff, const int32_t *members,
                                const int32_t *prow_of, uint32_t *count, const int64_t *out_ptr,
-                               int32_t *out_col, uint32_t *err, uint8_t *cls, hipStream_t s);
+                               int32_t *out_col, uint32_t *err, uint8_t *cls, int32_t *spare,
+                               bool later, hipStream_t s);
+hipError_t launch_p_copy(int64_t n, const int64_t *row_ptr, const int32_t *spare,
+                         const int64_t *prow, int32_t *pcol, hipStream_t s);
 hipError_t launch_p_values(int64_t n, int64_t p_nnz, const int64_t *row_ptr, const int32_t *col,
                            const double *val, const double *diag, const int32_t *agg,
                            const uint32_t *size, double omega, const int64_t *prow,
                            const int32_t *pcol, double *pval, int32_t *prow_of, hipStream_t s);
-hipError_t launch_ap_values(int64_t n, int64_t ap_nnz, const int64_t *row_ptr, const int32_t *col,
-                            const double *val, const double *diag, const int64_t *prow,
-                            const int32_t *pcol, const double *pval, const int64_t *aptr,
-                            const int32_t *acol, double *aval, hipStream_t s);
-hipError_t launch_c_values(int64_t n_agg, int64_t c_nnz, const int64_t *moff,
-                           const int32_t *members, const int32_t *prow_of, const double *pval,
-                           const int64_t *aptr, const int32_t *acol, const double *aval,
-                           const int64_t *crow, const int32_t *ccol, double *cval, hipStream_t s);
+// The columns and values of AP (kind 1) and of Ac (kind 2), once counted with
+// these flags.
+hipError_t launch_ap_fill(int64_t n, const int64_t *row_ptr, const int32_t *col, const double *val,
+                          const double *diag, const int64_t *prow, const int32_t *pcol,
+                          const double *pval, const int64_t *aptr, int32_t *acol, double *aval,
+                          uint8_t *cls, uint32_t flags, hipStream_t s);
+hipError_t launch_c_fill(int64_t n_agg, const int64_t *moff, const int32_t *members,
+                         const int32_t *prow_of, const double *pval, const int64_t *aptr,
+                         const int32_t *acol, const double *aval, const int64_t *crow,
+                         int32_t *ccol, double *cval, uint8_t *cls, uint32_t flags, hipStream_t s);
+// cnt[c] = entries of P in column c, rank[p] = entry p's place among them (in
+// no particular order); then members[moff[c] + rank[p]] = p.
+hipError_t launch_column_rank(int64_t p_nnz, const int32_t *pcol, int64_t n_agg, uint32_t *cnt,
+                              int32_t *rank, hipStream_t s);
+hipError_t launch_column_scatter(int64_t p_nnz, const int32_t *pcol, const int64_t *moff,
+                                 const int32_t *rank, int32_t *members, hipStream_t s);
 // cgs.hip: Algorithm 4 (cluster multicolor Gauss-Seidel).
 // st: [n] states (tuple, colour).  A pass colours what it can; list and cnt
 // ([n] each, but cnt at least 32) carry the uncoloured vertices from launch to
@@ -388,11 +406,6 @@ hipError_t launch_color_hist(int64_t n, const int32_t *color, int32_t n_colors, 
                              hipStream_t s);
 // The members of each cluster in increasing id, in place.
 hipError_t launch_sort_members(int64_t nc, const int64_t *moff, int32_t *members, hipStream_t s);
-// members[moff[a] .. moff[a+1]) = the rows of cluster a in increasing id
-// (cursor zero on entry).
-hipError_t launch_sorted_members(int64_t n, const int32_t *cluster, int64_t nc,
-                                 const int64_t *moff, uint32_t *cursor, int32_t *members,
-                                 hipStream_t s);
 hipError_t launch_gather_sizes(int64_t nk, const int32_t *order, const uint32_t *cnt,
                                uint32_t *out, hipStream_t s);
 hipError_t launch_place_rows(int64_t nk, const int32_t *order, const int64_t *moff,
