@@ -2249,7 +2249,8 @@ int mis2_cgs_apply(mis2_ctx *ctx, const mis2_graph *g, const double *val, const 
         return point ? launch_cgs_point(g->row_ptr, g->col, val, diag, b, x, plan->rows, co[c],
                                         co[c + 1], s)
                      : launch_cgs_sweep(g->row_ptr, g->col, val, diag, b, x, plan->rows, plan->pos,
-                                        plan->cluster_off, co[c], co[c + 1], backward, s);
+                                        plan->cluster_off, co[c], co[c + 1],
+                                        g->nnz / std::max<int64_t>(plan->n_clusters, 1), backward, s);
     };
     for (int32_t t = 0; t < sweeps; t++) {
         for (int32_t c = 0; c < plan->n_colors; c++) HIP_TRY(ctx, pass(c, false));

@@ -18,6 +18,7 @@
 // subset of the ready ones a pass happens to colour.
 #include "internal.h"
 #include "lanes.h"
+#include "rowset.h"
 
 namespace mis2 {
 
@@ -385,46 +386,54 @@ __global__ __launch_bounds__(kBlock) void k_scatter_pos(int64_t n, const int32_t
 
 // ---- apply ----------------------------------------------------------------
 //
-// One wavefront per cluster.  The cluster's rows are taken in batches of at
-// most 64 rows of at most 64 entries each and Cap entries in all; lane k
-// holds the batch's k-th row.  The batch is staged in LDS in parallel: for
-// each entry (row order, then CSR order) either the product a_ij * x_j with
-// index kOne (x_j is final for this pass when j is not a row of the batch:
-// another colour's x, a row of this cluster updated in an earlier batch, or
-// one not yet reached, whose old value Gauss-Seidel uses), or a_ij with the
-// batch index of j.  xb holds the batch's x, current as rows finish, and
-// xb[kOne] = 1 (an exact product).  The chain then runs the rows in order:
-// lane q forms the row's q-th term v * xb[index], and the terms are
-// subtracted from b_i one by one in CSR order, read across lanes; a row of
-// at most 8, 16, 32 (else 64) entries subtracts that many terms, the
-// missing ones +0.0, which leaves every value unchanged, so every rounding
-// is the sequential sweep's.  A row's LDS reads are issued while the row before it
-// runs (its indices and values two rows ahead); the one x they cannot see,
-// the previous row's, is taken from the chain directly.  A row longer than
-// 64 entries is a batch of its own, read from global memory in pieces of 64
-// (no row of its batch but itself, and it has no self-loop).
+// C clusters per workgroup, SL = 16, 64 or 256 lanes each to stage them and one
+// wavefront to run them.  A cluster's rows are taken in batches of at most
+// R = min(SL, 64) rows; staging lane k holds the batch's k-th row.  The batch is
+// staged in LDS in parallel, every row in L slots (L: the longest row of the
+// workgroup's batches; Cap slots in all): for each entry, in CSR order, either
+// the product a_ij * x_j with index R (x_j is final for this pass when j is not a
+// row of the batch: another colour's x, a row of this cluster updated in an
+// earlier batch, or one not yet reached, whose old value Gauss-Seidel uses), or
+// a_ij with the batch index of j; +0.0 with index R past the row's end.  xb holds
+// the batch's x, current as rows finish, and xb[R] = 1 (an exact product).  One
+// wavefront then runs the batches' chains side by side, a DPP row of 16 lanes for
+// each: lane q forms a row's q-th term v * xb[index] (of 16 at a time), and the
+// terms are subtracted from b_i one by one in CSR order, each read by all 16
+// lanes of the row; the missing ones, +0.0, leave every value unchanged, so every
+// rounding is the sequential sweep's.  A row's LDS reads are issued while the row
+// before it runs (its indices and values two rows ahead); the one x they cannot
+// see, the previous row's, is taken from the chain directly.  A row longer than
+// Cap entries is a batch of its own, read from global memory by its cluster's
+// lanes (no row of its batch but itself, and it has no self-loop).
+//
+// Bound by latency: a colour's launch lasts as long as its largest cluster, and
+// that is five dependent loads a batch, then about 7.5 cycles a term and 104 a
+// division.  One wavefront per cluster for both parts, a batch of 256 entries and
+// the term read across the wavefront by two moves took 57 us a colour on the
+// 27-point 100^3 grid (13 colours of 3400 clusters, 23 rows of 26 entries; this:
+// 37, of which 11 are the chains).  Symmetric sweeps, before and now: 27-point
+// 100^3 1467 and 866 us, 40^3 946 and 442; 7-point 100^3 535 and 319; 2-D 5-point
+// 700 x 800 295 and 155; elasticity (80 entries a row, before past the staged
+// length) 40^3 6482 and 2193.
 constexpr int kCgsWaves = kBlock / 64;
-constexpr int kOne = 64;
-// 256 entries per batch and 8 waves per SIMD (the most a SIMD holds): on the
-// 27-point and 7-point 100^3 plans, 384, 512, 768 and 1024 entries at the
-// occupancy their LDS allows (7, 6, 4, 3 waves) all sweep slower
-constexpr int kCgsLaunchCap = 256;
-constexpr int kCgsLaunchWaves = 8;
 
-template <int Cap>
+// R: rows of a batch
+template <int R, int Cap>
 struct CgsStage {
-    double v[Cap + 64];  // 64 spare entries: reads past a batch's end stay inside
-    uint8_t tag[Cap + 64];
-    double xb[65];
-    int64_t rs[64];
-    int32_t off[65];
+    double v[Cap + 16];  // 16 spare slots: reads past a batch's end stay inside
+    double xb[R + 1];
+    union {
+        struct {  // of the rows, for the staging
+            int64_t rs[R];
+            int32_t len[R];
+        };
+        struct {  // for the chains
+            double b[R], d[R];
+        };
+    };
+    int32_t nb, longest, more;
+    uint8_t tag[Cap + 16];
 };
-
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 __device__ __forceinline__ double lane_bcast(double v, int l) {
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
@@ -438,168 +447,301 @@ __device__ __forceinline__ int64_t lane_bcast64(int64_t v, int l) {
     return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-// acc minus the terms of lanes 0 .. W-1, in lane order; the lanes' values
-// are read eight at a time ahead of their eight subtractions
+// acc minus the terms of the first W lanes of its DPP row, in lane order, one
+// rounding each: acc + (-t) * 1.0.  The instructions name the lane they read; a
+// wait covers a term written just before, another a lane read just after.
 template <int W>
-__device__ __forceinline__ double chain_w(double acc, double term) {
-#pragma clang fp contract(off)
-#pragma unroll
-    for (int g = 0; g < W; g += 8) {
-        double t[8];
-#pragma unroll
-        for (int z = 0; z < 8; z++) t[z] = lane_bcast(term, g + z);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int z = 0; z < 8; z++) acc = acc - t[z];
-        __builtin_amdgcn_sched_barrier(0);
+__device__ __forceinline__ double chain(double acc, double term) {
+    static_assert(W == 8 || W == 12 || W == 16, "chain: 8, 12 or 16 lanes");
+#define MIS2_SUB(k) "v_fmac_f64_dpp %0, -%1, %2 row_newbcast:" #k " row_mask:0xf bank_mask:0xf\n"
+#define MIS2_SUB8                                                                         \
+    "s_nop 1\n" MIS2_SUB(0) MIS2_SUB(1) MIS2_SUB(2) MIS2_SUB(3) MIS2_SUB(4) MIS2_SUB(5) \
+        MIS2_SUB(6) MIS2_SUB(7)
+#define MIS2_SUB12 MIS2_SUB8 MIS2_SUB(8) MIS2_SUB(9) MIS2_SUB(10) MIS2_SUB(11)
+#define MIS2_SUB16 MIS2_SUB12 MIS2_SUB(12) MIS2_SUB(13) MIS2_SUB(14) MIS2_SUB(15)
+    if constexpr (W == 8) {
+        asm volatile(MIS2_SUB8 "s_nop 1" : "+v"(acc) : "v"(term), "v"(1.0));
+    } else if constexpr (W == 12) {
+        asm volatile(MIS2_SUB12 "s_nop 1" : "+v"(acc) : "v"(term), "v"(1.0));
+    } else {
+        asm volatile(MIS2_SUB16 "s_nop 1" : "+v"(acc) : "v"(term), "v"(1.0));
     }
+#undef MIS2_SUB
+#undef MIS2_SUB8
+#undef MIS2_SUB12
+#undef MIS2_SUB16
     return acc;
 }
 
-// Cap: LDS entries per batch; MinW: waves per SIMD that the LDS of a wave
-// (about 9 bytes per entry) still allows
-template <int Cap, int MinW>
-__global__ __launch_bounds__(kBlock, MinW) void k_cgs_cluster(const int64_t *__restrict__ row_ptr,
-                                                        const int32_t *__restrict__ col,
-                                                        const double *__restrict__ val,
-                                                        const double *__restrict__ diag,
-                                                        const double *__restrict__ b, double *x,
-                                                        const int32_t *__restrict__ rows,
-                                                        const int32_t *__restrict__ pos,
-                                                        const int64_t *__restrict__ cluster_off,
-                                                        int64_t k0, int64_t k1, int backward) {
+// The largest value among the group's lanes up to this one (x >= 0).
+template <int G>
+__device__ __forceinline__ int group_incl_max(int x) {
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true));
+    if constexpr (G == 64) {
+        x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false));
+        x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false));
+    }
+    return x;
+}
+
+// The chains of the four staged batches (the whole wavefront): NB rows, each of K
+// times 16 terms, the last W of them in the last step (16 (K - 1) < L <= 16 (K - 1) + W, or K = 1).
+template <int C, int K, int W, int R, int Cap>
+__device__ __forceinline__ void run_chains(CgsStage<R, Cap> *stage, int NB, int L) {
 #pragma clang fp contract(off)
-    constexpr int kCgsCap = Cap, kCgsU = Cap / 64;
-    __shared__ CgsStage<Cap> stage[kCgsWaves];
-    const int lane = threadIdx.x & 63;
-    CgsStage<Cap> &S = stage[threadIdx.x >> 6];
-    const int64_t k = k0 + (int64_t)blockIdx.x * kCgsWaves + (threadIdx.x >> 6);
-    if (k >= k1) return;
-    const int64_t r0 = cluster_off[k], r1 = cluster_off[k + 1], m = r1 - r0;
-    if (lane == 0) S.xb[kOne] = 1.0;
-    S.v[kCgsCap + lane] = 0.0;
-    S.tag[kCgsCap + lane] = kOne;
-    for (int64_t u = 0; u < m;) {
-        // the next (up to) 64 rows in visiting order, one per lane
-        const int64_t cand = u + lane;
-        const bool valid = cand < m;
-        const int64_t t = backward ? r1 - 1 - cand : r0 + cand;
-        const int32_t i = valid ? rows[t] : 0;
-        const int64_t rs = valid ? row_ptr[i] : 0;
-        const int64_t len = valid ? row_ptr[i + 1] - rs : 0;
-        const double bi = valid ? b[i] : 0.0;
-        const double di = valid ? diag[i] : 1.0;
-        const double xo = valid ? x[i] : 0.0;
-        // prefix of the lengths, each clamped to kCgsCap + 1: only prefixes up
-        // to kCgsCap are used, and those are exact
-        const int64_t incl =
-            (int64_t)wave_incl_scan((uint32_t)(len < kCgsCap + 1 ? len : kCgsCap + 1));
-        // rows before the first one longer than 64, within Cap entries
-        const uint64_t longm = __ballot(valid && len > 64);
-        const int first_long = longm ? __ffsll((unsigned long long)longm) - 1 : 64;
-        int nb = __popcll(__ballot(valid && incl <= kCgsCap));
-        nb = nb < first_long ? nb : first_long;
-        if (nb == 0) {
-            // lane 0's row alone, longer than 64 entries
-            const int32_t i0 = __builtin_amdgcn_readfirstlane(i);
-            const int64_t s0 = lane_bcast64(rs, 0), l0 = lane_bcast64(len, 0);
-            double acc = lane_bcast(bi, 0);
-            for (int64_t pc = 0; pc < l0; pc += 64) {
-                const int64_t q = pc + lane;
-                double term = 0.0;
-                if (q < l0) {
-                    const int64_t pe = s0 + q;
-                    term = val[pe] * x[col[pe]];
-                }
-                acc = chain_w<64>(acc, term);
-            }
-            const double xn = acc / lane_bcast(di, 0);
-            if (lane == 0) x[i0] = xn;
-            wave_sync();
-            u += 1;
-            continue;
+    const int lane = (int)(threadIdx.x & 63u), q = lane & 15;
+    CgsStage<R, Cap> &S = stage[(lane >> 4) & (C - 1)];
+    const int nbg = S.nb;
+    const bool in = 16 * (K - 1) + q < L;  // the last step's lanes inside a row
+    double v[K], w[K], x[K];
+    int t[K], u[K];
+    auto read = [&](int r, double (&rv)[K], int (&rt)[K]) {
+        const int e = min(r, NB - 1) * L + q;
+#pragma unroll
+        for (int c = 0; c < K; c++) {
+            rv[c] = S.v[e + 16 * c];
+            rt[c] = (int)S.tag[e + 16 * c];
         }
-        const int tot = (int)lane_bcast64(incl, nb - 1);
+        rv[K - 1] = in ? rv[K - 1] : 0.0;
+        rt[K - 1] = in ? rt[K - 1] : R;
+    };
+    read(0, v, t);
+    read(1, w, u);
+#pragma unroll
+    for (int c = 0; c < K; c++) x[c] = S.xb[t[c]];
+    double bk = S.b[0], dk = S.d[0];
+    double xs = 0.0;  // x of the previous row
+    for (int kk = 0; kk < NB; kk++) {
+        double term[K];
+#pragma unroll
+        for (int c = 0; c < K; c++)  // xb[kk - 1] was not yet written when x was read
+            term[c] = v[c] * (t[c] == kk - 1 ? xs : x[c]);
+        double acc = bk;
+        // reads for rows kk + 1 (x, b, d) and kk + 2 (values, indices)
+        const double dn = S.d[min(kk + 1, NB - 1)];
+        bk = S.b[min(kk + 1, NB - 1)];
+#pragma unroll
+        for (int c = 0; c < K; c++) {
+            x[c] = S.xb[u[c]];
+            v[c] = w[c];
+            t[c] = u[c];
+        }
+        read(kk + 2, w, u);
+#pragma unroll
+        for (int c = 0; c + 1 < K; c++) acc = chain<16>(acc, term[c]);
+        acc = chain<W>(acc, term[K - 1]);
+        xs = acc / dk;
+        if (q == 0 && lane < 16 * C && kk < nbg) S.xb[kk] = xs;
+        dk = dn;
+    }
+}
+
+// The same for longer rows, 16 terms at a time.
+template <int C, int R, int Cap>
+__device__ __forceinline__ void run_long_chains(CgsStage<R, Cap> *stage, int NB, int L) {
+#pragma clang fp contract(off)
+    const int lane = (int)(threadIdx.x & 63u), q = lane & 15;
+    CgsStage<R, Cap> &S = stage[(lane >> 4) & (C - 1)];
+    const int nbg = S.nb;
+    for (int kk = 0; kk < NB; kk++) {
+        double acc = S.b[kk];
+        const double dk = S.d[kk];
+        for (int c = 0; c < L; c += 16) {
+            const int e = kk * L + c + q;
+            const bool in = c + q < L;
+            const double p = S.v[e] * S.xb[in ? (int)S.tag[e] : R];
+            acc = chain<16>(acc, in ? p : 0.0);
+        }
+        const double xs = acc / dk;
+        if (q == 0 && lane < 16 * C && kk < nbg) S.xb[kk] = xs;
+    }
+}
+
+// The T = NB L slots of a batch's rows 0 .. NB - 1 (those past the group's own
+// batch are empty), U of a lane's at once: all of their loads go out together.
+template <int SL, int U, int R, int Cap>
+__device__ __forceinline__ void stage_entries(CgsStage<R, Cap> &S, int lane, int T, int L,
+                                              int64_t lo, int nb, int backward,
+                                              const int32_t *__restrict__ col,
+                                              const double *__restrict__ val, const double *x,
+                                              const int32_t *__restrict__ pos) {
+#pragma clang fp contract(off)
+    const float per = 1.0f / (float)L;
+    for (int q0 = lane; q0 - lane < T; q0 += SL * U) {
+        int64_t pp[U];
+        bool ok[U];
+#pragma unroll
+        for (int j = 0; j < U; j++) {
+            const int q = min(q0 + SL * j, T - 1);
+            // q / L: the product is off by less than 2^-21 of itself, and an
+            // integer is at least 0.5 / (q + 0.5) of it away
+            const int r = (int)(((float)q + 0.5f) * per), e = q - r * L;
+            ok[j] = e < S.len[r];
+            pp[j] = ok[j] ? S.rs[r] + e : 0;
+        }
+        int32_t jj[U];
+        double aa[U];
+#pragma unroll
+        for (int j = 0; j < U; j++) {
+            jj[j] = col[pp[j]];
+            aa[j] = val[pp[j]];
+        }
+        int32_t pj[U];
+        double xj[U];
+#pragma unroll
+        for (int j = 0; j < U; j++) {
+            pj[j] = pos[jj[j]];
+            xj[j] = x[jj[j]];
+        }
+#pragma unroll
+        for (int j = 0; j < U; j++) {
+            const int q = q0 + SL * j, at = (int)(pj[j] - lo);
+            const bool inb = pj[j] >= lo && pj[j] < lo + nb;
+            const int to = q < T ? q : Cap + 15;  // a spare slot
+            const double p = aa[j] * (inb ? 1.0 : xj[j]);
+            S.tag[to] = (uint8_t)(!inb || !ok[j] ? R : backward ? nb - 1 - at : at);
+            S.v[to] = ok[j] ? p : 0.0;
+        }
+    }
+}
+
+template <int C, int SL, int Cap, int U, int MinW>
+__global__ __launch_bounds__(C *SL, MinW) void k_cgs_cluster(
+    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+    const double *__restrict__ val, const double *__restrict__ diag, const double *__restrict__ b,
+    double *x, const int32_t *__restrict__ rows, const int32_t *__restrict__ pos,
+    const int64_t *__restrict__ cluster_off, int64_t k0, int64_t k1, int backward) {
+#pragma clang fp contract(off)
+    static_assert(SL == 16 || SL == 64 || SL == 256, "a DPP row or wavefronts stage a cluster");
+    constexpr int R = SL < 64 ? SL : 64;
+    __shared__ CgsStage<R, Cap> stage[C];
+    // the wavefronts of a group each work out its rows, and store the same
+    const int lane = (int)threadIdx.x % R, grp = (int)threadIdx.x / SL;
+    CgsStage<R, Cap> &S = stage[grp];
+    // each XCD takes one run of the clusters (the grid is a multiple of 8)
+    const int64_t blk = (int64_t)(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const int64_t k = k0 + blk * C + grp;
+    const int64_t r0 = k < k1 ? cluster_off[k] : 0;
+    const int64_t r1 = k < k1 ? cluster_off[k + 1] : 0, m = r1 - r0;
+    if (lane == 0) S.xb[R] = 1.0;
+    // the rows from position u on in visiting order, one per lane (no branch
+    // around a load, here and below: row 0 stands in)
+    int32_t i = 0;
+    int64_t rs = 0, re = 0;
+    double bi = 0.0, di = 1.0, xo = 0.0;
+    auto fetch = [&](int64_t u) {
+        const int64_t cand = u + lane;
+        i = rows[cand >= m ? 0 : backward ? r1 - 1 - cand : r0 + cand];
+        rs = row_ptr[i];
+        re = row_ptr[i + 1];
+        bi = b[i];
+        di = diag[i];
+        xo = x[i];
+    };
+    fetch(0);
+    for (int64_t u = 0;;) {
+        const bool valid = u + lane < m;
+        // the longest row so far, clamped past Cap; the rows that fit Cap slots
+        const int len = valid ? (int)min<int64_t>(re - rs, Cap + 1) : 0;
+        const int upto = group_incl_max<R>(len);
+        uint64_t fit = __ballot(valid && upto * (lane + 1) <= Cap);
+        if (SL == 16) fit = fit >> (grp * 16) & 0xFFFFull;
+        const int mine = __popcll(fit);
+        if (lane == 0) S.nb = 0;
+        if (lane == 0) S.longest = 0;
+        wave_sync();
+        if (lane == mine - 1) {
+            S.nb = mine;
+            S.longest = upto;
+        }
+        __syncthreads();
+        int L = 0;
+#pragma unroll
+        for (int g = 0; g < C; g++) L = max(L, stage[g].longest);
+        const int room = L > 0 ? Cap / L : R;
+        int NB = 0;
+#pragma unroll
+        for (int g = 0; g < C; g++) NB = max(NB, min(stage[g].nb, room));
+        L = __builtin_amdgcn_readfirstlane(L);
+        NB = __builtin_amdgcn_readfirstlane(NB);
+        const int nb = min(mine, room);
+        const int64_t next = u + max(nb, 1);
+        __syncthreads();
+        if (lane == 0) {
+            S.nb = nb;
+            S.more = next < m;
+        }
+        S.rs[lane] = rs;
+        S.len[lane] = lane < nb ? len : 0;
+        S.xb[lane] = xo;
+        wave_sync();
         // sweep positions of the batch: [lo, lo + nb)
         const int64_t lo = backward ? r1 - u - nb : r0 + u;
-        if (lane < nb) {
-            S.off[lane + 1] = (int32_t)incl;
-            S.rs[lane] = rs;
-            S.xb[lane] = xo;
-        }
-        if (lane == 0) S.off[0] = 0;
-        wave_sync();
-        // stage the batch's entries, all of a lane's loads in flight at once
-        // (slots past tot re-read entry 0 and store nothing).  A batch with no
-        // entries (rows without off-diagonal entries) loads nothing: its rows'
-        // CSR starts may equal nnz, one past the last entry
-        if (tot > 0) {
-            int64_t pp[kCgsU];
+        // (rows without off-diagonal entries stage nothing: there may be no entry
+        // in all of the matrix)
+        const int sl = (int)threadIdx.x % SL;
+        if (NB * L <= SL * (U / 2) && L > 0)
+            stage_entries<SL, U / 2>(S, sl, NB * L, L, lo, nb, backward, col, val, x, pos);
+        else if (L > 0)
+            stage_entries<SL, U>(S, sl, NB * L, L, lo, nb, backward, col, val, x, pos);
+        if (mine == 0 && u < m && sl < 64) {
+            // lane 0's row alone, longer than Cap entries
+            const int first = SL == 16 ? (int)(threadIdx.x & 48u) : 0;
+            const int32_t i0 = __shfl(i, first, 64);
+            const int64_t s0 = __shfl(rs, first, 64), l0 = __shfl(re, first, 64) - s0;
+            double acc = __shfl(bi, first, 64);
+            const double d0 = __shfl(di, first, 64);
+            for (int64_t pc = 0; pc < l0; pc += R * 4) {
+                double term[4];
 #pragma unroll
-            for (int c = 0; c < kCgsU; c++) {
-                const int q = lane + 64 * c < tot ? lane + 64 * c : 0;
-                int kr = 0;
-                for (int st = 32; st > 0; st >>= 1)
-                    if (kr + st < nb && S.off[kr + st] <= q) kr += st;
-                pp[c] = S.rs[kr] + (q - S.off[kr]);
-            }
-            int32_t jj[kCgsU];
-            double aa[kCgsU];
+                for (int c = 0; c < 4; c++) {
+                    const int64_t q = pc + R * c + lane, pe = s0 + (q < l0 ? q : 0);
+                    const double p = val[pe] * x[col[pe]];
+                    term[c] = q < l0 ? p : 0.0;
+                }
 #pragma unroll
-            for (int c = 0; c < kCgsU; c++) {
-                jj[c] = col[pp[c]];
-                aa[c] = val[pp[c]];
-            }
-#pragma unroll
-            for (int c = 0; c < kCgsU; c++) {
-                const int q = lane + 64 * c;
-                const int64_t pj = pos[jj[c]];
-                const double xj = x[jj[c]];
-                const bool inb = pj >= lo && pj < lo + nb;
-                if (q < tot) {
-                    S.tag[q] = inb ? (uint8_t)(backward ? lo + nb - 1 - pj : pj - lo) : kOne;
-                    S.v[q] = inb ? aa[c] : aa[c] * xj;
+                for (int c = 0; c < 4; c++) {
+                    acc = chain<16>(acc, term[c]);
+                    if (R == 64) {  // on through the other rows' 16 lanes
+                        acc = chain<16>(lane_bcast(acc, 0), term[c]);
+                        acc = chain<16>(lane_bcast(acc, 16), term[c]);
+                        acc = chain<16>(lane_bcast(acc, 32), term[c]);
+                        acc = lane_bcast(acc, 48);
+                    }
                 }
             }
+            const double xn = acc / d0;
+            if (lane == 0) x[i0] = xn;
         }
+        if (SL > 64) __syncthreads();
         wave_sync();
-        // the chain.  Row r's entries are [incl(r) - len(r), incl(r)); lane q
-        // reads entry q of a row (past its end: a spare zero entry, or the
-        // next row's, both masked out of the term)
-        auto start = [&](int r) { return r == 0 ? 0 : (int)lane_bcast64(incl, r - 1); };
-        const int s1 = start(1 < nb ? 1 : nb - 1);
-        // (an index read past a row's end may be stale: clamp it into xb)
-        double v0 = S.v[lane], v1 = S.v[s1 + lane];
-        int g0 = min((int)S.tag[lane], kOne), g1 = min((int)S.tag[s1 + lane], kOne);
-        double x0 = S.xb[g0];
-        double xs = 0.0;  // x of the previous row
-        for (int kk = 0; kk < nb; kk++) {
-            const int ln = (int)lane_bcast64(incl, kk) - start(kk);
-            // row kk's term; xb[kk - 1] was not yet written when x0 was read
-            const double xf = g0 == kk - 1 ? xs : x0;
-            const double term = lane < ln ? v0 * xf : 0.0;
-            // reads for rows kk + 1 (x) and kk + 2 (values, indices)
-            const double x1 = S.xb[g1];
-            const int s2 = start(kk + 2 < nb ? kk + 2 : nb - 1);
-            const double v2 = S.v[s2 + lane];
-            const int g2 = min((int)S.tag[s2 + lane], kOne);
-            double acc = lane_bcast(bi, kk);
-            acc = ln <= 8    ? chain_w<8>(acc, term)
-                  : ln <= 16 ? chain_w<16>(acc, term)
-                  : ln <= 32 ? chain_w<32>(acc, term)
-                             : chain_w<64>(acc, term);
-            const double xn = acc / lane_bcast(di, kk);
-            if (lane == 0) S.xb[kk] = xn;
-            if (lane == kk) x[i] = xn;
-            xs = xn;
-            v0 = v1;
-            g0 = g1;
-            x0 = x1;
-            v1 = v2;
-            g1 = g2;
+        S.b[lane] = bi;
+        S.d[lane] = lane < nb ? di : 1.0;
+        const int32_t done = i;
+        __syncthreads();
+        int more = 0;
+#pragma unroll
+        for (int g = 0; g < C; g++) more |= stage[g].more;
+        // the next batch's rows while the chains run (no x of theirs changes)
+        if (more) fetch(next);
+        if (threadIdx.x < 64u && NB > 0) {
+            if (L <= 8) run_chains<C, 1, 8>(stage, NB, L);
+            else if (L <= 16) run_chains<C, 1, 16>(stage, NB, L);
+            else if (L <= 28) run_chains<C, 2, 12>(stage, NB, L);
+            else if (L <= 32) run_chains<C, 2, 16>(stage, NB, L);
+            else if (L <= 48) run_chains<C, 3, 16>(stage, NB, L);
+            else if (L <= 64) run_chains<C, 4, 16>(stage, NB, L);
+            else if (L <= 80) run_chains<C, 5, 16>(stage, NB, L);
+            else run_long_chains<C>(stage, NB, L);
         }
-        wave_sync();
-        u += nb;
+        __syncthreads();
+        if (lane < nb && sl < 64) x[done] = S.xb[lane];
+        if (!more) break;
+        if (SL > 64) __syncthreads();  // before the other wavefronts read it
+        u = next;
     }
 }
 
@@ -801,14 +943,27 @@ hipError_t launch_scatter_pos(int64_t n, const int32_t *rows, int32_t *pos, hipS
 hipError_t launch_cgs_sweep(const int64_t *row_ptr, const int32_t *col, const double *val,
                             const double *diag, const double *b, double *x, const int32_t *rows,
                             const int32_t *pos, const int64_t *cluster_off, int64_t k0, int64_t k1,
-                            bool backward, hipStream_t s) {
+                            int64_t per, bool backward, hipStream_t s) {
     if (k1 <= k0) return hipSuccess;
-    const int64_t blocks = (k1 - k0 + kCgsWaves - 1) / kCgsWaves;
+    const int64_t blocks = ((k1 - k0 + 3) / 4 + 7) / 8 * 8;  // 4 clusters each
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_cgs_cluster<kCgsLaunchCap, kCgsLaunchWaves>), dim3((unsigned)blocks),
-                       dim3(kBlock), 0, s, row_ptr, col, val, diag, b, x, rows, pos, cluster_off,
-                       k0, k1, backward ? 1 : 0);
-    return hipGetLastError();
+    auto go = [&](auto kernel, int lanes) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(4 * lanes), 0, s, row_ptr, col, val,
+                           diag, b, x, rows, pos, cluster_off, k0, k1, backward ? 1 : 0);
+        return hipGetLastError();
+    };
+    // Lanes to stage a cluster by its entries (per, on average): a 7-point
+    // cluster has 40, so 16 lanes load it in three or four steps and one wavefront
+    // takes four clusters.  A 27-point one has 560: a wavefront each, and slots
+    // for 35 of its rows, the most that keep four workgroups on a compute unit
+    // (768 slots: 40 us a colour, 1152: 40, with two clusters a workgroup 37, one
+    // 40).  Where the workgroups are no more than the compute units, or a cluster
+    // has thousands of entries, four wavefronts load each: 27-point 40^3 442 us
+    // against 497 with one wavefront, elasticity 60^3 2856 against 3233; up to 2048
+    // clusters instead of 1024 the 27-point 60^3 grid slows from 497 to 558.
+    if (per <= 128) return go(k_cgs_cluster<4, 16, 128, 8, 4>, 16);
+    if (per <= 1024 && k1 - k0 > 1024) return go(k_cgs_cluster<4, 64, 928, 8, 4>, 64);
+    return go(k_cgs_cluster<4, 256, 2048, 8, 4>, 256);
 }
 
 hipError_t launch_cgs_point(const int64_t *row_ptr, const int32_t *col, const double *val,

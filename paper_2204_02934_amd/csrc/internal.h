@@ -424,7 +424,7 @@ hipError_t launch_galerkin(const int64_t *row_ptr, const int32_t *col, const dou
 hipError_t launch_cgs_sweep(const int64_t *row_ptr, const int32_t *col, const double *val,
                             const double *diag, const double *b, double *x, const int32_t *rows,
                             const int32_t *pos, const int64_t *cluster_off, int64_t k0, int64_t k1,
-                            bool backward, hipStream_t s);
+                            int64_t per, bool backward, hipStream_t s);
 hipError_t launch_cgs_point(const int64_t *row_ptr, const int32_t *col, const double *val,
                             const double *diag, const double *b, double *x, const int32_t *rows,
                             int64_t t0, int64_t t1, hipStream_t s);
