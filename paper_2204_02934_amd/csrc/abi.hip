@@ -1613,6 +1613,14 @@ int aggregate_impl(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int32_t *a
     return collect_sweeps(ctx, launches, ws, s);
 }
 
+// Pinned words that kernels wrote, after a synchronisation.
+int64_t pinned_i64(const mis2_ctx *ctx, int word) {
+    return (int64_t)__atomic_load_n((const unsigned long long *)ctx->pinned + word, __ATOMIC_ACQUIRE);
+}
+uint32_t pinned_u32(const mis2_ctx *ctx, int word) {
+    return __atomic_load_n(ctx->pinned + word, __ATOMIC_ACQUIRE);
+}
+
 // The quotient's arrays of a coarsening workspace.  Everything before them
 // (tuples, worklists, labels: 38 bytes per vertex) holds nothing that is
 // needed once the aggregation has returned, and is the quotient's spare buffer
@@ -1646,13 +1654,10 @@ int quotient_impl(mis2_ctx *ctx, const mis2_graph *g, const int32_t *agg, int64_
                   int64_t *crow, int32_t *ccol, int64_t *nnz_out, const Workspace &ws,
                   int32_t *idle, int64_t idle_cap, hipStream_t s) {
     const QuotientWs q = quotient_ws(ws, idle, idle_cap);
-    HIP_TRY(ctx, quotient_graph(g->row_ptr, g->col, g->n, g->nnz, agg, n_agg, crow, ccol, q, s));
-    int64_t nnz = 0;
-    HIP_TRY(ctx, hipMemcpyAsync(&ctx->pinned[0], crow + n_agg, sizeof(int64_t),
-                                hipMemcpyDeviceToHost, s));
+    HIP_TRY(ctx, quotient_graph(g->row_ptr, g->col, g->n, g->nnz, agg, n_agg, crow, ccol, q,
+                                (unsigned long long *)ctx->pinned, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
-    memcpy(&nnz, ctx->pinned, sizeof nnz);
-    if (nnz_out) *nnz_out = nnz;
+    if (nnz_out) *nnz_out = pinned_i64(ctx, 0);
     return MIS2_OK;
 }
 
@@ -1776,12 +1781,10 @@ int batch_level(mis2_ctx *ctx, const mis2_graph &cur, uint64_t seed, int64_t sto
     if (n_next > 0) {
         const QuotientWs q = quotient_ws(ws, idle, idle_cap);
         HIP_TRY(ctx, quotient_graph(cur.row_ptr, cur.col, cur.n, cur.nnz, ar.map, n_next, crow_next,
-                                    ccol_next, q, s));
-        HIP_TRY(ctx, hipMemcpyAsync(&ctx->pinned[0], crow_next + n_next, sizeof(int64_t),
-                                    hipMemcpyDeviceToHost, s));
+                                    ccol_next, q, (unsigned long long *)ctx->pinned, s));
     }
     HIP_TRY(ctx, hipStreamSynchronize(s));
-    if (n_next > 0) memcpy(&bl->nnz_next, ctx->pinned, sizeof(int64_t));
+    if (n_next > 0) bl->nnz_next = pinned_i64(ctx, 0);
     return MIS2_OK;
 }
 
@@ -1890,7 +1893,6 @@ int mis2_galerkin(mis2_ctx *ctx, const mis2_graph *g, const double *val, const d
     int32_t *rank = (int32_t *)take(4 * (size_t)n);
     int32_t *members = (int32_t *)take(4 * (size_t)n);
     unsigned long long *part = (unsigned long long *)take(8 * (size_t)scan_parts(na));
-    uint32_t *flag = (uint32_t *)take(256);
     if (ctx->validate) {
         // both graphs, before the arrays below are filled (same memory)
         Workspace ws;
@@ -1900,21 +1902,20 @@ int mis2_galerkin(mis2_ctx *ctx, const mis2_graph *g, const double *val, const d
         if ((rc = maybe_validate(ctx, coarse, ws, s))) return rc;
     }
     // ids in range before anything indexes by them
-    HIP_TRY(ctx, launch_fill_u32(flag, 0u, 1, s));
+    uint32_t *const flag = ctx->pinned;
+    for (int k = 0; k < 3; k++) __atomic_store_n(flag + k, 0u, __ATOMIC_RELEASE);
     HIP_TRY(ctx, launch_check_ids(n, agg, coarse->nnz, coarse->col, na, flag, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, flag, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
-    if (ctx->pinned[0] & 1u) return fail(ctx, MIS2_EINVAL, "aggregate id outside [0, %lld)", (long long)na);
-    if (ctx->pinned[0] & 2u) return fail(ctx, MIS2_EINVAL, "coarse column outside [0, %lld)", (long long)na);
+    if (pinned_u32(ctx, 0)) return fail(ctx, MIS2_EINVAL, "aggregate id outside [0, %lld)", (long long)na);
+    if (pinned_u32(ctx, 1)) return fail(ctx, MIS2_EINVAL, "coarse column outside [0, %lld)", (long long)na);
     // members of each aggregate by increasing id
     HIP_TRY(ctx, launch_member_lists(n, agg, na, cnt, moff, part, rank, members, s));
     HIP_TRY(ctx, launch_sort_members(na, moff, members, s));
     HIP_TRY(ctx, launch_galerkin(g->row_ptr, g->col, val, diag, agg, na, moff, members,
                                  coarse->row_ptr, coarse->col, coarse_val, coarse_diag, flag,
                                  g->nnz, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, flag, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
-    if (ctx->pinned[0] & 4u)
+    if (pinned_u32(ctx, 2))
         return fail(ctx, MIS2_EINVAL, "the coarse graph lacks a coupling of the aggregation");
     return MIS2_OK;
 }
@@ -1967,16 +1968,6 @@ SmoothedWs carve_smoothed(void *base, int64_t n, int64_t n_agg, int64_t p_nnz, i
     return w;
 }
 
-// *out = the int64 at device address src, and the error flags (one sync).
-int read_total(mis2_ctx *ctx, const int64_t *src, const uint32_t *flag, int64_t *out,
-               uint32_t *flags, hipStream_t s) {
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, src, 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned + 2, flag, 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
-    *out = (int64_t)((uint64_t)ctx->pinned[0] | ((uint64_t)ctx->pinned[1] << 32));
-    *flags = ctx->pinned[2];
-    return MIS2_OK;
-}
 }  // namespace
 
 int mis2_smoothed(mis2_ctx *ctx, const mis2_graph *g, const double *val, const double *diag,
@@ -2011,10 +2002,10 @@ int mis2_smoothed(mis2_ctx *ctx, const mis2_graph *g, const double *val, const d
     // aggregate ids in range (checked before any is used as an index), and
     // the aggregate sizes
     HIP_TRY(ctx, launch_fill_u32(w.flag, 0u, 16, s));
-    HIP_TRY(ctx, launch_check_ids(n, agg, 0, nullptr, n_agg, w.flag, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, w.flag, 4, hipMemcpyDeviceToHost, s));
+    __atomic_store_n(ctx->pinned, 0u, __ATOMIC_RELEASE);
+    HIP_TRY(ctx, launch_check_ids(n, agg, 0, nullptr, n_agg, ctx->pinned, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
-    if (ctx->pinned[0] & 1u)
+    if (pinned_u32(ctx, 0))
         return fail(ctx, MIS2_EINVAL, "mis2_smoothed: aggregate id outside [0, n_agg)");
     HIP_TRY(ctx, launch_fill_u32(w.size, 0u, n_agg, s));
     HIP_TRY(ctx, launch_count_of(n, agg, w.size, s));
@@ -2030,9 +2021,14 @@ int mis2_smoothed(mis2_ctx *ctx, const mis2_graph *g, const double *val, const d
             HIP_TRY(ctx, launch_smoothed_sym(kind, false, rows, g->nnz, g->row_ptr, g->col, agg, sptr,
                                              scol, w.moff, w.members, w.prow_of, w.cnt, nullptr,
                                              nullptr, flag, w.cls, spare, later != 0, s));
-            HIP_TRY(ctx, exclusive_scan_u32_i64(w.cnt, rows, ptr, w.part, s));
-            const int rc2 = read_total(ctx, ptr + rows, flag, total, &flags, s);
-            if (rc2 || !(flags & kSymLarge)) return rc2;
+            ScanHost host;
+            host.word = (unsigned long long *)ctx->pinned;
+            host.flag = flag;
+            HIP_TRY(ctx, exclusive_scan_u32_i64(w.cnt, rows, ptr, w.part, s, host));
+            HIP_TRY(ctx, hipStreamSynchronize(s));
+            *total = pinned_i64(ctx, 0);
+            flags = (uint32_t)pinned_i64(ctx, 1);
+            if (!(flags & kSymLarge)) break;
         }
         return MIS2_OK;
     };

@@ -58,7 +58,7 @@ __device__ __forceinline__ int64_t lane_bcast64(int64_t v, int l) {
     return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-// flag[0] |= 1 when an aggregate id is outside [0, n_agg); flag[0] |= 2 when a
+// flag[0] = 1 when an aggregate id is outside [0, n_agg); flag[1] = 1 when a
 // coarse column is.
 __global__ __launch_bounds__(kBlock) void k_check_ids(int64_t n, const int32_t *__restrict__ agg,
                                                       int64_t cnnz,
@@ -70,7 +70,8 @@ __global__ __launch_bounds__(kBlock) void k_check_ids(int64_t n, const int32_t *
         if (v < n && (agg[v] < 0 || agg[v] >= n_agg)) bad |= 1u;
         if (v < cnnz && (ccol[v] < 0 || ccol[v] >= n_agg)) bad |= 2u;
     }
-    if (bad) atomicOr(flag, bad);
+    if (bad & 1u) flag[0] = 1u;
+    if (bad & 2u) flag[1] = 1u;
 }
 
 // The slot of coarse column b in the ascending cs[0 .. d) (top: the largest
@@ -174,7 +175,7 @@ __device__ __forceinline__ void fold_chunk(int p, double v, int d, double *acc, 
     }
 }
 
-// flag[0] |= 4 when an entry's aggregate pair is missing from the coarse row.
+// flag[2] = 1 when an entry's aggregate pair is missing from the coarse row.
 __global__ __launch_bounds__(kBlock) void k_galerkin(
     const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
     const double *__restrict__ val, const double *__restrict__ diag,
@@ -271,7 +272,7 @@ __global__ __launch_bounds__(kBlock) void k_galerkin(
         cval[c0 + p] = acc[p] / sqrt(na * nb);
     }
     if (lane == 0) cdiag[a] = m1 > m0 ? *accd / sqrt(na * na) : *accd;
-    if (missing) atomicOr(flag, missing);
+    if (missing) flag[2] = 1u;
 }
 
 int grid_for(int64_t work, int cap) {

@@ -412,8 +412,10 @@ hipError_t launch_place_rows(int64_t nk, const int32_t *order, const int64_t *mo
                              const int32_t *members, const int64_t *cluster_off, int32_t *rows,
                              hipStream_t s);
 hipError_t launch_scatter_pos(int64_t n, const int32_t *rows, int32_t *pos, hipStream_t s);
-// galerkin.hip: *flag |= 1 (an aggregate id outside [0, n_agg)), 2 (a coarse
-// column outside it), 4 (a coupling missing from the coarse graph).
+// galerkin.hip: words set to 1 where something is wrong (host-pinned, read once
+// the stream is synchronised): flag[0] an aggregate id outside [0, n_agg),
+// flag[1] a coarse column outside it, flag[2] a coupling missing from the coarse
+// graph.
 hipError_t launch_check_ids(int64_t n, const int32_t *agg, int64_t cnnz, const int32_t *ccol,
                             int64_t n_agg, uint32_t *flag, hipStream_t s);
 hipError_t launch_galerkin(const int64_t *row_ptr, const int32_t *col, const double *val,
@@ -527,11 +529,24 @@ hipError_t compact_u32_eq(const uint32_t *a, uint32_t value, int64_t n, int32_t 
                           uint32_t *d_count, uint32_t *blocksum, hipStream_t s);
 hipError_t compact_u8_nz(const uint8_t *a, int64_t n, int32_t *out, uint32_t *d_count,
                          uint32_t *blocksum, hipStream_t s);
+// Where a scan's last thread leaves what the host reads after the stream's next
+// synchronisation, instead of a copy each: word[0] = the total, word[1] = *flag
+// (host-pinned; either may be null).
+struct ScanHost {
+    unsigned long long *word = nullptr;
+    const uint32_t *flag = nullptr;
+    __device__ __forceinline__ void store(unsigned long long total) const {
+        if (!word) return;
+        word[0] = total;
+        if (flag) word[1] = *flag;
+    }
+};
 // Exclusive prefix sum of n u32 values into int64 out[0..n]; part needs
 // scan_parts(n) entries.
 int64_t scan_parts(int64_t n);
 hipError_t exclusive_scan_u32_i64(const uint32_t *in, int64_t n, int64_t *out,
-                                  unsigned long long *part, hipStream_t s);
+                                  unsigned long long *part, hipStream_t s,
+                                  const ScanHost &host = ScanHost{});
 // Exclusive scan of blocksum[0..nb) in place; total -> blocksum[nb], *d_total.
 hipError_t launch_scan_tiles(uint32_t *blocksum, int64_t nb, uint32_t *d_total, hipStream_t s);
 
@@ -564,10 +579,12 @@ struct QuotientWs {
 hipError_t launch_member_lists(int64_t n, const int32_t *agg, int64_t n_agg, uint32_t *cnt,
                                int64_t *moff, unsigned long long *part, int32_t *rank,
                                int32_t *members, hipStream_t s);
-// nnz: stored entries of the fine graph (no coarse row has more candidates).
+// nnz: stored entries of the fine graph (no coarse row has more candidates);
+// host_nnz: the coarse graph's entries, to be read once the stream is
+// synchronised (host-pinned, may be null).
 hipError_t quotient_graph(const int64_t *row_ptr, const int32_t *col, int64_t n, int64_t nnz,
                           const int32_t *agg, int64_t n_agg, int64_t *crow, int32_t *ccol,
-                          const QuotientWs &q, hipStream_t s);
+                          const QuotientWs &q, unsigned long long *host_nnz, hipStream_t s);
 
 // batch.hip: graph-local numbering of a union's aggregates.
 hipError_t launch_graph_bounds(const int32_t *list, const uint32_t *d_count, const int64_t *voff,

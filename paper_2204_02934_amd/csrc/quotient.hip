@@ -305,6 +305,61 @@ __global__ __launch_bounds__(kBlock) void k_member_scatter(int64_t n, const int3
     }
 }
 
+// The same, with the offsets, for small graphs: one workgroup, the counts in LDS
+// (one launch of 6 us instead of five: fill, ranks, scan, scatter).
+constexpr int kFewThreads = 1024, kFewVertices = 8192;
+
+__global__ __launch_bounds__(kFewThreads) void k_member_few(int n, const int32_t *__restrict__ agg,
+                                                            int n_agg, uint32_t *__restrict__ cnt,
+                                                            int64_t *__restrict__ moff,
+                                                            int32_t *__restrict__ members) {
+    constexpr int kPer = kFewVertices / kFewThreads;
+    __shared__ uint32_t at[kFewVertices];
+    __shared__ uint32_t wsum[kFewThreads / 64];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < n_agg; i += kFewThreads) at[i] = 0u;
+    __syncthreads();
+    int32_t a[kPer];
+    uint32_t rank[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; k++) {
+        const int v = k * kFewThreads + tid;
+        a[k] = v < n ? agg[v] : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; k++)
+        if (a[k] >= 0) rank[k] = atomicAdd(&at[a[k]], 1u);
+    __syncthreads();
+    // the offsets: kPer counts in a row per thread
+    uint32_t c[kPer], mine = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; k++) {
+        const int i = tid * kPer + k;
+        c[k] = i < n_agg ? at[i] : 0u;
+        mine += c[k];
+    }
+    const uint32_t incl = wave_incl_scan(mine);
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t run = incl - mine;
+    for (int w = 0; w < wave; w++) run += wsum[w];
+#pragma unroll
+    for (int k = 0; k < kPer; k++) {
+        const int i = tid * kPer + k;
+        if (i < n_agg) {
+            at[i] = run;
+            cnt[i] = c[k];
+            moff[i] = (int64_t)run;
+        }
+        run += c[k];
+    }
+    if (tid == kFewThreads - 1) moff[n_agg] = (int64_t)run;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPer; k++)
+        if (a[k] >= 0) members[at[a[k]] + rank[k]] = k * kFewThreads + tid;
+}
+
 // Sum over the workgroup (all threads must call it; result in every thread).
 __device__ __forceinline__ unsigned long long block_sum(unsigned long long x,
                                                         unsigned long long *scratch) {
@@ -602,8 +657,9 @@ __global__ __launch_bounds__(kBlock) void k_coarse_rows(
     }
 }
 
-// Giant rows, one bitmap slot each (gmeta: rows [0, S), smallest ids
-// [S, 2S), largest ids [2S, 3S), rows claimed [3S]).  Slots blockIdx.y,
+// Giant rows, one bitmap slot each (gmeta: rows [0, S), INT32_MAX less the
+// smallest ids [S, 2S), the largest ids plus one [2S, 3S), rows claimed [3S]; all
+// zero before a count pass).  Slots blockIdx.y,
 // blockIdx.y + gridDim.y, ...; the workgroups of a slot share its members in chunks of kBlock, kGiantParts
 // workgroups to a chunk (a chunk that holds hubs has a hundred times the
 // entries of another).  Where the
@@ -659,8 +715,8 @@ __global__ __launch_bounds__(kBlock) void k_giant_set(const int64_t *__restrict_
                 for (int i = (tmin >> 5) + (int)threadIdx.x; i <= tmax >> 5; i += kBlock)
                     if (buf[i]) atomicOr(&bits[i], buf[i]);
             if (threadIdx.x == 0) {
-                atomicMin((int32_t *)&gmeta[kGiantSlots + slot], tmin);
-                atomicMax((int32_t *)&gmeta[2 * kGiantSlots + slot], tmax);
+                atomicMax(&gmeta[kGiantSlots + slot], (uint32_t)(INT32_MAX - tmin));
+                atomicMax(&gmeta[2 * kGiantSlots + slot], (uint32_t)(tmax + 1));
             }
         }
         __syncthreads();  // the bitmap is cleared for the next slot
@@ -682,8 +738,8 @@ __global__ __launch_bounds__(kBlock) void k_giant_emit(const uint32_t *__restric
     const int slot = (int)blockIdx.x;
     if ((uint32_t)slot >= min(gmeta[3 * kGiantSlots], slots)) return;
     const int64_t a = gmeta[slot];
-    const int32_t lo = (int32_t)gmeta[kGiantSlots + slot];
-    const int32_t hi = (int32_t)gmeta[2 * kGiantSlots + slot];
+    const int32_t lo = INT32_MAX - (int32_t)gmeta[kGiantSlots + slot];
+    const int32_t hi = (int32_t)gmeta[2 * kGiantSlots + slot] - 1;
     const uint32_t *bits = gbits + (int64_t)slot * words;
     uint32_t run = 0;
     if (hi >= 0) {
@@ -717,16 +773,6 @@ __global__ __launch_bounds__(kBlock) void k_giant_emit(const uint32_t *__restric
     if (!FILL && threadIdx.x == 0) ccnt[a] = run;
 }
 
-// gmeta before a count pass: no rows, empty ranges.
-__global__ __launch_bounds__(kBlock) void k_giant_init(uint32_t *__restrict__ gmeta) {
-    const int i = (int)threadIdx.x;
-    static_assert(kGiantMeta <= kBlock, "one thread per word");
-    if (i < kGiantMeta)
-        gmeta[i] = (i >= kGiantSlots && i < 2 * kGiantSlots) ? (uint32_t)INT32_MAX
-                   : (i >= 2 * kGiantSlots && i < 3 * kGiantSlots) ? 0xFFFFFFFFu
-                   : 0u;
-}
-
 int grid_for(int64_t work, int per_block, int cap) {
     int64_t b = (work + per_block - 1) / per_block;
     if (b < 1) b = 1;
@@ -736,11 +782,19 @@ int grid_for(int64_t work, int per_block, int cap) {
 
 }  // namespace
 
-hipError_t launch_member_lists(int64_t n, const int32_t *agg, int64_t n_agg, uint32_t *cnt,
-                               int64_t *moff, unsigned long long *part, int32_t *rank,
-                               int32_t *members, hipStream_t s) {
+namespace {
+
+// cnt is zero already (cleared), unless the few-vertices kernel clears its own.
+hipError_t member_lists(int64_t n, const int32_t *agg, int64_t n_agg, uint32_t *cnt, int64_t *moff,
+                        unsigned long long *part, int32_t *rank, int32_t *members, bool cleared,
+                        hipStream_t s) {
     hipError_t e;
-    if ((e = launch_fill_u32(cnt, 0u, n_agg, s)) != hipSuccess) return e;
+    if (n <= kFewVertices && n_agg <= kFewVertices) {
+        hipLaunchKernelGGL(k_member_few, dim3(1), dim3(kFewThreads), 0, s, (int)n, agg, (int)n_agg,
+                           cnt, moff, members);
+        return hipGetLastError();
+    }
+    if (!cleared && (e = launch_fill_u32(cnt, 0u, n_agg, s)) != hipSuccess) return e;
     const int blocks = grid_for(n, kBlock, 8192);
     if (n > 0)
         hipLaunchKernelGGL(k_member_rank, dim3(blocks), dim3(kBlock), 0, s, n, agg, cnt, rank);
@@ -751,13 +805,18 @@ hipError_t launch_member_lists(int64_t n, const int32_t *agg, int64_t n_agg, uin
     return hipGetLastError();
 }
 
+}  // namespace
+
+hipError_t launch_member_lists(int64_t n, const int32_t *agg, int64_t n_agg, uint32_t *cnt,
+                               int64_t *moff, unsigned long long *part, int32_t *rank,
+                               int32_t *members, hipStream_t s) {
+    return member_lists(n, agg, n_agg, cnt, moff, part, rank, members, false, s);
+}
+
 hipError_t quotient_graph(const int64_t *row_ptr, const int32_t *col, int64_t n, int64_t nnz,
                           const int32_t *agg, int64_t n_agg, int64_t *crow, int32_t *ccol,
-                          const QuotientWs &q, hipStream_t s) {
+                          const QuotientWs &q, unsigned long long *host_nnz, hipStream_t s) {
     hipError_t e;
-    if ((e = launch_member_lists(n, agg, n_agg, q.cnt, q.moff, q.part, q.rank, q.members, s)) !=
-        hipSuccess)
-        return e;
     // no coarse row has more candidates than the fine graph has entries
     const bool giant = nnz > kGiantCand && n_agg > 0;
     const int64_t words = (int64_t)giant_words(n_agg);
@@ -786,12 +845,16 @@ hipError_t quotient_graph(const int64_t *row_ptr, const int32_t *col, int64_t n,
     const int bwords = (int)std::min<int64_t>(words, kBitWords);
     const bool wide = nnz > 0xFFFFFFFFll;
     {
-        FillSpans f;
+        FillSpans f;  // all that has to be clear, in one launch
+        f.add(q.cnt, 0u, n_agg);
         f.add(sp.cursor, 0u, kSpareParts * kSpareLine);
         if (giant) f.add(q.gbits, 0u, (int64_t)slots * words);
+        if (giant) f.add(q.gmeta, 0u, kGiantMeta);
         if ((e = launch_fill_spans(f, s)) != hipSuccess) return e;
     }
-    if (giant) hipLaunchKernelGGL(k_giant_init, dim3(1), dim3(kBlock), 0, s, q.gmeta);
+    if ((e = member_lists(n, agg, n_agg, q.cnt, q.moff, q.part, q.rank, q.members, true, s)) !=
+        hipSuccess)
+        return e;
     auto group = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(gblocks), dim3(kBlock), 0, s, row_ptr, col, agg, n_agg,
                            q.moff, q.members, maxc, q.cnt, sp, q.cls,
@@ -831,7 +894,9 @@ hipError_t quotient_graph(const int64_t *row_ptr, const int32_t *col, int64_t n,
                            (const uint32_t *)q.gbits, words, (const uint32_t *)q.gmeta, slots, q.cnt,
                            (const int64_t *)nullptr, (int32_t *)nullptr);
     }
-    if ((e = exclusive_scan_u32_i64(q.cnt, n_agg, crow, q.part, s)) != hipSuccess) return e;
+    ScanHost host;
+    host.word = host_nnz;
+    if ((e = exclusive_scan_u32_i64(q.cnt, n_agg, crow, q.part, s, host)) != hipSuccess) return e;
     if (n_agg > 0) {
         hipLaunchKernelGGL(k_copy_rows, dim3(grid_for(n_agg, kBlock / 16, 8192)), dim3(kBlock), 0,
                            s, n_agg, q.moff, (const int64_t *)crow, (const uint8_t *)q.cls, sp,
