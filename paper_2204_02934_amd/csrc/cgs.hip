@@ -447,32 +447,6 @@ __device__ __forceinline__ int64_t lane_bcast64(int64_t v, int l) {
     return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-// acc minus the terms of the first W lanes of its DPP row, in lane order, one
-// rounding each: acc + (-t) * 1.0.  The instructions name the lane they read; a
-// wait covers a term written just before, another a lane read just after.
-template <int W>
-__device__ __forceinline__ double chain(double acc, double term) {
-    static_assert(W == 8 || W == 12 || W == 16, "chain: 8, 12 or 16 lanes");
-#define MIS2_SUB(k) "v_fmac_f64_dpp %0, -%1, %2 row_newbcast:" #k " row_mask:0xf bank_mask:0xf\n"
-#define MIS2_SUB8                                                                         \
-    "s_nop 1\n" MIS2_SUB(0) MIS2_SUB(1) MIS2_SUB(2) MIS2_SUB(3) MIS2_SUB(4) MIS2_SUB(5) \
-        MIS2_SUB(6) MIS2_SUB(7)
-#define MIS2_SUB12 MIS2_SUB8 MIS2_SUB(8) MIS2_SUB(9) MIS2_SUB(10) MIS2_SUB(11)
-#define MIS2_SUB16 MIS2_SUB12 MIS2_SUB(12) MIS2_SUB(13) MIS2_SUB(14) MIS2_SUB(15)
-    if constexpr (W == 8) {
-        asm volatile(MIS2_SUB8 "s_nop 1" : "+v"(acc) : "v"(term), "v"(1.0));
-    } else if constexpr (W == 12) {
-        asm volatile(MIS2_SUB12 "s_nop 1" : "+v"(acc) : "v"(term), "v"(1.0));
-    } else {
-        asm volatile(MIS2_SUB16 "s_nop 1" : "+v"(acc) : "v"(term), "v"(1.0));
-    }
-#undef MIS2_SUB
-#undef MIS2_SUB8
-#undef MIS2_SUB12
-#undef MIS2_SUB16
-    return acc;
-}
-
 // The largest value among the group's lanes up to this one (x >= 0).
 template <int G>
 __device__ __forceinline__ int group_incl_max(int x) {
@@ -531,8 +505,8 @@ __device__ __forceinline__ void run_chains(CgsStage<R, Cap> *stage, int NB, int 
         }
         read(kk + 2, w, u);
 #pragma unroll
-        for (int c = 0; c + 1 < K; c++) acc = chain<16>(acc, term[c]);
-        acc = chain<W>(acc, term[K - 1]);
+        for (int c = 0; c + 1 < K; c++) acc = chain_sub<16>(acc, term[c]);
+        acc = chain_sub<W>(acc, term[K - 1]);
         xs = acc / dk;
         if (q == 0 && lane < 16 * C && kk < nbg) S.xb[kk] = xs;
         dk = dn;
@@ -553,7 +527,7 @@ __device__ __forceinline__ void run_long_chains(CgsStage<R, Cap> *stage, int NB,
             const int e = kk * L + c + q;
             const bool in = c + q < L;
             const double p = S.v[e] * S.xb[in ? (int)S.tag[e] : R];
-            acc = chain<16>(acc, in ? p : 0.0);
+            acc = chain_sub<16>(acc, in ? p : 0.0);
         }
         const double xs = acc / dk;
         if (q == 0 && lane < 16 * C && kk < nbg) S.xb[kk] = xs;
@@ -704,11 +678,11 @@ __global__ __launch_bounds__(C *SL, MinW) void k_cgs_cluster(
                 }
 #pragma unroll
                 for (int c = 0; c < 4; c++) {
-                    acc = chain<16>(acc, term[c]);
+                    acc = chain_sub<16>(acc, term[c]);
                     if (R == 64) {  // on through the other rows' 16 lanes
-                        acc = chain<16>(lane_bcast(acc, 0), term[c]);
-                        acc = chain<16>(lane_bcast(acc, 16), term[c]);
-                        acc = chain<16>(lane_bcast(acc, 32), term[c]);
+                        acc = chain_sub<16>(lane_bcast(acc, 0), term[c]);
+                        acc = chain_sub<16>(lane_bcast(acc, 16), term[c]);
+                        acc = chain_sub<16>(lane_bcast(acc, 32), term[c]);
                         acc = lane_bcast(acc, 48);
                     }
                 }

@@ -66,6 +66,39 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
     return x;
 }
 
+// acc plus (minus) the terms of the first W lanes of its DPP row of 16, in lane
+// order, one rounding each: acc + t * 1.0.  The instructions name the lane they
+// read, 7.5 cycles a term; a wait covers a term written just before, another a
+// lane read just after.
+#define MIS2_ADD(sign, k) \
+    "v_fmac_f64_dpp %0, " sign "%1, %2 row_newbcast:" #k " row_mask:0xf bank_mask:0xf\n"
+#define MIS2_ADD8(sign)                                                                      \
+    "s_nop 1\n" MIS2_ADD(sign, 0) MIS2_ADD(sign, 1) MIS2_ADD(sign, 2) MIS2_ADD(sign, 3)    \
+        MIS2_ADD(sign, 4) MIS2_ADD(sign, 5) MIS2_ADD(sign, 6) MIS2_ADD(sign, 7)
+#define MIS2_ADD12(sign) \
+    MIS2_ADD8(sign) MIS2_ADD(sign, 8) MIS2_ADD(sign, 9) MIS2_ADD(sign, 10) MIS2_ADD(sign, 11)
+#define MIS2_ADD16(sign) \
+    MIS2_ADD12(sign) MIS2_ADD(sign, 12) MIS2_ADD(sign, 13) MIS2_ADD(sign, 14) MIS2_ADD(sign, 15)
+template <int W>
+__device__ __forceinline__ double chain_sub(double acc, double term) {
+    static_assert(W == 8 || W == 12 || W == 16, "chain_sub: 8, 12 or 16 lanes");
+    if constexpr (W == 8)
+        asm volatile(MIS2_ADD8("-") "s_nop 1" : "+v"(acc) : "v"(term), "v"(1.0));
+    else if constexpr (W == 12)
+        asm volatile(MIS2_ADD12("-") "s_nop 1" : "+v"(acc) : "v"(term), "v"(1.0));
+    else
+        asm volatile(MIS2_ADD16("-") "s_nop 1" : "+v"(acc) : "v"(term), "v"(1.0));
+    return acc;
+}
+__device__ __forceinline__ double chain_add16(double acc, double term) {
+    asm volatile(MIS2_ADD16("") "s_nop 1" : "+v"(acc) : "v"(term), "v"(1.0));
+    return acc;
+}
+#undef MIS2_ADD
+#undef MIS2_ADD8
+#undef MIS2_ADD12
+#undef MIS2_ADD16
+
 // Reductions over aligned groups of L lanes (L a power of two <= 64); every
 // lane of a group gets the group's result.
 #define MIS2_GROUP_REDUCE(NAME, T, XOR, OP)                    \
