@@ -1117,6 +1117,14 @@ int mis2_create(mis2_ctx **out, int device) {
         delete ctx;
         return MIS2_EHIP;
     }
+    if (hipHostMalloc((void **)&ctx->stage, kStageBytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipHostFree(ctx->pinned);
+        (void)hipHostFree(ctx->pinned_ctr);
+        (void)hipHostFree(ctx->alive_host);
+        (void)hipHostFree(ctx->pinned_rt);
+        delete ctx;
+        return MIS2_EHIP;
+    }
     *out = ctx;
     return MIS2_OK;
 }
@@ -1127,6 +1135,7 @@ void mis2_destroy(mis2_ctx *ctx) {
     if (ctx->pinned_ctr) (void)hipHostFree(ctx->pinned_ctr);
     if (ctx->alive_host) (void)hipHostFree(ctx->alive_host);
     if (ctx->pinned_rt) (void)hipHostFree(ctx->pinned_rt);
+    if (ctx->stage) (void)hipHostFree(ctx->stage);
     for (hipEvent_t e : ctx->events) (void)hipEventDestroy(e);
     delete ctx;
 }
@@ -1691,6 +1700,22 @@ size_t batch_bytes(int32_t G, int64_t n, int64_t nnz) {
            3 * align_up(4 * ug) + 2 * align_up(ug);
 }
 
+// The per-graph tables of a level's G graphs, packed so that each of the three
+// exchanges with the host is one copy: up, the vertex offsets and id bits; down,
+// the row bounds and root prefixes; up, the new offsets and two flags.  (Eight
+// copies from and to pageable memory took some 210 us a level for 512 graphs.)
+struct BatchTables {
+    size_t down, up2, end;  // where the second and third begin, and the end
+};
+static BatchTables batch_tables(int32_t G) {
+    const size_t k = (size_t)G + 1;
+    BatchTables t;
+    t.down = align_up(12 * k);
+    t.up2 = t.down + align_up(16 * k);
+    t.end = t.up2 + align_up(10 * k);
+    return t;
+}
+
 BatchArena carve_batch_arena(void *base, int32_t G, int64_t n, int64_t nnz) {
     BatchArena a;
     a.head = workspace_bytes(n, MIS2_OP_COARSEN);
@@ -1707,14 +1732,7 @@ BatchArena carve_batch_arena(void *base, int32_t G, int64_t n, int64_t nnz) {
     const size_t ug = (size_t)G + 1;
     a.map = (int32_t *)take(4 * (size_t)n);
     a.gid = (int32_t *)take(4 * (size_t)n);
-    a.voff = (int64_t *)take(8 * ug);
-    a.newoff = (int64_t *)take(8 * ug);
-    a.bnd = (int64_t *)take(8 * ug);
-    a.gb = (uint32_t *)take(4 * ug);
-    a.P1 = (uint32_t *)take(4 * ug);
-    a.P2 = (uint32_t *)take(4 * ug);
-    a.cont = (uint8_t *)take(ug);
-    a.live = (uint8_t *)take(ug);
+    a.tab = (char *)take(batch_tables(G).end);
     return a;
 }
 
@@ -1723,15 +1741,33 @@ int batch_level(mis2_ctx *ctx, const mis2_graph &cur, uint64_t seed, int64_t sto
                 int32_t *idle, int64_t idle_cap, BatchLevel *bl, hipStream_t s) {
     int rc;
     const int32_t cg = (int32_t)bl->voff.size() - 1;
-    std::vector<uint32_t> gb(cg);
-    for (int32_t i = 0; i < cg; i++) gb[i] = (uint32_t)id_bits(bl->voff[i + 1] - bl->voff[i]);
-    HIP_TRY(ctx, hipMemcpyAsync(ar.voff, bl->voff.data(), 8 * ((size_t)cg + 1),
-                                hipMemcpyHostToDevice, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ar.gb, gb.data(), 4 * (size_t)cg, hipMemcpyHostToDevice, s));
-    HIP_TRY(ctx, launch_gather_i64(cur.row_ptr, ar.voff, (int64_t)cg + 1, ar.bnd, s));
+    const size_t k = (size_t)cg + 1;
+    const BatchTables tb = batch_tables(cg);
+    int64_t *const d_voff = (int64_t *)ar.tab;
+    uint32_t *const d_gb = (uint32_t *)(d_voff + k);
+    int64_t *const d_bnd = (int64_t *)(ar.tab + tb.down);
+    uint32_t *const d_P1 = (uint32_t *)(d_bnd + k), *const d_P2 = d_P1 + k;
+    int64_t *const d_newoff = (int64_t *)(ar.tab + tb.up2);
+    uint8_t *const d_cont = (uint8_t *)(d_newoff + k), *const d_live = d_cont + k;
+    // their host side: pinned, or for very many graphs a buffer of this call
+    std::vector<char> many;
+    char *host = ctx->stage;
+    if (tb.end > kStageBytes) {
+        many.resize(tb.end);
+        host = many.data();
+    }
+    int64_t *const voff = (int64_t *)host, *const bnd = (int64_t *)(host + tb.down);
+    int64_t *const newoff = (int64_t *)(host + tb.up2);
+    uint32_t *const gb = (uint32_t *)(voff + k);
+    const uint32_t *const P1 = (const uint32_t *)(bnd + k), *const P2 = P1 + k;
+    uint8_t *const cont = (uint8_t *)(newoff + k), *const live = cont + k;
+    memcpy(voff, bl->voff.data(), 8 * k);
+    for (int32_t i = 0; i < cg; i++) gb[i] = (uint32_t)id_bits(voff[i + 1] - voff[i]);
+    HIP_TRY(ctx, hipMemcpyAsync(ar.tab, host, 12 * k, hipMemcpyHostToDevice, s));
+    HIP_TRY(ctx, launch_gather_i64(cur.row_ptr, d_voff, (int64_t)cg + 1, d_bnd, s));
     BatchInfo bt;
-    bt.voff = ar.voff;
-    bt.gb = ar.gb;
+    bt.voff = d_voff;
+    bt.gb = d_gb;
     bt.G = cg;
     while ((int64_t{1} << bt.steps) < (int64_t)cg + 1) bt.steps++;
     HIP_TRY(ctx, launch_graph_ids(cur.n, bt, ar.gid, s));
@@ -1746,19 +1782,15 @@ int batch_level(mis2_ctx *ctx, const mis2_graph &cur, uint64_t seed, int64_t sto
     ws.colc = ccol_next;
     ws.lenc = (int32_t *)crow_next;
     int64_t na_all = 0;
-    if ((rc = aggregate_impl(ctx, &cur, seed, agg_dst, &na_all, nullptr, ws, s, ar.P1, ar.P2)))
+    if ((rc = aggregate_impl(ctx, &cur, seed, agg_dst, &na_all, nullptr, ws, s, d_P1, d_P2)))
         return rc;
-    std::vector<uint32_t> P1(cg + 1), P2(cg + 1);
-    std::vector<int64_t> bnd(cg + 1);
-    HIP_TRY(ctx, hipMemcpyAsync(P1.data(), ar.P1, 4 * ((size_t)cg + 1), hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipMemcpyAsync(P2.data(), ar.P2, 4 * ((size_t)cg + 1), hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipMemcpyAsync(bnd.data(), ar.bnd, 8 * ((size_t)cg + 1), hipMemcpyDeviceToHost, s));
+    HIP_TRY(ctx, hipMemcpyAsync(host + tb.down, ar.tab + tb.down, 16 * k, hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
 
     bl->nagg.assign(cg, 0);
     bl->nnz.assign(cg, 0);
     bl->cont.assign(cg, 0);
-    std::vector<int64_t> newoff(cg + 1, 0);
+    newoff[0] = 0;
     bl->next_voff.assign(1, 0);
     for (int32_t i = 0; i < cg; i++) {
         const int64_t ni = bl->voff[i + 1] - bl->voff[i];
@@ -1768,13 +1800,12 @@ int batch_level(mis2_ctx *ctx, const mis2_graph &cur, uint64_t seed, int64_t sto
         bl->cont[i] = bl->live[i] && bl->allow[i] && na != ni && na > 0 && na >= stop_below;
         newoff[i + 1] = newoff[i] + (bl->cont[i] ? na : 0);
         if (bl->cont[i]) bl->next_voff.push_back(newoff[i + 1]);
+        cont[i] = bl->cont[i];
+        live[i] = bl->live[i];
     }
     const int64_t n_next = newoff[cg];
-    HIP_TRY(ctx, hipMemcpyAsync(ar.cont, bl->cont.data(), (size_t)cg, hipMemcpyHostToDevice, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ar.live, bl->live.data(), (size_t)cg, hipMemcpyHostToDevice, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ar.newoff, newoff.data(), 8 * ((size_t)cg + 1),
-                                hipMemcpyHostToDevice, s));
-    HIP_TRY(ctx, launch_batch_local(cur.n, bt, ar.P1, ar.P2, agg_dst, ar.live, ar.cont, ar.newoff,
+    HIP_TRY(ctx, hipMemcpyAsync(d_newoff, newoff, 10 * k, hipMemcpyHostToDevice, s));
+    HIP_TRY(ctx, launch_batch_local(cur.n, bt, d_P1, d_P2, agg_dst, d_live, d_cont, d_newoff,
                                     n_next > 0 ? ar.map : nullptr, s));
     bl->n_next = n_next;
     bl->nnz_next = 0;

@@ -649,15 +649,14 @@ hipError_t launch_phase3(int lanes, int blocks, const int64_t *row_ptr, const in
 // Batched coarsening (abi.hip).  The arena is the caller's workspace: the
 // coarsening workspace of the union, two coarse-union CSR buffers, the
 // coarse-id map and the per-graph tables.
+constexpr size_t kStageBytes = (size_t)256 << 10;  // some 7000 graphs
 struct BatchArena {
     size_t head;           // bytes of the coarsening workspace at the start
     int64_t *crow[2];      // [n + 1]
     int32_t *ccol[2];      // [nnz]
     int32_t *map;          // [n]
     int32_t *gid;          // [n]
-    int64_t *voff, *newoff, *bnd;  // [G + 1]
-    uint32_t *gb, *P1, *P2;        // [G + 1]
-    uint8_t *cont, *live;          // [G + 1]
+    char *tab;             // the per-graph tables of a level
 };
 size_t batch_bytes(int32_t G, int64_t n, int64_t nnz);
 BatchArena carve_batch_arena(void *base, int32_t G, int64_t n, int64_t nnz);
@@ -693,6 +692,7 @@ struct mis2_ctx {
     void *ws = nullptr;
     size_t ws_bytes = 0;
     uint32_t *pinned = nullptr;  // host-pinned scalars for read-back
+    char *stage = nullptr;       // host-pinned [kStageBytes]: a batched level's tables
     uint32_t *pinned_ctr = nullptr;  // host-pinned [2][kCtrList]: worklist1 counters per chunk
     uint32_t epoch = 0;                        // of the last run of rounds (host words)
     unsigned long long *alive_host = nullptr;  // host-pinned [8]: (round << 32) | |worklist1|,
