@@ -288,6 +288,114 @@ __device__ __forceinline__ void coop_decide(const int32_t *__restrict__ col,
     all_eq = (int)group_and<64>((uint32_t)ae);
 }
 
+constexpr int kFlatEP = 8;     // consecutive edges per lane per step
+constexpr int kFlatRows = 64;  // rows per batch (one per lane)
+constexpr int64_t kFlatHeavy = 4096;  // rows longer than this take the cooperative path
+
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Per-wavefront LDS of a flat batch.
+struct FlatLds {
+    uint32_t off[kFlatRows + 1];  // flat offsets of the compacted non-empty rows
+    int64_t start[kFlatRows];     // their first column index
+    uint32_t t0[kFlatRows];       // their T_v (Decide Set)
+    uint32_t acc[kFlatRows];      // min (Refresh Column) or any-OUT (Decide Set)
+    uint32_t acc2[kFlatRows];     // all-equal (Decide Set)
+};
+
+// Loads the batch's rows (one per lane), compacts the non-empty light rows
+// into the LDS table and returns this lane's table index (-1 if none).
+// total: flat length of the batch.
+__device__ __forceinline__ int flat_table(FlatLds &sh, int64_t s, int64_t len, bool light,
+                                          uint32_t &total) {
+    const int lane = (int)(threadIdx.x & 63u);
+    const bool in = light && len > 0;
+    const uint64_t mask = __ballot(in);
+    const int idx = (int)__popcll(mask & lanes_below(lane));
+    // exclusive prefix of the lengths over the compacted rows
+    uint32_t l32 = in ? (uint32_t)len : 0u;
+    uint32_t incl = l32;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    total = (uint32_t)__shfl((int)incl, 63, 64);
+    if (in) {
+        sh.off[idx] = incl - l32;
+        sh.start[idx] = s;
+    }
+    if (lane == 0) sh.off[__popcll(mask)] = total;
+    return in ? idx : -1;
+}
+
+// Row of flat edge f: the last table row whose offset is <= f (7 fixed steps).
+__device__ __forceinline__ int flat_row(const FlatLds &sh, int nrows, uint32_t f) {
+    int lo = 0, hi = nrows;
+    for (int k = 0; k < 7; k++) {
+        const int mid = (lo + hi) >> 1;
+        if (mid > lo && sh.off[mid] <= f) lo = mid; else if (mid > lo) hi = mid;
+    }
+    return lo;
+}
+
+// The least tuple, computed, among this lane's row's entries [s, s + len), for a
+// step of one-lane rows of very different lengths: their entries in one flat
+// range, dealt out evenly, 4 at a time.  (A lane hashing its own row takes as
+// many steps as the longest of 64 rows: with 9 entries on average and some rows
+// of 32, three of four hashes were padding.)  All lanes must call it.
+__device__ __forceinline__ uint32_t flat_hash(FlatLds &sh, const int32_t *__restrict__ col,
+                                              const TupleParams &t0, int64_t s, int64_t len) {
+    const int lane = (int)(threadIdx.x & 63u);
+    uint32_t total;
+    const int me = flat_table(sh, s, len, true, total);
+    const int nrows = (int)__popcll(__ballot(me >= 0));
+    if (me >= 0) sh.acc[me] = kOut;
+    wave_lds_sync();
+    const uint32_t per = (total + 63) / 64;
+    const uint32_t f0 = min(per * (uint32_t)lane, total), f1 = min(f0 + per, total);
+    int r = f0 < f1 ? flat_row(sh, nrows, f0) : 0;
+    uint32_t next = sh.off[r + 1];
+    int64_t base = sh.start[r] - (int64_t)sh.off[r];
+    uint32_t part = kOut;
+    for (uint32_t j0 = 0; j0 < per; j0 += 4) {
+        int32_t x[4];
+        int rr[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const uint32_t f = f0 + j0 + j;
+            if (f < f1 && f >= next) {  // (no row of the table is empty)
+                r++;
+                next = sh.off[r + 1];
+                base = sh.start[r] - (int64_t)sh.off[r];
+            }
+            rr[j] = r;
+            x[j] = col[f < f1 ? base + (int64_t)f : 0];
+        }
+        uint32_t t[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) t[j] = make_tuple(t0, (uint32_t)x[j]);
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const uint32_t f = f0 + j0 + j;
+            if (f < f1) {
+                part = min(part, t[j]);
+                if (f + 1 == f1 || (j < 3 ? rr[j < 3 ? j + 1 : 3] != rr[j] : f + 1 >= next)) {
+                    atomicMin(&sh.acc[rr[j]], part);
+                    part = kOut;
+                }
+            }
+        }
+    }
+    wave_lds_sync();
+    const uint32_t m = me >= 0 ? sh.acc[me] : kOut;
+    wave_lds_sync();  // the table is rewritten by the next step
+    return m;
+}
+
 // Refresh Column over the wavefront's segment: U rows per lane group per
 // step, and K chunks of each row's column indices loaded before any of their
 // gathers, so that U * K independent loads are in flight.  Loads are issued
@@ -308,8 +416,11 @@ __device__ __forceinline__ uint32_t sweep_column(const int64_t *__restrict__ row
                                                  const int32_t *__restrict__ col,
                                                  const uint32_t *__restrict__ T,
                                                  uint32_t *__restrict__ M, const SegIO &io,
-                                                 const Seg &sg) {
+                                                 const Seg &sg, FlatLds *sh = nullptr) {
     constexpr int G = 64 / L;  // rows per wavefront per unrolled slot
+    // rounds that compute the tuples, one lane per row: flat_hash instead of
+    // lanes of their own where rows need more than one batch of loads
+    const bool flat = L == 1 && sh && io.gen0;
     const int lane = (int)(threadIdx.x & 63u);
     const int sub = lane & (L - 1);
     const int32_t *colc = io.ccol_in;
@@ -364,6 +475,7 @@ __device__ __forceinline__ uint32_t sweep_column(const int64_t *__restrict__ row
             // only for them)
             if (!RD && !WR && heavy && io.long_flag && lane == 0)
                 io.long_flag[(blockIdx.x % kSplit) * kCtrLine] = 1u;
+            if (flat) heavy = __ballot(sub == 0 && e[u] - s[u] > kFlatHeavy);
             while (heavy) {
                 const int src = __ffsll((unsigned long long)heavy) - 1;
                 heavy &= heavy - 1;
@@ -382,7 +494,13 @@ __device__ __forceinline__ uint32_t sweep_column(const int64_t *__restrict__ row
                 }
             }
         }
-        const int64_t steps = wave_max_len<U>(s, e);
+        int64_t steps = wave_max_len<U>(s, e);
+        if constexpr (L == 1) {
+            if (flat && steps > K) {
+                m[0] = min(m[0], flat_hash(*sh, col, io.t0, s[0], e[0] - s[0]));
+                steps = 0;
+            }
+        }
         for (int64_t c0 = 0; c0 < steps; c0 += (int64_t)L * K) {
             int32_t x[U][K];
 #pragma unroll
@@ -960,60 +1078,6 @@ __device__ __forceinline__ uint32_t sweep_decide_staged(const int64_t *__restric
 // first by the whole wavefront (coop_min_T / coop_decide) and leave the
 // flat range.
 // ---------------------------------------------------------------------------
-constexpr int kFlatEP = 8;     // consecutive edges per lane per step
-constexpr int kFlatRows = 64;  // rows per batch (one per lane)
-constexpr int64_t kFlatHeavy = 4096;  // rows longer than this take the cooperative path
-
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Per-wavefront LDS of a flat batch.
-struct FlatLds {
-    uint32_t off[kFlatRows + 1];  // flat offsets of the compacted non-empty rows
-    int64_t start[kFlatRows];     // their first column index
-    uint32_t t0[kFlatRows];       // their T_v (Decide Set)
-    uint32_t acc[kFlatRows];      // min (Refresh Column) or any-OUT (Decide Set)
-    uint32_t acc2[kFlatRows];     // all-equal (Decide Set)
-};
-
-// Loads the batch's rows (one per lane), compacts the non-empty light rows
-// into the LDS table and returns this lane's table index (-1 if none).
-// total: flat length of the batch.
-__device__ __forceinline__ int flat_table(FlatLds &sh, int64_t s, int64_t len, bool light,
-                                          uint32_t &total) {
-    const int lane = (int)(threadIdx.x & 63u);
-    const bool in = light && len > 0;
-    const uint64_t mask = __ballot(in);
-    const int idx = (int)__popcll(mask & lanes_below(lane));
-    // exclusive prefix of the lengths over the compacted rows
-    uint32_t l32 = in ? (uint32_t)len : 0u;
-    uint32_t incl = l32;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = (uint32_t)__shfl_up((int)incl, o, 64);
-        if (lane >= o) incl += y;
-    }
-    total = (uint32_t)__shfl((int)incl, 63, 64);
-    if (in) {
-        sh.off[idx] = incl - l32;
-        sh.start[idx] = s;
-    }
-    if (lane == 0) sh.off[__popcll(mask)] = total;
-    return in ? idx : -1;
-}
-
-// Row of flat edge f: the last table row whose offset is <= f (7 fixed steps).
-__device__ __forceinline__ int flat_row(const FlatLds &sh, int nrows, uint32_t f) {
-    int lo = 0, hi = nrows;
-    for (int k = 0; k < 7; k++) {
-        const int mid = (lo + hi) >> 1;
-        if (mid > lo && sh.off[mid] <= f) lo = mid; else if (mid > lo) hi = mid;
-    }
-    return lo;
-}
-
 template <int U>
 __device__ __forceinline__ uint32_t flat_column(const int64_t *__restrict__ row_ptr,
                                                 const int32_t *__restrict__ col,
@@ -1249,6 +1313,11 @@ __device__ __forceinline__ uint32_t any_decide(const int64_t *__restrict__ row_p
 // lists and does nothing; workgroup 0 of each Refresh Column records the
 // round's sizes and reports |worklist1| to the host.
 // ---------------------------------------------------------------------------
+// Refresh Column of rounds 0 and 1 computes the neighbours' tuples.
+__host__ __device__ __forceinline__ bool computes_tuples(const RoundsArgs &a, int r) {
+    return r <= 1 && a.gen0 && !a.masked && !a.batch.voff && !a.abl;
+}
+
 __device__ __forceinline__ SegIO round_col_io(const RoundsArgs &a, int r) {
     const int cur = r & 1, nxt = cur ^ 1;
     const bool first = r == 0;
@@ -1264,7 +1333,7 @@ __device__ __forceinline__ SegIO round_col_io(const RoundsArgs &a, int r) {
     io.S = a.S;
     io.nnz = a.nnz;
     if (r == 0 && !a.masked) io.long_flag = a.lflag;
-    if (r <= 1 && a.gen0 && !a.masked && !a.batch.voff && !a.abl) {
+    if (computes_tuples(a, r)) {
         io.gen0 = r + 1;
         io.t0 = TupleParams{xs64star((a.seed << 32) ^ (uint64_t)r), a.pmask, a.b, a.batch};
     }
@@ -1358,7 +1427,14 @@ __device__ __forceinline__ void col_round(const int64_t *__restrict__ row_ptr,
     }
     const int64_t w = wave_id();
     const Seg sg = seg_of(io, w);
-    const uint32_t kept = any_column<L, RD, WR>(row_ptr, col, T, M, io, sg);
+    uint32_t kept;
+    if constexpr (GEN && L == 1) {
+        __shared__ FlatLds sh[kBlock / 64];
+        kept = sweep_column<L, kRows, kChunks<L>, RD, WR>(row_ptr, col, T, M, io, sg,
+                                                          &sh[threadIdx.x >> 6]);
+    } else {
+        kept = any_column<L, RD, WR>(row_ptr, col, T, M, io, sg);
+    }
     seg_finish(io, w, kept);
 }
 
@@ -1371,9 +1447,10 @@ __global__ __launch_bounds__(kBlock) void k_col_round(const int64_t *__restrict_
     col_round<L, false, false>(row_ptr, col, T, M, a, r);
 }
 
-// Rounds 0 and 1: computes the neighbours' tuples where that is exact
-// (unmasked, one graph; round 1 after k_push_in), else gathers them as
-// k_col_round does.
+// Rounds 0 and 1 where the neighbours' tuples are computed and that is exact
+// (unmasked, one graph; round 1 after k_push_in).  One lane per row: with
+// flat_hash, Chung-Lu 4M vertices 304 -> 189 us a round.  The other runs' first
+// rounds take k_col_round, with fewer registers.
 template <int L>
 __global__ __launch_bounds__(kBlock) void k_col_round0(const int64_t *__restrict__ row_ptr,
                                                        const int32_t *__restrict__ col,
@@ -2321,7 +2398,7 @@ hipError_t launch_col_round(int lanes, int blocks, const int64_t *row_ptr, const
     } else if (mode == 2) {
         MIS2_LANE_DISPATCH_TIMED(lanes, k_col_round_rw, dim3(blocks), dim3(kBlock), s, e0, e1,
                                  row_ptr, col, T, M, a, r);
-    } else if (r <= 1) {
+    } else if (computes_tuples(a, r)) {
         MIS2_LANE_DISPATCH_TIMED(lanes, k_col_round0, dim3(blocks), dim3(kBlock), s, e0, e1,
                                  row_ptr, col, T, M, a, r);
     } else {
