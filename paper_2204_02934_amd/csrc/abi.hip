@@ -1435,6 +1435,14 @@ int mis2_last_tuning(const mis2_ctx *ctx, mis2_tune_record *out, int32_t cap, in
 
 namespace {
 
+// Pinned words that kernels wrote, after a synchronisation.
+int64_t pinned_i64(const mis2_ctx *ctx, int word) {
+    return (int64_t)__atomic_load_n((const unsigned long long *)ctx->pinned + word, __ATOMIC_ACQUIRE);
+}
+uint32_t pinned_u32(const mis2_ctx *ctx, int word) {
+    return __atomic_load_n(ctx->pinned + word, __ATOMIC_ACQUIRE);
+}
+
 // Algorithm 3 on a validated graph with n > 0 and a carved workspace.  In a
 // batched run (ctx->batch set) P1 / P2 (device, [G + 1] each) receive the
 // per-graph root bounds of phases 1 and 2 (see batch.hip) and agg_id holds
@@ -1450,6 +1458,9 @@ int phase1_labels(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Works
     int rc;
     const int64_t n = g->n;
     uint32_t *sc = ws.scalars;
+    // the counts and the error word of the run are written to the host's copies
+    // by the kernels that have them
+    __atomic_store_n(ctx->pinned + kS_Err, 0u, __ATOMIC_RELEASE);
     HIP_TRY(ctx, launch_init_tuples(tparams(ctx, n, seed, 0), n, ws.T, round_fills(g, ws, false),
                                     s));
     if ((rc = run_rounds(ctx, g, seed, ws, gm, false, 0, s, iters, launches, long_rows, nullptr,
@@ -1461,9 +1472,11 @@ int phase1_labels(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Works
         FillSpans f;
         f.add(sc, 0u, kScalars);
         f.add((uint32_t *)ws.label, 0xFFFFFFFFu, n);  // -1
+        f.add(ws.ctr, 0u, kCtrSlot);  // a masked run's active count goes to slot 0
         HIP_TRY(ctx, count_in_with_fills(ws.T, n, f, roots, ws.blocksum, s));
     }
-    HIP_TRY(ctx, scatter_counted_u32_eq(ws.T, kIn, n, ws.list, sc + kS_Count1, ws.blocksum, s));
+    HIP_TRY(ctx, scatter_counted_u32_eq(ws.T, kIn, n, ws.list, sc + kS_Count1, ws.blocksum, s,
+                                        ctx->pinned + kS_Count1));
     HIP_TRY(ctx, launch_label_roots(n, g->row_ptr, g->col, ws.list, sc + kS_Count1, nullptr, false,
                                     ws.label, ws.aggsize, roots, 1, s));
     return MIS2_OK;
@@ -1475,7 +1488,6 @@ int aggregate_basic_impl(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int3
                          int64_t *n_agg, uint8_t *roots, const Workspace &ws, hipStream_t s) {
     int rc;
     const int64_t n = g->n;
-    uint32_t *sc = ws.scalars;
     PlanScope ps{ctx, g, ctx->plan};
     if ((rc = apply_plan(ctx, g, ws, s, &ps.saved))) return rc;
     ps.armed = true;
@@ -1500,13 +1512,12 @@ int aggregate_basic_impl(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int3
     join_io.seg = gm.seg;
     join_io.S = gm.S;
     HIP_TRY(ctx, launch_join_min(lanes > 0 ? group_lanes(lanes) : 4, gm.blocks, g->row_ptr, g->col, ws.label,
-                                 join_io, agg_id, sc + kS_Err, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, sc, 8 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+                                 join_io, agg_id, ctx->pinned + kS_Err, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
     parse_trace(ctx, 0);
-    if (ctx->pinned[kS_Err])
+    if (pinned_u32(ctx, kS_Err))
         return fail(ctx, MIS2_EINTERNAL, "a vertex without an aggregated neighbour");
-    if (n_agg) *n_agg = (int64_t)ctx->pinned[kS_Count1];
+    if (n_agg) *n_agg = (int64_t)pinned_u32(ctx, kS_Count1);
     return collect_sweeps(ctx, launches, ws, s);
 }
 
@@ -1552,8 +1563,8 @@ int aggregate_impl(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int32_t *a
     // Phase 2: MIS-2 of the subgraph induced by the unlabelled vertices (same
     // ids and b, round counter from 0); roots with >= 2 unlabelled neighbours
     // become aggregates n1 + k.
-    // the active count goes to slot 0 of the size counters (round 0)
-    HIP_TRY(ctx, launch_fill_u32(ws.ctr, 0u, kCtrSlot, s));
+    // the active count goes to slot 0 of the size counters (round 0, clear
+    // since phase 1's end)
     SegIO act_io{};
     act_io.wl_out = ws.wl1[0];
     act_io.cnt_out = ws.cnt1[0];
@@ -1570,7 +1581,8 @@ int aggregate_impl(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int32_t *a
     // stores), then the ordered scatter
     HIP_TRY(ctx, launch_accept_phase2(n, g->row_ptr, g->col, ws.T, ws.label, ws.flag, s));
     HIP_TRY(ctx, count_u8_nz(ws.flag, n, ws.blocksum, s));
-    HIP_TRY(ctx, scatter_counted_u8_nz(ws.flag, n, ws.list, sc + kS_Count2, ws.blocksum, s));
+    HIP_TRY(ctx, scatter_counted_u8_nz(ws.flag, n, ws.list, sc + kS_Count2, ws.blocksum, s,
+                                       ctx->pinned + kS_Count2));
     HIP_TRY(ctx, launch_label_roots(n, g->row_ptr, g->col, ws.list, sc + kS_Count2,
                                     sc + kS_Count1, true, ws.label, ws.aggsize, roots, 2, s));
     if (P2)
@@ -1608,26 +1620,18 @@ int aggregate_impl(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int32_t *a
     const int64_t max_row = long_rows == 0 && lanes_for(ctx, g) > 0
                                 ? coop_threshold(lanes_for(ctx, g)) : INT64_MAX;
     HIP_TRY(ctx, launch_phase3(p3_lanes, gm.blocks, g->row_ptr, g->col, ws.label,
-                               ws.aggsize, p3_io, mid_io, max_row, agg_id, sc + kS_Err, s));
+                               ws.aggsize, p3_io, mid_io, max_row, agg_id, ctx->pinned + kS_Err, s));
 
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, sc, 8 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    // (the counts and the error word are in host memory already)
     HIP_TRY(ctx, hipStreamSynchronize(s));
     it1 = parse_trace(ctx, 0);
     it2 = parse_trace(ctx, 1);
-    if (ctx->pinned[kS_Err])
+    if (pinned_u32(ctx, kS_Err))
         return fail(ctx, MIS2_EINTERNAL, "phase-3 vertex without an aggregated neighbour");
-    if (n_agg) *n_agg = (int64_t)ctx->pinned[kS_Count1] + (int64_t)ctx->pinned[kS_Count2];
+    if (n_agg) *n_agg = (int64_t)pinned_u32(ctx, kS_Count1) + (int64_t)pinned_u32(ctx, kS_Count2);
     (void)it1;
     (void)it2;
     return collect_sweeps(ctx, launches, ws, s);
-}
-
-// Pinned words that kernels wrote, after a synchronisation.
-int64_t pinned_i64(const mis2_ctx *ctx, int word) {
-    return (int64_t)__atomic_load_n((const unsigned long long *)ctx->pinned + word, __ATOMIC_ACQUIRE);
-}
-uint32_t pinned_u32(const mis2_ctx *ctx, int word) {
-    return __atomic_load_n(ctx->pinned + word, __ATOMIC_ACQUIRE);
 }
 
 // The quotient's arrays of a coarsening workspace.  Everything before them
@@ -1729,7 +1733,6 @@ BatchArena carve_batch_arena(void *base, int32_t G, int64_t n, int64_t nnz) {
         a.crow[i] = (int64_t *)take(8 * ((size_t)n + 1));
         a.ccol[i] = (int32_t *)take(4 * (size_t)nnz);
     }
-    const size_t ug = (size_t)G + 1;
     a.map = (int32_t *)take(4 * (size_t)n);
     a.gid = (int32_t *)take(4 * (size_t)n);
     a.tab = (char *)take(batch_tables(G).end);

@@ -296,7 +296,7 @@ __global__ __launch_bounds__(kBlock) void k_phase3(const int64_t *__restrict__ r
             if (bc > 0)
                 agg_out[v] = ba;
             else
-                atomicOr(err, 1u);
+                *err = 1u;
         }
         const bool keep = valid && sub == 0 && is_long;
         const uint64_t mask = __ballot(keep);
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(kBlock) void k_phase3_mid(const int64_t *__restrict
                 if (bc > 0)
                     agg_out[vr] = ba;
                 else
-                    atomicOr(err, 1u);
+                    *err = 1u;
             }
         }
     }
@@ -469,7 +469,7 @@ __global__ __launch_bounds__(kBlock) void k_phase3_long(const int64_t *__restric
             if (bc > 0)
                 agg_out[v] = ba;
             else
-                atomicOr(err, 1u);
+                *err = 1u;
         }
         __syncthreads();
     };
@@ -529,7 +529,7 @@ __device__ __forceinline__ uint32_t coop_min_label(const int32_t *__restrict__ c
 // One group of L lanes per row of the wavefront's segment of io.wl_in (the
 // unaggregated vertices), K chunks of L column indices loaded before their
 // labels are gathered; rows longer than 32 * L go to the whole wavefront.
-// A vertex with no aggregated neighbour sets bit 1 of *err.
+// A vertex with no aggregated neighbour sets *err (host-pinned: a plain store).
 template <int L>
 __global__ __launch_bounds__(kBlock) void k_join_min(const int64_t *__restrict__ row_ptr,
                                                      const int32_t *__restrict__ col,
@@ -581,7 +581,7 @@ __global__ __launch_bounds__(kBlock) void k_join_min(const int64_t *__restrict__
         m = group_min<L>(m);
         if (valid && sub == 0) {
             if (m == 0xFFFFFFFFu)
-                atomicOr(err, 2u);
+                *err = 2u;
             else
                 agg_out[v] = (int32_t)m;
         }

@@ -57,7 +57,8 @@ __global__ __launch_bounds__(kBlock) void k_tile_count(P pred, int64_t n,
 // Exclusive scan of blocksum[0..nb) in place; the total goes to
 // blocksum[nb] and *d_count.  One workgroup, chunks of kBlock with a carry.
 __global__ __launch_bounds__(kBlock) void k_scan_tiles(uint32_t *__restrict__ blocksum, int64_t nb,
-                                                       uint32_t *__restrict__ d_count) {
+                                                       uint32_t *__restrict__ d_count,
+                                                       uint32_t *__restrict__ h_count) {
     __shared__ uint32_t wsum[kWaves];
     __shared__ uint32_t carry_s;
     if (threadIdx.x == 0) carry_s = 0;
@@ -84,6 +85,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_tiles(uint32_t *__restrict__ bl
     if (threadIdx.x == 0) {
         blocksum[nb] = carry_s;
         *d_count = carry_s;
+        if (h_count) *h_count = carry_s;
     }
 }
 
@@ -143,12 +145,14 @@ __global__ __launch_bounds__(kBlock) void k_tile_count_fill(P pred, int64_t n,
 
 // k_tile_scatter with its own scan: workgroup b sums the counts of tiles
 // 0 .. b-1 itself (blocksum holds every tile's count, as k_tile_count wrote
-// it), and the last workgroup writes the total to *d_count.
+// it), and the last workgroup writes the total to *d_count, and to *h_count
+// (host-pinned) unless that is null.
 template <class P>
 __global__ __launch_bounds__(kBlock) void k_scan_scatter(P pred, int64_t n,
                                                          const uint32_t *__restrict__ blocksum,
                                                          int32_t *__restrict__ out,
-                                                         uint32_t *__restrict__ d_count) {
+                                                         uint32_t *__restrict__ d_count,
+                                                         uint32_t *__restrict__ h_count) {
     __shared__ uint32_t wcount[kItems][kWaves];
     __shared__ uint32_t red[kWaves];
     const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x >> 6);
@@ -177,19 +181,22 @@ __global__ __launch_bounds__(kBlock) void k_scan_scatter(P pred, int64_t n,
             out[before + (uint32_t)__popcll(masks[j] & lanes_below(lane))] = (int32_t)i;
         for (int w = 0; w < kWaves; w++) run += wcount[j][w];
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *d_count = run;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        *d_count = run;
+        if (h_count) *h_count = run;
+    }
 }
 
 template <class P>
 hipError_t scatter_counted(P pred, int64_t n, int32_t *out, uint32_t *d_count,
-                           uint32_t *blocksum, hipStream_t s) {
+                           uint32_t *blocksum, uint32_t *h_count, hipStream_t s) {
     const int64_t nb = compact_blocks(n);
     if (nb > 0 && nb <= kOnePassTiles) {
         hipLaunchKernelGGL(k_scan_scatter<P>, dim3((unsigned)nb), dim3(kBlock), 0, s, pred, n,
-                           (const uint32_t *)blocksum, out, d_count);
+                           (const uint32_t *)blocksum, out, d_count, h_count);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kBlock), 0, s, blocksum, nb, d_count);
+    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kBlock), 0, s, blocksum, nb, d_count, h_count);
     if (nb > 0) {
         hipLaunchKernelGGL(k_tile_scatter<P>, dim3((unsigned)nb), dim3(kBlock), 0, s, pred, n,
                            (const uint32_t *)blocksum, out);
@@ -205,7 +212,8 @@ hipError_t compact(P pred, int64_t n, int32_t *out, uint32_t *d_count, uint32_t 
         hipLaunchKernelGGL(k_tile_count<P>, dim3((unsigned)nb), dim3(kBlock), 0, s, pred, n,
                            blocksum);
     }
-    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kBlock), 0, s, blocksum, nb, d_count);
+    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kBlock), 0, s, blocksum, nb, d_count,
+                       (uint32_t *)nullptr);
     if (nb > 0) {
         hipLaunchKernelGGL(k_tile_scatter<P>, dim3((unsigned)nb), dim3(kBlock), 0, s, pred, n,
                            blocksum, out);
@@ -232,13 +240,15 @@ hipError_t count_in_with_fills(const uint32_t *T, int64_t n, const FillSpans &f,
 }
 
 hipError_t scatter_counted_u32_eq(const uint32_t *a, uint32_t value, int64_t n, int32_t *out,
-                                  uint32_t *d_count, uint32_t *blocksum, hipStream_t s) {
-    return scatter_counted(PredU32Eq{a, value}, n, out, d_count, blocksum, s);
+                                  uint32_t *d_count, uint32_t *blocksum, hipStream_t s,
+                                  uint32_t *h_count) {
+    return scatter_counted(PredU32Eq{a, value}, n, out, d_count, blocksum, h_count, s);
 }
 
 hipError_t scatter_counted_u8_nz(const uint8_t *a8, int64_t n, int32_t *out, uint32_t *d_count,
-                                 uint32_t *blocksum, hipStream_t s) {
-    return scatter_counted(PredU8Nz{a8}, n, out, d_count, blocksum, s);
+                                 uint32_t *blocksum, hipStream_t s,
+                                 uint32_t *h_count) {
+    return scatter_counted(PredU8Nz{a8}, n, out, d_count, blocksum, h_count, s);
 }
 
 hipError_t count_u8_nz(const uint8_t *a8, int64_t n, uint32_t *blocksum, hipStream_t s) {
@@ -402,7 +412,8 @@ __global__ __launch_bounds__(kOneScanThreads) void k_scan_one_u32(const uint32_t
 }
 
 hipError_t launch_scan_tiles(uint32_t *blocksum, int64_t nb, uint32_t *d_total, hipStream_t s) {
-    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kBlock), 0, s, blocksum, nb, d_total);
+    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kBlock), 0, s, blocksum, nb, d_total,
+                       (uint32_t *)nullptr);
     return hipGetLastError();
 }
 

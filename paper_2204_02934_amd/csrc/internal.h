@@ -519,10 +519,12 @@ hipError_t count_in_with_fills(const uint32_t *T, int64_t n, const FillSpans &f,
 // out = the indices i with a[i] == value (or a8[i] != 0), in increasing
 // order, *d_count = how many.  One launch up to kOnePassTiles tiles (each
 // workgroup sums the counts of the tiles before it), else scan and scatter.
+// (h_count: host-pinned copy of the count, or null)
 hipError_t scatter_counted_u32_eq(const uint32_t *a, uint32_t value, int64_t n, int32_t *out,
-                                  uint32_t *d_count, uint32_t *blocksum, hipStream_t s);
+                                  uint32_t *d_count, uint32_t *blocksum, hipStream_t s,
+                                  uint32_t *h_count = nullptr);
 hipError_t scatter_counted_u8_nz(const uint8_t *a8, int64_t n, int32_t *out, uint32_t *d_count,
-                                 uint32_t *blocksum, hipStream_t s);
+                                 uint32_t *blocksum, hipStream_t s, uint32_t *h_count = nullptr);
 // Per-tile counts of a8[i] != 0 into blocksum (plain stores, every tile).
 hipError_t count_u8_nz(const uint8_t *a8, int64_t n, uint32_t *blocksum, hipStream_t s);
 hipError_t compact_u32_eq(const uint32_t *a, uint32_t value, int64_t n, int32_t *out,
