@@ -589,11 +589,10 @@ __device__ __forceinline__ uint32_t sweep_decide(const int64_t *__restrict__ row
                                                  uint32_t *__restrict__ T,
                                                  const uint32_t *__restrict__ M,
                                                  const TupleParams &next, const SegIO &io,
-                                                 const Seg &sg) {
+                                                 const Seg &sg, uint32_t kept = 0) {
     constexpr int G = 64 / L;
     const int lane = (int)(threadIdx.x & 63u);
     const int sub = lane & (L - 1);
-    uint32_t kept = 0;
     unsigned long long dsum = 0;
     // The rows of step i + 1 are loaded while step i's gathers are in flight
     // (as in sweep_column).
@@ -1480,6 +1479,66 @@ __global__ __launch_bounds__(kBlock) void k_col_round_rw(const int64_t *__restri
     col_round<L, true, true>(row_ptr, col, T, M, a, r);
 }
 
+// Decide Set where most rows are settled by their own M and T (round 0: a row
+// whose M differs from its tuple stays undecided): every lane looks at a vertex
+// of its own, kAhead of them at once, and only the rows that have to be read go,
+// through a list in LDS, to the sweep.  (The survivors of a segment are then in
+// no particular order.)  Staged rows, and rows of several lanes, each held a step
+// of the wavefront up: 27-point 100^3 24 us, elasticity 60^3 25 us, now 10 each.
+// With one lane a row the sweep looks at 64 rows a step anyhow (Chung-Lu 4M 75 us
+// either way, 512 subdomains 260).
+constexpr int kAhead = 4, kToRead = 512;
+
+template <int L>
+__device__ __forceinline__ uint32_t decide_few(const int64_t *__restrict__ row_ptr,
+                                               const int32_t *__restrict__ col,
+                                               uint32_t *__restrict__ T,
+                                               const uint32_t *__restrict__ M,
+                                               const TupleParams &next, const SegIO &io,
+                                               const Seg &sg) {
+    // (slots past a list's end are loaded and not used)
+    __shared__ int32_t to_read[kBlock / 64][kToRead + 64];
+    int32_t *list = to_read[threadIdx.x >> 6];
+    const int lane = (int)(threadIdx.x & 63u);
+    uint32_t kept = 0, count = 0;
+    for (int64_t i0 = 0; i0 < sg.count; i0 += 64 * kAhead) {
+        int32_t v[kAhead];
+        uint32_t t[kAhead], m[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; k++) {
+            const int64_t i = min(i0 + 64 * k + lane, sg.count - 1);
+            v[k] = io.wl_in ? io.wl_in[sg.base + i] : (int32_t)(sg.base + i);
+        }
+#pragma unroll
+        for (int k = 0; k < kAhead; k++) {
+            t[k] = T[v[k]];
+            m[k] = M[v[k]];
+        }
+#pragma unroll
+        for (int k = 0; k < kAhead; k++) {
+            const bool ok = i0 + 64 * k + lane < sg.count;
+            const bool read = ok && (m[k] == t[k] || m[k] == kOut);
+            const uint64_t mask = __ballot(read);
+            if (read) list[count + (uint32_t)__popcll(mask & lanes_below(lane))] = v[k];
+            count += (uint32_t)__popcll(mask);
+            const bool keep = ok && !read;
+            if (keep) T[v[k]] = make_tuple(next, (uint32_t)v[k]);
+            seg_append(io, sg, keep, v[k], kept);
+        }
+        if (count > kToRead - 64 * kAhead || i0 + 64 * kAhead >= sg.count) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            SegIO rows = io;
+            rows.wl_in = list - sg.base;
+            kept = sweep_decide<L, kRows, kChunks<L>>(row_ptr, col, T, M, next, rows,
+                                                      Seg{sg.base, (int64_t)count}, kept);
+            count = 0;
+        }
+    }
+    return kept;
+}
+
 template <int L>
 __global__ __launch_bounds__(kBlock) void k_dec_round(const int64_t *__restrict__ row_ptr,
                                                       const int32_t *__restrict__ col,
@@ -1491,6 +1550,22 @@ __global__ __launch_bounds__(kBlock) void k_dec_round(const int64_t *__restrict_
     const int64_t w = wave_id();
     const Seg sg = seg_of(io, w);
     const uint32_t kept = any_decide<L>(row_ptr, col, T, M, next, io, sg);
+    seg_finish(io, w, kept);
+}
+
+// Round 0 (not in accounting runs, which sum the lengths of all rows); L lanes
+// for each row that has to be read.
+template <int L>
+__global__ __launch_bounds__(kBlock) void k_dec_round0(const int64_t *__restrict__ row_ptr,
+                                                       const int32_t *__restrict__ col,
+                                                       uint32_t *__restrict__ T,
+                                                       const uint32_t *__restrict__ M,
+                                                       RoundsArgs a) {
+    const SegIO io = round_dec_io(a, 0);
+    const TupleParams next{xs64star((a.seed << 32) ^ 1ull), a.pmask, a.b, a.batch};
+    const int64_t w = wave_id();
+    const Seg sg = seg_of(io, w);
+    const uint32_t kept = decide_few<L>(row_ptr, col, T, M, next, io, sg);
     seg_finish(io, w, kept);
 }
 
@@ -2415,6 +2490,20 @@ hipError_t launch_col_round(int lanes, int blocks, const int64_t *row_ptr, const
 hipError_t launch_dec_round(int lanes, int blocks, const int64_t *row_ptr, const int32_t *col,
                             uint32_t *T, const uint32_t *M, const RoundsArgs &a, int r,
                             hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    // (k_dec_round0: not with one or two lanes a row, see decide_few)
+    if (r == 0 && !a.dsplit && !a.abl && lanes != 1 && lanes != 2) {
+        const int few = lanes == kStagedLanes || lanes <= 0 ? 4 : std::min(lanes, 16);
+        auto go = [&](auto kernel) {
+            if (e0)
+                hipExtLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, s, e0, e1, 0, row_ptr,
+                                      col, T, M, a);
+            else
+                hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, s, row_ptr, col, T, M, a);
+            return hipGetLastError();
+        };
+        if (few == 4) return go(k_dec_round0<4>);
+        return few == 8 ? go(k_dec_round0<8>) : go(k_dec_round0<16>);
+    }
     MIS2_LANE_DISPATCH_TIMED(lanes, k_dec_round, dim3(blocks), dim3(kBlock), s, e0, e1, row_ptr,
                              col, T, M, a, r);
     if (a.dsplit)
