@@ -366,6 +366,15 @@ FillSpans round_fills(const mis2_graph *g, const Workspace &ws, bool masked) {
 // LDS, which pays while rows are dense and costs 1-2 us per launch once they
 // are sparse.
 constexpr int kLateLanes = 4;
+
+// A compacting round of a graph whose T outgrows an XCD's L2 asks a bit per
+// vertex (n / 8 bytes, which stay in it) which neighbours are OUT before it
+// gathers the others' tuples, while |worklist1| * kLiveShare >= n; later rounds
+// are launch and latency bound and the bit is one more step of their chain.
+// Measured on gfx950, Chung-Lu 4M vertices (18 of 100 neighbours live in
+// round 2, 7 in round 4): rounds 2 to 6 662, 350, 292, 184, 115 -> 500, 283,
+// 204, 131, 82 us, the bits 5 us each; with |worklist1| near n / 60 22 -> 29 us.
+constexpr uint64_t kLiveShare = 16;
 constexpr uint64_t kLateShare = 4;
 
 int run_rounds(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Workspace &ws,
@@ -480,6 +489,14 @@ int run_rounds(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Workspac
             if (can_compact && longs > 0) {
                 if (cstart < 0) cstart = round;
                 mode = round == cstart ? 1 : 2;
+                // the live bits take the place of round 1's marks, read for
+                // the last time by its Decide Set
+                a.live = nullptr;
+                if (ws.near && g->n >= kGenMinN &&
+                    (seen < 0 || (uint64_t)live * kLiveShare >= (uint64_t)g->n)) {
+                    a.live = (const uint32_t *)ws.near;
+                    HIP_TRY(ctx, launch_live_bits(g->n, ws.T, (uint32_t *)ws.near, s));
+                }
             }
             // the staged sweeps hand the sparse rounds to 4-lane kernels
             // (same segments, same results), whose per-launch cost is lower

@@ -117,7 +117,8 @@ constexpr int kMaxWaves = kMaxBlocks * (kBlock / 64);
 struct Workspace {
     uint32_t *T = nullptr;        // [n] packed row status tuples
     uint32_t *M = nullptr;        // [n] radius-1 minima
-    uint8_t *near = nullptr;      // [n] 1: within distance 2 of an IN vertex of round 0 (k_push_near)
+    uint8_t *near = nullptr;      // [n] 1: within distance 2 of an IN vertex of round 0 (k_push_near);
+                                  // after round 1 the live bits (k_live_bits)
     int32_t *wl1[2] = {};         // [n] undecided vertices (per-wave segments), double buffered
     int32_t *wl2[2] = {};         // [n] vertices without an IN neighbour, double buffered
     uint32_t *cnt1[2] = {};       // [kMaxWaves] per-wave sizes of wl1[i]
@@ -232,6 +233,8 @@ struct SegIO {
     // OUT keeps M OUT, any other has no IN neighbour, so all its
     // neighbours' tuples are round 1's function of the id.
     int gen0;
+    // Refresh Column's compacting rounds: live bits of T (gather_live), or null.
+    const uint32_t *live;
     TupleParams t0;
     // Decide Set of round 0: no vertex is IN yet, so no M is OUT and a row
     // whose own M differs from its tuple stays undecided without reading its
@@ -277,6 +280,7 @@ struct RoundsArgs {
     int abl;         // ablation kernels only: kAblFixed | kAblXorshift
     int gen0;        // 1: rounds 0 and 1 of Refresh Column may compute the tuples they gather
     uint8_t *near;   // Workspace::near
+    const uint32_t *live;  // [ceil(n/32)] Refresh Column's live bits (launch_live_bits), or null
     int64_t n, seg, S;
     int64_t nnz;
     uint64_t seed, pmask;
@@ -452,6 +456,8 @@ hipError_t launch_push_in(int64_t n, const int64_t *row_ptr, const int32_t *col,
 // vertices of round 0 and their neighbours) and on its neighbours.
 hipError_t launch_push_near(int64_t n, const int64_t *row_ptr, const int32_t *col,
                             const uint32_t *M, uint8_t *near, hipStream_t s);
+// Bit v of live clear only where T[v] is OUT.  Writes ceil(n / 64) * 2 words.
+hipError_t launch_live_bits(int64_t n, const uint32_t *T, uint32_t *live, hipStream_t s);
 hipError_t launch_dec_round(int lanes, int blocks, const int64_t *row_ptr, const int32_t *col,
                             uint32_t *T, const uint32_t *M, const RoundsArgs &a, int r,
                             hipStream_t s, hipEvent_t e0, hipEvent_t e1);

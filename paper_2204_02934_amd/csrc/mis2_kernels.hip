@@ -216,6 +216,23 @@ __device__ __forceinline__ int64_t heavy_threshold() {
 }
 constexpr int kCoopLoads = 8;  // loads per lane per cooperative step
 
+// t[k] = T[x[k]], read only where the live bit is set: T is OUT elsewhere.  The
+// dead entries' lanes all read T[0], one line.
+template <int K>
+__device__ __forceinline__ void gather_live(const uint32_t *__restrict__ T,
+                                            const uint32_t *__restrict__ live,
+                                            const int32_t (&x)[K], uint32_t (&t)[K]) {
+    uint32_t w[K];
+#pragma unroll
+    for (int k = 0; k < K; k++) w[k] = live[(uint32_t)x[k] >> 5];
+#pragma unroll
+    for (int k = 0; k < K; k++) w[k] = (w[k] >> (x[k] & 31)) & 1u;
+#pragma unroll
+    for (int k = 0; k < K; k++) t[k] = T[w[k] ? x[k] : 0];
+#pragma unroll
+    for (int k = 0; k < K; k++) t[k] = w[k] ? t[k] : kOut;
+}
+
 // Minimum of T over the column indices [s, e), by the whole wavefront.
 // With out != null the indices whose T is not OUT are also written, in
 // order, to out[s ...] (out may be the array read: every store lands at or
@@ -239,6 +256,8 @@ __device__ __forceinline__ uint32_t coop_min_T(const int32_t *col, const uint32_
         if (gio && gio->gen0) {
 #pragma unroll
             for (int k = 0; k < kCoopLoads; k++) t[k] = make_tuple(gio->t0, (uint32_t)x[k]);
+        } else if (gio && gio->live) {
+            gather_live<kCoopLoads>(T, gio->live, x, t);
         } else {
 #pragma unroll
             for (int k = 0; k < kCoopLoads; k++) t[k] = T[x[k]];
@@ -531,6 +550,9 @@ __device__ __forceinline__ uint32_t sweep_column(const int64_t *__restrict__ row
                 for (int u = 0; u < U; u++)
 #pragma unroll
                     for (int k = 0; k < K; k++) t[u][k] = make_tuple(io.t0, (uint32_t)x[u][k]);
+            } else if ((RD || WR) && io.live) {
+#pragma unroll
+                for (int u = 0; u < U; u++) gather_live<K>(T, io.live, x[u], t[u]);
             } else {
 #pragma unroll
                 for (int u = 0; u < U; u++)
@@ -1424,6 +1446,7 @@ __device__ __forceinline__ void col_round(const int64_t *__restrict__ row_ptr,
         io.ccol_out = a.colc;
         io.lenc_out = a.lenc;
     }
+    if (RD || WR) io.live = a.live;
     const int64_t w = wave_id();
     const Seg sg = seg_of(io, w);
     uint32_t kept;
@@ -2131,6 +2154,28 @@ __global__ __launch_bounds__(kBlock) void k_push_near(int64_t n, const int64_t *
     }
 }
 
+// The live bits of Refresh Column: bit v clear where T[v] is OUT, which it then
+// stays.  A wavefront reads 512 tuples at a time and writes their 64 bytes.
+__global__ __launch_bounds__(kBlock) void k_live_bits(int64_t n, const uint32_t *__restrict__ T,
+                                                      unsigned long long *__restrict__ live) {
+    constexpr int K = 8;
+    const int lane = (int)(threadIdx.x & 63u);
+    const int64_t words = (n + 63) / 64;
+    for (int64_t w0 = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * K; w0 < words;
+         w0 += (int64_t)gridDim.x * (kBlock / 64) * K) {
+        uint32_t t[K];
+#pragma unroll
+        for (int k = 0; k < K; k++) t[k] = T[min((w0 + k) * 64 + lane, n - 1)];
+        uint64_t mine = 0;
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            const uint64_t b = __ballot((w0 + k) * 64 + lane < n && t[k] != kOut);
+            if (lane == k) mine = b;
+        }
+        if (lane < K && w0 + lane < words) live[w0 + lane] = mine;
+    }
+}
+
 // status[v] = (T_v == IN); the tile's IN count goes to blocksum[tile] (tiles
 // of kCountTile vertices, one per workgroup).
 constexpr int kCountTile = kBlock * 8;
@@ -2460,6 +2505,13 @@ hipError_t launch_push_near(int64_t n, const int64_t *row_ptr, const int32_t *co
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_push_near, dim3(grid_for(n, kBlock, 8192)), dim3(kBlock), 0, s, n,
                        row_ptr, col, M, near);
+    return hipGetLastError();
+}
+
+hipError_t launch_live_bits(int64_t n, const uint32_t *T, uint32_t *live, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_live_bits, dim3(grid_for(n, 8 * kBlock, 2048)), dim3(kBlock), 0, s, n, T,
+                       (unsigned long long *)live);
     return hipGetLastError();
 }
 
