@@ -373,7 +373,8 @@ constexpr int kLateLanes = 4;
 // are launch and latency bound and the bit is one more step of their chain.
 // Measured on gfx950, Chung-Lu 4M vertices (18 of 100 neighbours live in
 // round 2, 7 in round 4): rounds 2 to 6 662, 350, 292, 184, 115 -> 500, 283,
-// 204, 131, 82 us, the bits 5 us each; with |worklist1| near n / 60 22 -> 29 us.
+// 204, 131, 82 us (with flat_min since, 469, 251, 175, 114, 65), the bits 5 us
+// each; with |worklist1| near n / 60 22 -> 29 us.
 constexpr uint64_t kLiveShare = 16;
 constexpr uint64_t kLateShare = 4;
 

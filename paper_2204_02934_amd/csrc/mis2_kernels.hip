@@ -361,16 +361,21 @@ __device__ __forceinline__ int flat_row(const FlatLds &sh, int nrows, uint32_t f
     return lo;
 }
 
-// The least tuple, computed, among this lane's row's entries [s, s + len), for a
-// step of one-lane rows of very different lengths: their entries in one flat
-// range, dealt out evenly, 4 at a time.  (A lane hashing its own row takes as
-// many steps as the longest of 64 rows: with 9 entries on average and some rows
-// of 32, three of four hashes were padding.)  All lanes must call it.
-__device__ __forceinline__ uint32_t flat_hash(FlatLds &sh, const int32_t *__restrict__ col,
-                                              const TupleParams &t0, int64_t s, int64_t len) {
+// The least tuple among this lane's row's entries, the len column indices at
+// row, for a step of one-lane rows of very different lengths: their entries in
+// one flat range, dealt out evenly, J at a time; get(x, t) fetches or computes
+// the tuples of J neighbours.  (A lane that walks its own row takes as many
+// steps as the longest of 64 rows: with 9 entries on average and some rows of
+// 32, three of four steps were padding.)  4 at a time leave the compacting
+// sweeps 5 wavefronts per SIMD, 8 leave 4: Chung-Lu 4M vertices, all compacting
+// rounds, one lane per row 2.09, 8 at a time 1.89, 4 at a time 1.85 ms.  All lanes must call it.  any: J
+// readable column indices, for the lanes past the end.
+template <int J, class GET>
+__device__ __forceinline__ uint32_t flat_min(FlatLds &sh, const int32_t *any, const int32_t *row,
+                                             int64_t len, GET get) {
     const int lane = (int)(threadIdx.x & 63u);
     uint32_t total;
-    const int me = flat_table(sh, s, len, true, total);
+    const int me = flat_table(sh, (int64_t)(uintptr_t)row, len, true, total);
     const int nrows = (int)__popcll(__ballot(me >= 0));
     if (me >= 0) sh.acc[me] = kOut;
     wave_lds_sync();
@@ -378,31 +383,32 @@ __device__ __forceinline__ uint32_t flat_hash(FlatLds &sh, const int32_t *__rest
     const uint32_t f0 = min(per * (uint32_t)lane, total), f1 = min(f0 + per, total);
     int r = f0 < f1 ? flat_row(sh, nrows, f0) : 0;
     uint32_t next = sh.off[r + 1];
-    int64_t base = sh.start[r] - (int64_t)sh.off[r];
+    int64_t base = sh.start[r] - 4 * (int64_t)sh.off[r];
     uint32_t part = kOut;
-    for (uint32_t j0 = 0; j0 < per; j0 += 4) {
-        int32_t x[4];
-        int rr[4];
+    for (uint32_t j0 = 0; j0 < per; j0 += J) {
+        int32_t x[J];
+        int rr[J];
 #pragma unroll
-        for (int j = 0; j < 4; j++) {
+        for (int j = 0; j < J; j++) {
             const uint32_t f = f0 + j0 + j;
             if (f < f1 && f >= next) {  // (no row of the table is empty)
                 r++;
                 next = sh.off[r + 1];
-                base = sh.start[r] - (int64_t)sh.off[r];
+                base = sh.start[r] - 4 * (int64_t)sh.off[r];
             }
             rr[j] = r;
-            x[j] = col[f < f1 ? base + (int64_t)f : 0];
+            const int64_t at = f < f1 ? base + 4 * (int64_t)f : (int64_t)(uintptr_t)any;
+            x[j] = *(const __attribute__((address_space(1))) int32_t *)(uintptr_t)at;
         }
-        uint32_t t[4];
+        uint32_t t[J];
+        get(x, t);
 #pragma unroll
-        for (int j = 0; j < 4; j++) t[j] = make_tuple(t0, (uint32_t)x[j]);
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
+        for (int j = 0; j < J; j++) {
             const uint32_t f = f0 + j0 + j;
             if (f < f1) {
                 part = min(part, t[j]);
-                if (f + 1 == f1 || (j < 3 ? rr[j < 3 ? j + 1 : 3] != rr[j] : f + 1 >= next)) {
+                if (f + 1 == f1 ||
+                    (j < J - 1 ? rr[j < J - 1 ? j + 1 : j] != rr[j] : f + 1 >= next)) {
                     atomicMin(&sh.acc[rr[j]], part);
                     part = kOut;
                 }
@@ -437,7 +443,7 @@ __device__ __forceinline__ uint32_t sweep_column(const int64_t *__restrict__ row
                                                  uint32_t *__restrict__ M, const SegIO &io,
                                                  const Seg &sg, FlatLds *sh = nullptr) {
     constexpr int G = 64 / L;  // rows per wavefront per unrolled slot
-    // rounds that compute the tuples, one lane per row: flat_hash instead of
+    // rounds that compute the tuples, one lane per row: flat_min instead of
     // lanes of their own where rows need more than one batch of loads
     const bool flat = L == 1 && sh && io.gen0;
     const int lane = (int)(threadIdx.x & 63u);
@@ -516,7 +522,32 @@ __device__ __forceinline__ uint32_t sweep_column(const int64_t *__restrict__ row
         int64_t steps = wave_max_len<U>(s, e);
         if constexpr (L == 1) {
             if (flat && steps > K) {
-                m[0] = min(m[0], flat_hash(*sh, col, io.t0, s[0], e[0] - s[0]));
+                m[0] = min(m[0], flat_min<4>(*sh, col, col + s[0], e[0] - s[0],
+                                             [&](const int32_t(&x)[4], uint32_t(&t)[4]) {
+#pragma unroll
+                                                 for (int j = 0; j < 4; j++)
+                                                     t[j] = make_tuple(io.t0, (uint32_t)x[j]);
+                                             }));
+                steps = 0;
+            }
+            if ((RD || WR) && sh && steps > K) {
+                if (!fetched) {
+                    sn[0] = row_ptr[vn[0]];
+                    en[0] = row_ptr[vn[0] + 1];
+                    mn[0] = T[vn[0]];
+                    lcn[0] = RD ? lenc[vn[0]] : 0;
+                    fetched = true;
+                }
+                const int32_t *row = (RD && cf[0] ? colc : col) + s[0];
+                m[0] = min(m[0], flat_min<4>(*sh, col, row, e[0] - s[0],
+                                             [&](const int32_t(&x)[4], uint32_t(&t)[4]) {
+                                                 if (io.live) {
+                                                     gather_live<4>(T, io.live, x, t);
+                                                     return;
+                                                 }
+#pragma unroll
+                                                 for (int j = 0; j < 4; j++) t[j] = T[x[j]];
+                                             }));
                 steps = 0;
             }
         }
@@ -1450,7 +1481,7 @@ __device__ __forceinline__ void col_round(const int64_t *__restrict__ row_ptr,
     const int64_t w = wave_id();
     const Seg sg = seg_of(io, w);
     uint32_t kept;
-    if constexpr (GEN && L == 1) {
+    if constexpr ((GEN || RD || WR) && L == 1) {
         __shared__ FlatLds sh[kBlock / 64];
         kept = sweep_column<L, kRows, kChunks<L>, RD, WR>(row_ptr, col, T, M, io, sg,
                                                           &sh[threadIdx.x >> 6]);
@@ -1471,7 +1502,7 @@ __global__ __launch_bounds__(kBlock) void k_col_round(const int64_t *__restrict_
 
 // Rounds 0 and 1 where the neighbours' tuples are computed and that is exact
 // (unmasked, one graph; round 1 after k_push_in).  One lane per row: with
-// flat_hash, Chung-Lu 4M vertices 304 -> 189 us a round.  The other runs' first
+// flat_min, Chung-Lu 4M vertices 304 -> 189 us a round.  The other runs' first
 // rounds take k_col_round, with fewer registers.
 template <int L>
 __global__ __launch_bounds__(kBlock) void k_col_round0(const int64_t *__restrict__ row_ptr,
