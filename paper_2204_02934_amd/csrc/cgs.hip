@@ -2,11 +2,10 @@
 //
 // Setup colours a graph (the coarse graph of an aggregation, or the graph
 // itself for point multicolor Gauss-Seidel) and orders the rows by colour,
-// then by cluster, then by row id.  Apply runs, for each colour in turn, one
-// wavefront per cluster: the wave updates its cluster's rows one after the
-// other.  Clusters of one colour share no edge, so no wave reads a value
-// another wave of the same launch writes, and the result is that of the
-// sequential sweep in the same order.
+// then by cluster, then by row id.  Apply runs, for each colour in turn, every
+// cluster's rows one after the other, the clusters side by side.  Clusters of
+// one colour share no edge, so none reads a value another one of the same launch
+// writes, and the result is that of the sequential sweep in the same order.
 //
 // Colouring (the paper takes it from other work): Jones-Plassmann with fixed
 // priorities, the packed tuple of h(seed, 0, v) (Sections V-A, V-C): every

@@ -17,9 +17,10 @@
 // set per lane group (k_coarse_rows_group, several rows per wavefront where
 // aggregates are small), a 1024-slot set per wavefront (only where an LDS
 // bitmap cannot hold every coarse id), one workgroup, and for rows of more than
-// kGiantCand candidates a bitmap slot that the whole grid fills.  The first two rank the distinct ids; a workgroup sweeps the
-// coarse ids with an LDS bitmap (of as many bits as there are coarse ids, in
-// windows of 32*kBitWords where that is more), which emits them in increasing
+// kGiantCand candidates a bitmap slot that the whole grid fills.  The first two
+// rank the distinct ids; a workgroup sweeps the coarse ids with an LDS bitmap
+// (of as many bits as there are coarse ids, in windows of 32*kBitWords where
+// that is more), which emits them in increasing
 // order and, after the first window, visits only the range the row's
 // candidates span.  Every path deals the members' entries out evenly over its
 // lanes.  The first three write their rows to a spare buffer while they count
