@@ -55,37 +55,51 @@ __global__ __launch_bounds__(kBlock) void k_tile_count(P pred, int64_t n,
 }
 
 // Exclusive scan of blocksum[0..nb) in place; the total goes to
-// blocksum[nb] and *d_count.  One workgroup, chunks of kBlock with a carry.
+// blocksum[nb] and *d_count.  One workgroup, kScanRows * kBlock values at a time
+// with a carry (kBlock at a time, 8638 tiles took 34 trips to memory and 25 us;
+// now 14).
+constexpr int kScanRows = 8;
 __global__ __launch_bounds__(kBlock) void k_scan_tiles(uint32_t *__restrict__ blocksum, int64_t nb,
                                                        uint32_t *__restrict__ d_count,
                                                        uint32_t *__restrict__ h_count) {
-    __shared__ uint32_t wsum[kWaves];
-    __shared__ uint32_t carry_s;
-    if (threadIdx.x == 0) carry_s = 0;
-    __syncthreads();
+    __shared__ uint32_t wsum[kScanRows][kWaves];
     const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x >> 6);
-    for (int64_t c0 = 0; c0 < nb; c0 += kBlock) {
-        const int64_t i = c0 + threadIdx.x;
-        const uint32_t x = i < nb ? blocksum[i] : 0u;
-        // inclusive scan inside the wavefront
-        uint32_t incl = x;
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t y = (uint32_t)__shfl_up((int)incl, off, 64);
-            if (lane >= off) incl += y;
+    uint32_t carry = 0;  // the same in every thread
+    for (int64_t c0 = 0; c0 < nb; c0 += kScanRows * kBlock) {
+        uint32_t x[kScanRows], incl[kScanRows];
+#pragma unroll
+        for (int j = 0; j < kScanRows; j++) {
+            const int64_t i = c0 + j * kBlock + threadIdx.x;
+            x[j] = blocksum[min(i, nb - 1)];
+            if (i >= nb) x[j] = 0u;
         }
-        if (lane == 63) wsum[wave] = incl;
+        // inclusive scans inside the wavefront
+#pragma unroll
+        for (int j = 0; j < kScanRows; j++) {
+            incl[j] = x[j];
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t y = (uint32_t)__shfl_up((int)incl[j], off, 64);
+                if (lane >= off) incl[j] += y;
+            }
+            if (lane == 63) wsum[j][wave] = incl[j];
+        }
         __syncthreads();
-        uint32_t before = carry_s;
-        for (int w = 0; w < wave; w++) before += wsum[w];
-        if (i < nb) blocksum[i] = before + incl - x;
-        __syncthreads();
-        if (threadIdx.x == kBlock - 1) carry_s = before + incl;
-        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kScanRows; j++) {
+            uint32_t before = carry;
+            for (int w = 0; w < kWaves; w++) {
+                if (w < wave) before += wsum[j][w];
+                carry += wsum[j][w];
+            }
+            const int64_t i = c0 + j * kBlock + threadIdx.x;
+            if (i < nb) blocksum[i] = before + incl[j] - x[j];
+        }
+        __syncthreads();  // wsum is rewritten
     }
     if (threadIdx.x == 0) {
-        blocksum[nb] = carry_s;
-        *d_count = carry_s;
-        if (h_count) *h_count = carry_s;
+        blocksum[nb] = carry;
+        *d_count = carry;
+        if (h_count) *h_count = carry;
     }
 }
 

@@ -89,7 +89,7 @@ constexpr uint8_t kSpared = 3;   // second part of the spare buffer
 // hundreds of candidates.  Measured, counting and writing together, against one
 // wavefront per row with a set as large as its candidates (and a workgroup's
 // sort past 1024 of them), run twice: 2.5M rows of a 512-subdomain union
-// (level 0: 5 members, 40 candidates) 4.0 -> 0.87 ms; 14 000 rows of 40
+// (level 0: 5 members, 40 candidates) 4.0 -> 0.79 ms; 14 000 rows of 40
 // members and 1000 candidates (27-point 83x71x97) 1.38 -> 0.06 ms.
 // ccnt[a], the ids in increasing order in the spare buffer and cls[a] (class 0
 // or 3); class `over` for a row it leaves to another path.
@@ -107,11 +107,40 @@ __global__ __launch_bounds__(kBlock) void k_coarse_rows_group(
     // each XCD takes one run of the rows of a step (the grid is a multiple of
     // 8): neighbouring rows share columns and labels
     const int64_t blk = (int64_t)(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    for (int64_t a = blk * kGroups + grp; a < n_agg; a += (int64_t)gridDim.x * kGroups) {
-        const int64_t m0 = moff[a], m1 = moff[a + 1];
+    // small groups: the next row's members and their extents load while this row
+    // is gathered and written, and the offsets of the one after it: 873 -> 794 us
+    // for the 2.5M rows above.  (A wavefront per row has one row or two, and the
+    // loads are in its way: 58 -> 65 us.)
+    constexpr bool kAhead = G < 64;
+    const int64_t stride = (int64_t)gridDim.x * kGroups, a0 = blk * kGroups + grp;
+    auto offsets = [&](int64_t a, int64_t &m0, int64_t &m1) {
+        const int64_t ac = min(a, n_agg - 1);
+        m0 = moff[ac];
+        m1 = moff[ac + 1];
+    };
+    auto member = [&](int64_t m0, int64_t m1) {
+        return members[m1 > m0 ? min(m0 + lane, m1 - 1) : 0];
+    };
+    int64_t m0, m1, n0 = 0, n1 = 0, rs0 = 0, d0 = 0;
+    offsets(a0, m0, m1);
+    if (kAhead) {
+        offsets(a0 + stride, n0, n1);
+        const int32_t v = member(m0, m1);
+        rs0 = row_ptr[v];
+        d0 = row_ptr[v + 1] - rs0;
+    }
+    for (int64_t a = a0; a < n_agg; a += stride) {
+        int64_t l0 = 0, l1 = 0;
+        const int32_t vn = kAhead ? member(n0, n1) : 0;
+        if (kAhead) offsets(a + 2 * stride, l0, l1);
         const bool fits = row_gather<G, CAP, LIM, U>(
             S, lane, m0, m1, maxc,
             [&](int64_t i, int64_t &rs, int64_t &d) {
+                if (kAhead && i - m0 < G) {
+                    rs = rs0;
+                    d = d0;
+                    return;
+                }
                 const int32_t v = members[i];
                 rs = row_ptr[v];
                 d = row_ptr[v + 1] - rs;
@@ -121,6 +150,10 @@ __global__ __launch_bounds__(kBlock) void k_coarse_rows_group(
                 const int32_t c = agg[x];
                 return (int64_t)c == a ? -1 : c;
             });
+        if (kAhead) {
+            rs0 = row_ptr[vn];
+            d0 = row_ptr[vn + 1] - rs0;
+        }
         const uint32_t m = S.num;
         int64_t at = m0 * sp.per;
         if (fits && (int64_t)m > (m1 - m0) * sp.per) {
@@ -139,24 +172,53 @@ __global__ __launch_bounds__(kBlock) void k_coarse_rows_group(
             cls[a] = !done ? over : at == m0 * sp.per ? kInPlace : kSpared;
         }
         row_clear(S, lane, m, !fits);
+        if (kAhead) {
+            m0 = n0;
+            m1 = n1;
+            n0 = l0;
+            n1 = l1;
+        } else {
+            offsets(a + stride, m0, m1);
+        }
     }
 }
 
-// The rows in the spare buffer to their place, 16 lanes each.
+// The rows in the spare buffer to their place, 16 lanes each, four rows' loads at
+// once (1.5M rows 191 -> 140 us: three loads in a row of trips to memory).
 __global__ __launch_bounds__(kBlock) void k_copy_rows(int64_t n_agg, const int64_t *__restrict__ moff,
                                                       const int64_t *__restrict__ crow,
                                                       const uint8_t *__restrict__ cls, Spare sp,
                                                       int32_t *__restrict__ ccol) {
+    constexpr int K = 4;
     const int lane = (int)(threadIdx.x & 15u);
-    for (int64_t a = (int64_t)blockIdx.x * (kBlock / 16) + (threadIdx.x >> 4); a < n_agg;
-         a += (int64_t)gridDim.x * (kBlock / 16)) {
-        const int64_t d0 = crow[a], len = crow[a + 1] - d0;
-        const uint8_t k = cls[a];
-        if (len == 0 || (k != kInPlace && k != kSpared)) continue;
-        int64_t s0 = moff[a] * sp.per;
-        if (k == kSpared)
-            s0 = (int64_t)(uint32_t)sp.buf[s0] | (int64_t)((uint64_t)(uint32_t)sp.buf[s0 + 1] << 32);
-        for (int64_t i = lane; i < len; i += 16) ccol[d0 + i] = sp.buf[s0 + i];
+    const int64_t stride = (int64_t)gridDim.x * (kBlock / 16);
+    for (int64_t a0 = (int64_t)blockIdx.x * (kBlock / 16) + (threadIdx.x >> 4); a0 < n_agg;
+         a0 += K * stride) {
+        int64_t d0[K], len[K], s0[K];
+        uint8_t c[K];
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            const int64_t a = min(a0 + k * stride, n_agg - 1);
+            d0[k] = crow[a];
+            len[k] = crow[a + 1] - d0[k];
+            c[k] = cls[a];
+            s0[k] = moff[a] * sp.per;
+        }
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            if (a0 + k * stride >= n_agg || (c[k] != kInPlace && c[k] != kSpared)) len[k] = 0;
+            if (len[k] > 0 && c[k] == kSpared)
+                s0[k] = (int64_t)(uint32_t)sp.buf[s0[k]] |
+                        (int64_t)((uint64_t)(uint32_t)sp.buf[s0[k] + 1] << 32);
+        }
+        int32_t x[K];
+#pragma unroll
+        for (int k = 0; k < K; k++) x[k] = sp.buf[lane < len[k] ? s0[k] + lane : 0];
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            if (lane < len[k]) ccol[d0[k] + lane] = x[k];
+            for (int64_t i = lane + 16; i < len[k]; i += 16) ccol[d0[k] + i] = sp.buf[s0[k] + i];
+        }
     }
 }
 
@@ -899,7 +961,7 @@ hipError_t quotient_graph(const int64_t *row_ptr, const int32_t *col, int64_t n,
     host.word = host_nnz;
     if ((e = exclusive_scan_u32_i64(q.cnt, n_agg, crow, q.part, s, host)) != hipSuccess) return e;
     if (n_agg > 0) {
-        hipLaunchKernelGGL(k_copy_rows, dim3(grid_for(n_agg, kBlock / 16, 8192)), dim3(kBlock), 0,
+        hipLaunchKernelGGL(k_copy_rows, dim3(grid_for(n_agg, kBlock / 16, 2048)), dim3(kBlock), 0,
                            s, n_agg, q.moff, (const int64_t *)crow, (const uint8_t *)q.cls, sp,
                            ccol);
         if (hashed)
