@@ -118,8 +118,11 @@ __global__ __launch_bounds__(kBlock) void k_coarse_rows_group(
         m0 = moff[ac];
         m1 = moff[ac + 1];
     };
+    // (an aggregate without members: vertex 0; members[0] is loaded, but where no
+    // vertex has a label nothing has written it)
     auto member = [&](int64_t m0, int64_t m1) {
-        return members[m1 > m0 ? min(m0 + lane, m1 - 1) : 0];
+        const int32_t v = members[m1 > m0 ? min(m0 + lane, m1 - 1) : 0];
+        return m1 > m0 ? v : 0;
     };
     int64_t m0, m1, n0 = 0, n1 = 0, rs0 = 0, d0 = 0;
     offsets(a0, m0, m1);
