@@ -55,27 +55,29 @@ __global__ __launch_bounds__(kBlock) void k_tile_count(P pred, int64_t n,
 }
 
 // Exclusive scan of blocksum[0..nb) in place; the total goes to
-// blocksum[nb] and *d_count.  One workgroup, kScanRows * kBlock values at a time
-// with a carry (kBlock at a time, 8638 tiles took 34 trips to memory and 25 us;
-// now 14).
-constexpr int kScanRows = 8;
+// blocksum[nb] and *d_count.  One workgroup, ROWS * kBlock values at a time with
+// a carry: 8638 tiles took 34 trips to memory and 25 us one row at a time, eight
+// rows 14.  Few tiles take as many rows as they fill: 192 values 1.9 us with one
+// row and 3.7 with eight, 432 in two rows 2.2, 957 in four 2.7, 1954 in eight 4.1
+// (one row at a time 2.7, 3.8 and 7.1).
+template <int ROWS>
 __global__ __launch_bounds__(kBlock) void k_scan_tiles(uint32_t *__restrict__ blocksum, int64_t nb,
                                                        uint32_t *__restrict__ d_count,
                                                        uint32_t *__restrict__ h_count) {
-    __shared__ uint32_t wsum[kScanRows][kWaves];
+    __shared__ uint32_t wsum[ROWS][kWaves];
     const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x >> 6);
     uint32_t carry = 0;  // the same in every thread
-    for (int64_t c0 = 0; c0 < nb; c0 += kScanRows * kBlock) {
-        uint32_t x[kScanRows], incl[kScanRows];
+    for (int64_t c0 = 0; c0 < nb; c0 += ROWS * kBlock) {
+        uint32_t x[ROWS], incl[ROWS];
 #pragma unroll
-        for (int j = 0; j < kScanRows; j++) {
+        for (int j = 0; j < ROWS; j++) {
             const int64_t i = c0 + j * kBlock + threadIdx.x;
             x[j] = blocksum[min(i, nb - 1)];
             if (i >= nb) x[j] = 0u;
         }
         // inclusive scans inside the wavefront
 #pragma unroll
-        for (int j = 0; j < kScanRows; j++) {
+        for (int j = 0; j < ROWS; j++) {
             incl[j] = x[j];
             for (int off = 1; off < 64; off <<= 1) {
                 const uint32_t y = (uint32_t)__shfl_up((int)incl[j], off, 64);
@@ -85,7 +87,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_tiles(uint32_t *__restrict__ bl
         }
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kScanRows; j++) {
+        for (int j = 0; j < ROWS; j++) {
             uint32_t before = carry;
             for (int w = 0; w < kWaves; w++) {
                 if (w < wave) before += wsum[j][w];
@@ -101,6 +103,17 @@ __global__ __launch_bounds__(kBlock) void k_scan_tiles(uint32_t *__restrict__ bl
         *d_count = carry;
         if (h_count) *h_count = carry;
     }
+}
+
+void scan_tiles(uint32_t *blocksum, int64_t nb, uint32_t *d_count, uint32_t *h_count,
+                hipStream_t s) {
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(kBlock), 0, s, blocksum, nb, d_count, h_count);
+    };
+    if (nb <= kBlock) go(k_scan_tiles<1>);
+    else if (nb <= 2 * kBlock) go(k_scan_tiles<2>);
+    else if (nb <= 4 * kBlock) go(k_scan_tiles<4>);
+    else go(k_scan_tiles<8>);
 }
 
 template <class P>
@@ -210,7 +223,7 @@ hipError_t scatter_counted(P pred, int64_t n, int32_t *out, uint32_t *d_count,
                            (const uint32_t *)blocksum, out, d_count, h_count);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kBlock), 0, s, blocksum, nb, d_count, h_count);
+    scan_tiles(blocksum, nb, d_count, h_count, s);
     if (nb > 0) {
         hipLaunchKernelGGL(k_tile_scatter<P>, dim3((unsigned)nb), dim3(kBlock), 0, s, pred, n,
                            (const uint32_t *)blocksum, out);
@@ -226,8 +239,7 @@ hipError_t compact(P pred, int64_t n, int32_t *out, uint32_t *d_count, uint32_t 
         hipLaunchKernelGGL(k_tile_count<P>, dim3((unsigned)nb), dim3(kBlock), 0, s, pred, n,
                            blocksum);
     }
-    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kBlock), 0, s, blocksum, nb, d_count,
-                       (uint32_t *)nullptr);
+    scan_tiles(blocksum, nb, d_count, nullptr, s);
     if (nb > 0) {
         hipLaunchKernelGGL(k_tile_scatter<P>, dim3((unsigned)nb), dim3(kBlock), 0, s, pred, n,
                            blocksum, out);
@@ -426,8 +438,7 @@ __global__ __launch_bounds__(kOneScanThreads) void k_scan_one_u32(const uint32_t
 }
 
 hipError_t launch_scan_tiles(uint32_t *blocksum, int64_t nb, uint32_t *d_total, hipStream_t s) {
-    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kBlock), 0, s, blocksum, nb, d_total,
-                       (uint32_t *)nullptr);
+    scan_tiles(blocksum, nb, d_total, nullptr, s);
     return hipGetLastError();
 }
 
