@@ -332,9 +332,11 @@ RoundsArgs round_args(const mis2_ctx *ctx, const mis2_graph *g, uint64_t seed,
     return a;
 }
 
-// long_rows: for an unmasked run, out: 1 if round 0 met rows longer than the
-// cooperative threshold, 0 if not, -1 if the run did not say; for a masked run,
-// in: the value of the unmasked run of the same graph.  Refresh Column compacts (launch modes 1 then 2) only when it is 1.
+// long_rows: for an unmasked run, out: kRowsLong if round 0 met rows longer than
+// the cooperative threshold, plus kRowsPastWave if it met rows of more than
+// kP3Wave entries, -1 if the run did not say; for a masked run, in: the value of
+// the unmasked run of the same graph.  Refresh Column compacts (launch modes 1
+// then 2) only with kRowsLong.
 // The ablation kernels' configuration (null: the production kernels).
 struct AblRun {
     bool unpacked = false;  // three-field tuples
@@ -410,7 +412,8 @@ int run_rounds(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Workspac
         a.abl = abl->pflags;
     }
     // compaction: unknown (-1) until round 1 reports what round 0 met
-    int longs = masked ? (*long_rows > 0 ? 1 : 0) : -1;
+    int longs = masked ? std::max(*long_rows, 0) : -1;
+    auto compacts = [&]() { return longs > 0 && (longs & kRowsLong); };
     const int cfrom = masked ? 0 : kCompactFrom;
     int cstart = -1;  // first compacting round
     // a new epoch: words still arriving from the late rounds of the run
@@ -433,7 +436,12 @@ int run_rounds(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Workspac
         if (v != ~0ull && (uint32_t)(v >> 48) == a.epoch) {
             seen = (int)((v >> 32) & 0xFFFFu);
             live = (uint32_t)v & ~kLongRowsBit;
-            if (longs < 0 && seen >= 1) longs = ((uint32_t)v & kLongRowsBit) ? 1 : 0;
+            if (longs < 0 && seen >= 1) {
+                // (word 1 of this round or a later one, written before word 0)
+                const unsigned long long w2 = __atomic_load_n(ctx->alive_host + 1, __ATOMIC_ACQUIRE);
+                const bool past = ((uint32_t)w2 & kLongRowsBit) || (uint32_t)(w2 >> 48) != a.epoch;
+                longs = ((uint32_t)v & kLongRowsBit ? kRowsLong : 0) | (past ? kRowsPastWave : 0);
+            }
         }
         if (live == 0u) break;  // worklist1 empty: the run has ended at round `seen`
         if (seen != last_seen) {
@@ -459,9 +467,10 @@ int run_rounds(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Workspac
                 // worklist2 at round `seen` (word 1, written before word 0)
                 const unsigned long long w2 = __atomic_load_n(ctx->alive_host + 1, __ATOMIC_ACQUIRE);
                 if (w2 != ~0ull && (uint32_t)(w2 >> 48) == a.epoch &&
-                    (int)((w2 >> 32) & 0xFFFFu) == seen && (uint32_t)w2 < (uint32_t)kTailCap) {
+                    (int)((w2 >> 32) & 0xFFFFu) == seen &&
+                    ((uint32_t)w2 & ~kLongRowsBit) < (uint32_t)kTailCap) {
                     int cs = -1;  // first compacting round
-                    if (a.colc && longs > 0) cs = cstart >= 0 ? cstart : std::max(round, cfrom);
+                    if (a.colc && compacts()) cs = cstart >= 0 ? cstart : std::max(round, cfrom);
                     Launch lt{3, phase, round, lanes, nullptr, nullptr};
                     lt.cstart = cs;
                     if (ctx->profile) {
@@ -487,7 +496,7 @@ int run_rounds(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Workspac
                 }
             }
             int mode = 0;
-            if (can_compact && longs > 0) {
+            if (can_compact && compacts()) {
                 if (cstart < 0) cstart = round;
                 mode = round == cstart ? 1 : 2;
                 // the live bits take the place of round 1's marks, read for
@@ -503,10 +512,10 @@ int run_rounds(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Workspac
             // (same segments, same results), whose per-launch cost is lower
             // once few rows are left; only where no row is long, so that no
             // round compacts (the two kernels' compaction thresholds differ)
-            if (lanes == kStagedLanes && !abl && !late_lanes && longs == 0) {
+            if (lanes == kStagedLanes && !abl && !late_lanes && longs >= 0 && !compacts()) {
                 const unsigned long long w2 = __atomic_load_n(ctx->alive_host + 1, __ATOMIC_ACQUIRE);
                 if (w2 != ~0ull && (uint32_t)(w2 >> 48) == a.epoch &&
-                    (uint64_t)(uint32_t)w2 * kLateShare < (uint64_t)g->n)
+                    (uint64_t)((uint32_t)w2 & ~kLongRowsBit) * kLateShare < (uint64_t)g->n)
                     late_lanes = kLateLanes;
             }
             const int rl = late_lanes ? late_lanes : lanes;
@@ -1634,9 +1643,14 @@ int aggregate_impl(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int32_t *a
     // or every 27-point row would be long (27-point 100^3 aggregation with
     // 1 lane: 1.7 ms, with 4: 0.78 ms)
     const int p3_lanes = std::max(4, group_lanes(lanes_for(ctx, g)));
-    // phase 1 has seen every row: none past the cooperative threshold, or any
-    const int64_t max_row = long_rows == 0 && lanes_for(ctx, g) > 0
-                                ? coop_threshold(lanes_for(ctx, g)) : INT64_MAX;
+    // phase 1 has seen every row (a persistent launch does not say): kernels for
+    // rows that the graph does not have are not launched, some 4 us each
+    int64_t max_row = INT64_MAX;
+    if (long_rows >= 0 && !(long_rows & kRowsPastWave)) {
+        const int lanes = lanes_for(ctx, g);
+        const bool brief = !(long_rows & kRowsLong) && (lanes <= 0 || coop_threshold(lanes) <= 32);
+        max_row = brief ? 32 : kP3Wave;
+    }
     HIP_TRY(ctx, launch_phase3(p3_lanes, gm.blocks, g->row_ptr, g->col, ws.label,
                                ws.aggsize, p3_io, mid_io, max_row, agg_id, ctx->pinned + kS_Err, s));
 

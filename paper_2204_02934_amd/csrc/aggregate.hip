@@ -306,12 +306,16 @@ __global__ __launch_bounds__(kBlock) void k_phase3(const int64_t *__restrict__ r
     if (lane == 0) io.cnt_out[w] = kept;
 }
 
-// The rows k_phase3 listed: those of up to kP3Mid entries here, longer ones
+// The rows k_phase3 listed: those of up to kP3Wave entries here, longer ones
 // listed again, in order, for k_phase3_long.  `share` wavefronts take one
 // segment's rows between them, so the device is full where segments are few.
 // It is bound by each row's chain of loads (columns, labels, sizes); without
 // LDS eight wavefronts per SIMD hide it.  Elasticity 60^3 (rows of 80): an LDS
-// hash map per wavefront, 16 KiB and so two per SIMD, took 285 us.
+// hash map per wavefront, 16 KiB and so two per SIMD, took 285 us.  Chung-Lu with
+// 33 587, 221 710, 1 065 829 and 4M vertices: that map 9.5, 17, 33 and 85 us for
+// all rows of more than 32 entries, this and k_phase3_long 13.9, 16, 31 and 74
+// (rows of up to 512 here, one aggregate at a time: 28, 30 and 47 for the first
+// three).
 __global__ __launch_bounds__(kBlock) void k_phase3_mid(const int64_t *__restrict__ row_ptr,
                                                        const int32_t *__restrict__ col,
                                                        const int32_t *__restrict__ label,
@@ -330,8 +334,8 @@ __global__ __launch_bounds__(kBlock) void k_phase3_mid(const int64_t *__restrict
         const bool valid = i0 + lane < count;
         const int32_t v = valid ? io.wl_in[sbase + i0 + lane] : 0;
         const int64_t s = row_ptr[v], d = row_ptr[v + 1] - s;
-        const bool longer = valid && d > kP3Mid;
-        const int len = (int)min(d, (int64_t)kP3Mid);
+        const bool longer = valid && d > kP3Wave;
+        const int len = (int)min(d, kP3Wave);
         const uint64_t again = __ballot(longer);
         if (part == 0) {
             if (longer) io.wl_out[sbase + kept + (uint32_t)__popcll(again & lanes_below(lane))] = v;
@@ -347,7 +351,7 @@ __global__ __launch_bounds__(kBlock) void k_phase3_mid(const int64_t *__restrict
                 (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(s >> 32), l) << 32) |
                           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)s, l));
             int bc = 0, bs = 0x7FFFFFFF, ba = 0x7FFFFFFF;
-            p3_mid(
+            p3_mid<kP3Wave>(
                 lr, [&](int j) { return col[sr + j]; }, [&](int32_t u) { return label[u]; },
                 [&](int32_t y) { return aggsize[y]; }, bc, bs, ba);
             if (lane == 0) {
@@ -361,8 +365,9 @@ __global__ __launch_bounds__(kBlock) void k_phase3_mid(const int64_t *__restrict
     if (part == 0 && lane == 0) io.cnt_out[w] = kept;
 }
 
-// Rows of more than kP3Mid entries, one workgroup each: the couplings are
-// counted in an LDS hash map (aggregate id -> count) of kP3Slots slots, of the
+// Rows of more than kP3Wave entries, one workgroup each: the couplings are
+// counted in an LDS hash map (aggregate id -> count) of twice as many slots as
+// entries, kP3Slots at most, of the
 // ids in one of `parts` classes of a hash at a time, parts chosen so that a
 // class is expected to fill half the map; a class that does not fit restarts
 // the row with twice the classes.  The workgroup then reduces the entries with
@@ -381,7 +386,7 @@ __global__ __launch_bounds__(kBlock) void k_phase3_long(const int64_t *__restric
                                                         SegIO io, int32_t *__restrict__ agg_out,
                                                         uint32_t *__restrict__ err) {
     constexpr uint32_t kEmpty = 0xFFFFFFFFu;
-    constexpr int kBits = __builtin_ctz(kP3Slots), kWv = kBlock / 64;
+    constexpr int kBits = __builtin_ctz(kP3Slots), kLeast = 9, kWv = kBlock / 64;
     constexpr uint32_t kMost = kP3Slots * 3 / 4;  // ids in the map; each thread may add one more
     static_assert(kMost + kBlock < kP3Slots, "a probe always ends at an empty slot");
     __shared__ uint32_t keys[kP3Slots], cnts[kP3Slots];
@@ -394,10 +399,15 @@ __global__ __launch_bounds__(kBlock) void k_phase3_long(const int64_t *__restric
     auto row = [&](const int32_t v) {
         const int64_t s = row_ptr[v], e = row_ptr[v + 1];
         int bc = 0, bs = 0x7FFFFFFF, ba = 0x7FFFFFFF;
+        // (the map of a row of up to kP3Slots / 2 entries is never more than half
+        // full, so only rows in classes restart)
+        int bits = kLeast;
+        while (bits < kBits && (int64_t)1 << bits < 2 * (e - s)) bits++;
+        const int slots = 1 << bits;
         // (a class value is shared by some 128 ids, so doubling comes to an end)
         uint32_t parts = (uint32_t)((e - s + kP3Slots / 2 - 1) / (kP3Slots / 2));
         for (uint32_t p = 0; p < parts;) {
-            for (int k = tid; k < kP3Slots; k += kBlock) {
+            for (int k = tid; k < slots; k += kBlock) {
                 keys[k] = kEmpty;
                 cnts[k] = 0u;
             }
@@ -415,7 +425,7 @@ __global__ __launch_bounds__(kBlock) void k_phase3_long(const int64_t *__restric
                     const uint32_t key = (uint32_t)a[k], h0 = key * 2654435761u;
                     // the class by other bits than the slot
                     if (((h0 & 0xFFFFu) ^ (key >> 7)) % parts != p) continue;
-                    uint32_t h = h0 >> (32 - kBits);
+                    uint32_t h = h0 >> (32 - bits);
                     for (;;) {
                         uint32_t prev = keys[h];
                         if (prev == kEmpty) {
@@ -427,14 +437,14 @@ __global__ __launch_bounds__(kBlock) void k_phase3_long(const int64_t *__restric
                             atomicAdd(&cnts[h], 1u);
                             break;
                         }
-                        h = (h + 1) & (kP3Slots - 1);
+                        h = (h + 1) & (uint32_t)(slots - 1);
                     }
                 }
             }
             __syncthreads();
             const bool full = *vnum > kMost;
             if (!full)
-                for (int k = tid; k < kP3Slots; k += kBlock) {
+                for (int k = tid; k < slots; k += kBlock) {
                     const uint32_t key = keys[k];
                     if (key == kEmpty) continue;
                     const int c = (int)cnts[k], sz = aggsize[key];
@@ -664,12 +674,14 @@ hipError_t launch_phase3(int lanes, int blocks, const int64_t *row_ptr, const in
     MIS2_P3_DISPATCH(lanes, dim3(blocks), dim3(kBlock), 0, s, row_ptr, col, label, aggsize, io,
                      agg_out, err);
     if (max_row > 32) {  // k_phase3 keeps up to 32 entries whatever its lanes
-        // about 8 wavefronts per SIMD (of 1024)
-        const int share = (int)std::max<int64_t>(1, std::min<int64_t>(8, 8192 / io_mid.S));
+        // about 16 wavefronts per SIMD (of 1024), twice what is resident, so that a
+        // segment of many hubs does not hold the launch up (Chung-Lu 1 065 829
+        // vertices: 8 per SIMD 30.6 us, 16 19.8)
+        const int share = (int)std::max<int64_t>(1, std::min<int64_t>(8, 16384 / io_mid.S));
         hipLaunchKernelGGL(k_phase3_mid, dim3((unsigned)(blocks * share)), dim3(kBlock), 0, s,
                            row_ptr, col, label, aggsize, io_mid, share, agg_out, err);
     }
-    if (max_row > kP3Mid) {
+    if (max_row > kP3Wave) {
         SegIO io_long = io_mid;
         io_long.wl_in = io_mid.wl_out;
         io_long.cnt_in = io_mid.cnt_out;

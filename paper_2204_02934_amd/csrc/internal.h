@@ -221,8 +221,9 @@ struct SegIO {
     int32_t *ccol_out;
     int32_t *lenc_out;
     // Refresh Column of round 0 (unmasked): a wavefront that meets a row
-    // longer than the cooperative threshold sets one of kSplit flags
-    // (stride kCtrLine), or null.
+    // longer than the cooperative threshold (flat sweeps: than 32 entries) sets
+    // one of kSplit flags (stride kCtrLine), and the word after it for a row of
+    // more than kP3Wave entries; or null.
     uint32_t *long_flag;
     int64_t nnz;  // entries of the CSR (the staged sweeps' 16-byte loads stay below it)
     // Refresh Column of rounds 0 and 1 of an unmasked run on one graph: a
@@ -276,7 +277,8 @@ struct RoundsArgs {
     uint32_t *bar;
     int32_t *colc;   // [nnz] compacted rows, or null (no compaction)
     int32_t *lenc;   // [n] their lengths
-    uint32_t *lflag; // [kSplit][kCtrLine] set by round 0 when a row is long (zero at the start)
+    uint32_t *lflag; // [kSplit][kCtrLine] set by round 0 when a row is long (SegIO::long_flag;
+                     // zero at the start)
     int abl;         // ablation kernels only: kAblFixed | kAblXorshift
     int gen0;        // 1: rounds 0 and 1 of Refresh Column may compute the tuples they gather
     uint8_t *near;   // Workspace::near
@@ -308,8 +310,13 @@ struct AblTuples {
 };
 
 // Bit of the host-reported |worklist1| word that says round 0 met rows long
-// enough for the cooperative pass (|worklist1| < 2^31 always).
+// enough for the cooperative pass, and of the |worklist2| word that it met rows
+// of more than kP3Wave entries (both sizes are below 2^31 always).
 constexpr uint32_t kLongRowsBit = 0x80000000u;
+constexpr int kRowsLong = 1, kRowsPastWave = 2;  // the same, as run_rounds keeps them
+// Phase 3: a wavefront takes rows of up to kP3Wave entries, a workgroup longer
+// ones.
+constexpr int64_t kP3Wave = 128;
 constexpr uint32_t kEpochMax = 0x7FFFu;  // epochs in the top 16 bits of a host word
 // A host word: epoch, round and a 32-bit value.
 __host__ __device__ inline unsigned long long host_word(uint32_t epoch, int round, uint32_t value) {

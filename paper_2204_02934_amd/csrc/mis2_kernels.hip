@@ -216,6 +216,15 @@ __device__ __forceinline__ int64_t heavy_threshold() {
 }
 constexpr int kCoopLoads = 8;  // loads per lane per cooperative step
 
+// Round 0 of Refresh Column says whether the wavefront met rows past the
+// cooperative threshold and rows of more than kP3Wave entries.
+__device__ __forceinline__ void report_rows(const SegIO &io, uint64_t heavy, uint64_t past) {
+    uint32_t *flag = io.long_flag + (blockIdx.x % kSplit) * kCtrLine;
+    if ((threadIdx.x & 63u) != 0) return;
+    if (heavy) flag[0] = 1u;
+    if (past) flag[1] = 1u;
+}
+
 // t[k] = T[x[k]], read only where the live bit is set: T is OUT elsewhere.  The
 // dead entries' lanes all read T[0], one line.
 template <int K>
@@ -498,8 +507,8 @@ __device__ __forceinline__ uint32_t sweep_column(const int64_t *__restrict__ row
             uint64_t heavy = __ballot(sub == 0 && e[u] - s[u] > heavy_threshold<L>());
             // round 0 reports that the graph has such rows (compaction pays
             // only for them)
-            if (!RD && !WR && heavy && io.long_flag && lane == 0)
-                io.long_flag[(blockIdx.x % kSplit) * kCtrLine] = 1u;
+            if (!RD && !WR && io.long_flag && (heavy || heavy_threshold<L>() > kP3Wave))
+                report_rows(io, heavy, __ballot(e[u] - s[u] > kP3Wave));
             if (flat) heavy = __ballot(sub == 0 && e[u] - s[u] > kFlatHeavy);
             while (heavy) {
                 const int src = __ffsll((unsigned long long)heavy) - 1;
@@ -920,8 +929,7 @@ __device__ __forceinline__ uint32_t sweep_column_staged(const int64_t *__restric
         bool wrote = false;
         // long rows: the whole wavefront streams each one in turn
         uint64_t heavy = __ballot(sub == 0 && e - s > kStagedCap);
-        if (!RD && !WR && heavy && io.long_flag && lane == 0)
-            io.long_flag[(blockIdx.x % kSplit) * kCtrLine] = 1u;
+        if (!RD && !WR && heavy && io.long_flag) report_rows(io, heavy, __ballot(e - s > kP3Wave));
         while (heavy) {
             const int src = __ffsll((unsigned long long)heavy) - 1;
             heavy &= heavy - 1;
@@ -1148,6 +1156,7 @@ __device__ __forceinline__ uint32_t flat_column(const int64_t *__restrict__ row_
         uint32_t m = T[v];
         const int64_t len = ok ? e - s : 0;
         dsum += (unsigned long long)len;
+        if (io.long_flag) report_rows(io, __ballot(len > 32), __ballot(len > kP3Wave));
         // high-degree rows: the whole wavefront, one at a time
         uint64_t heavy = __ballot(len > kFlatHeavy);
         while (heavy) {
@@ -1428,14 +1437,16 @@ __device__ __forceinline__ void round_sizes(const RoundsArgs &a, int r, uint32_t
 }
 
 // Refresh Column of round r.  Workgroup 0 records the round's sizes and
-// reports (r, |worklist1|) to the host, with bit 31 of the low word set from
-// round 1 on when round 0 met rows long enough for the cooperative pass.
+// reports (r, |worklist1|) and (r, |worklist2|) to the host, with bit 31 of the
+// low words set from round 1 on when round 0 met long rows (kLongRowsBit).
 // RD / WR: read / write the compacted rows.
 __device__ __forceinline__ void round_start(const RoundsArgs &a, int r) {
     if (blockIdx.x == 0 && threadIdx.x < 64) {
         uint32_t c1, c2;
         round_sizes(a, r, c1, c2);
-        const uint32_t longs = (r >= 1 && !a.masked && a.lflag) ? ctr_sum(a.lflag) : 0u;
+        const bool report = r >= 1 && !a.masked && a.lflag;
+        const uint32_t longs = report ? ctr_sum(a.lflag) : 0u;
+        const uint32_t past = report ? ctr_sum(a.lflag + 1) : 0u;
         if (threadIdx.x == 0) {
             a.rt[(size_t)r * kRoundStride] = c1;
             a.rt[(size_t)r * kRoundStride + 1] = c2;
@@ -1447,8 +1458,9 @@ __device__ __forceinline__ void round_start(const RoundsArgs &a, int r) {
             if (a.alive_host) {
                 // word 1: (round, |worklist2|), stored before word 0 so that a
                 // host that reads word 0 of round r finds word 1 of round r
-                __hip_atomic_store(a.alive_host + 1, host_word(a.epoch, r, c2), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_SYSTEM);
+                __hip_atomic_store(a.alive_host + 1,
+                                   host_word(a.epoch, r, c2 | (past ? kLongRowsBit : 0u)),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
                 __hip_atomic_store(a.alive_host,
                                    host_word(a.epoch, r, c1 | (longs ? kLongRowsBit : 0u)),
                                    __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);

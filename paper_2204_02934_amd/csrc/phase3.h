@@ -73,16 +73,22 @@ __device__ __forceinline__ void p3_count(const int32_t (&a)[K], const int32_t (&
 }
 
 // Rows of up to kP3Mid entries, one wavefront each, K entries per lane in
-// registers.  A row couples to few aggregates (a 27-point row of three
+// registers.  On a mesh a row couples to few aggregates (a 27-point row of three
 // unknowns: 80 entries, some 6 aggregates), so they are counted one by one: the
 // first lane not yet counted names its label, and ballots count it among all
-// K * 64 entries.  Returns (scalars) the best candidate in the order above.
+// K * 64 entries, some 100 cycles an aggregate.  A hub's row may couple to as
+// many aggregates as it has entries: past kP3Few of them a row of up to 128
+// entries compares each label with all, as p3_count does, some 10 cycles an
+// entry (Chung-Lu 33 587 vertices, k_phase3_mid 23.5 us with up to 128 aggregates
+// one by one).  Returns (scalars) the best candidate in the order above.
 constexpr int kP3Mid = 512;
+constexpr int kP3Few = 8;
 // nb(j): the row's j-th neighbour; lab(u): a vertex's label (negative: none);
 // size(y): an aggregate's size.
 template <int K, typename NB, typename LAB, typename SIZE>
 __device__ __forceinline__ void p3_mid_row(int len, NB nb, LAB lab, SIZE size, int &bc, int &bs,
                                            int &ba) {
+    constexpr bool kPairs = K <= 2;
     const int lane = (int)(threadIdx.x & 63u);
     int32_t a[K], sz[K];
 #pragma unroll
@@ -96,9 +102,10 @@ __device__ __forceinline__ void p3_mid_row(int len, NB nb, LAB lab, SIZE size, i
         left[k] = __ballot(a[k] >= 0);
         sz[k] = size(a[k] >= 0 ? a[k] : 0);
     }
+    int found = 0;
 #pragma unroll
     for (int k = 0; k < K; k++) {
-        while (left[k]) {
+        while (left[k] && (!kPairs || found < kP3Few)) {
             const int l = __ffsll((unsigned long long)left[k]) - 1;
             const int32_t y = __builtin_amdgcn_readlane(a[k], l);
             const int ysz = __builtin_amdgcn_readlane(sz[k], l);
@@ -114,16 +121,48 @@ __device__ __forceinline__ void p3_mid_row(int len, NB nb, LAB lab, SIZE size, i
                 bs = ysz;
                 ba = y;
             }
+            found++;
         }
+    }
+    if constexpr (kPairs) {
+        uint64_t rest = 0;
+#pragma unroll
+        for (int k = 0; k < K; k++) rest |= left[k];
+        if (!rest) return;
+        int cnt[K] = {}, c = 0, s = 0x7FFFFFFF, y = 0x7FFFFFFF;
+#pragma unroll
+        for (int q = 0; q < K; q++) {
+            const int m = min(64, len - q * 64);
+            for (int t = 0; t < m; t++) {
+                const int32_t b = __builtin_amdgcn_readlane(a[q], t);
+#pragma unroll
+                for (int k = 0; k < K; k++) cnt[k] += b == a[k];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            if (a[k] >= 0 && better(cnt[k], sz[k], a[k], c, s, y)) {
+                c = cnt[k];
+                s = sz[k];
+                y = a[k];
+            }
+        }
+        p3_group_best<64>(c, s, y);
+        // (the aggregates counted one by one are among these)
+        bc = __builtin_amdgcn_readfirstlane(c);
+        bs = __builtin_amdgcn_readfirstlane(s);
+        ba = __builtin_amdgcn_readfirstlane(y);
     }
 }
 
-template <typename NB, typename LAB, typename SIZE>
+// Rows of up to MAX entries (kP3Mid, or 128).
+template <int MAX, typename NB, typename LAB, typename SIZE>
 __device__ __forceinline__ void p3_mid(int len, NB nb, LAB lab, SIZE size, int &bc, int &bs,
                                        int &ba) {
+    static_assert(MAX == 128 || MAX == kP3Mid, "p3_mid: two or kP3Mid / 64 entries a lane");
     if (len <= 64)
         p3_mid_row<1>(len, nb, lab, size, bc, bs, ba);
-    else if (len <= 128)
+    else if (MAX == 128 || len <= 128)
         p3_mid_row<2>(len, nb, lab, size, bc, bs, ba);
     else
         p3_mid_row<kP3Mid / 64>(len, nb, lab, size, bc, bs, ba);

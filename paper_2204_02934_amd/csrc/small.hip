@@ -380,7 +380,7 @@ __global__ __launch_bounds__(kSmThreads) void k_small(SmallArgs a) {
                 const int v = v0 + l;
                 const int rs = start(v);
                 int bc = 0, bs = 0x7FFFFFFF, ba = 0x7FFFFFFF;
-                p3_mid(
+                p3_mid<kP3Mid>(
                     start(v + 1) - rs, [&](int j) { return nb(rs + j); }, lab,
                     [&](int y) { return (int)S.size[y]; }, bc, bs, ba);
                 if (lane == 0) {
