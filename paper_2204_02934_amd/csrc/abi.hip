@@ -502,7 +502,7 @@ int run_rounds(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Workspac
                 // the live bits take the place of round 1's marks, read for
                 // the last time by its Decide Set
                 a.live = nullptr;
-                if (ws.near && g->n >= kGenMinN &&
+                if (ws.near && g->n >= kGenMinN && lanes <= kLiveLanes &&
                     (seen < 0 || (uint64_t)live * kLiveShare >= (uint64_t)g->n)) {
                     a.live = (const uint32_t *)ws.near;
                     HIP_TRY(ctx, launch_live_bits(g->n, ws.T, (uint32_t *)ws.near, s));

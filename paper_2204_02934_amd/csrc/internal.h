@@ -463,6 +463,11 @@ hipError_t launch_push_in(int64_t n, const int64_t *row_ptr, const int32_t *col,
 // vertices of round 0 and their neighbours) and on its neighbours.
 hipError_t launch_push_near(int64_t n, const int64_t *row_ptr, const int32_t *col,
                             const uint32_t *M, uint8_t *near, hipStream_t s);
+// Refresh Column asks live bits with at most this many lanes a row.  Aggregation
+// of Chung-Lu 2.5M without and with them (kernels, us): 1 lane 2978 and 2579, 2
+// 3035 and 2910, 4 3226 and 3051, 8 3679 and 3526; 16 4595 and 4731, staged 3074
+// and 3108.
+constexpr int kLiveLanes = 8;
 // Bit v of live clear only where T[v] is OUT.  Writes ceil(n / 64) * 2 words.
 hipError_t launch_live_bits(int64_t n, const uint32_t *T, uint32_t *live, hipStream_t s);
 hipError_t launch_dec_round(int lanes, int blocks, const int64_t *row_ptr, const int32_t *col,

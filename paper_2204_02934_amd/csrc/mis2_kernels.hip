@@ -1470,9 +1470,9 @@ __device__ __forceinline__ void round_start(const RoundsArgs &a, int r) {
     clear_slot(a.ctr, r);
 }
 
-// GEN: the kernel that may compute the tuples of rounds 0 and 1
-// (k_col_round0); the others never do, so the code that would is compiled
-// out of them.
+// GEN: the kernels of large graphs: rounds 0 and 1 that may compute the tuples
+// (k_col_round0), compacting rounds that may ask the live bits and, with one
+// lane a row, take flat_min.  The code that would is compiled out of the others.
 template <int L, bool RD, bool WR, bool GEN = false>
 __device__ __forceinline__ void col_round(const int64_t *__restrict__ row_ptr,
                                           const int32_t *__restrict__ col,
@@ -1489,11 +1489,11 @@ __device__ __forceinline__ void col_round(const int64_t *__restrict__ row_ptr,
         io.ccol_out = a.colc;
         io.lenc_out = a.lenc;
     }
-    if (RD || WR) io.live = a.live;
+    if (GEN && (RD || WR)) io.live = a.live;
     const int64_t w = wave_id();
     const Seg sg = seg_of(io, w);
     uint32_t kept;
-    if constexpr ((GEN || RD || WR) && L == 1) {
+    if constexpr (GEN && L == 1) {
         __shared__ FlatLds sh[kBlock / 64];
         kept = sweep_column<L, kRows, kChunks<L>, RD, WR>(row_ptr, col, T, M, io, sg,
                                                           &sh[threadIdx.x >> 6]);
@@ -1543,6 +1543,25 @@ __global__ __launch_bounds__(kBlock) void k_col_round_rw(const int64_t *__restri
                                                          uint32_t *__restrict__ M, RoundsArgs a,
                                                          int r) {
     col_round<L, true, true>(row_ptr, col, T, M, a, r);
+}
+
+// The compacting rounds of large graphs (see launch_col_round).
+template <int L>
+__global__ __launch_bounds__(kBlock) void k_col_round_w_live(const int64_t *__restrict__ row_ptr,
+                                                             const int32_t *__restrict__ col,
+                                                             const uint32_t *__restrict__ T,
+                                                             uint32_t *__restrict__ M,
+                                                             RoundsArgs a, int r) {
+    col_round<L, false, true, true>(row_ptr, col, T, M, a, r);
+}
+
+template <int L>
+__global__ __launch_bounds__(kBlock) void k_col_round_rw_live(const int64_t *__restrict__ row_ptr,
+                                                              const int32_t *__restrict__ col,
+                                                              const uint32_t *__restrict__ T,
+                                                              uint32_t *__restrict__ M,
+                                                              RoundsArgs a, int r) {
+    col_round<L, true, true, true>(row_ptr, col, T, M, a, r);
 }
 
 // Decide Set where most rows are settled by their own M and T (round 0: a row
@@ -2562,7 +2581,29 @@ hipError_t launch_col_round(int lanes, int blocks, const int64_t *row_ptr, const
                             const uint32_t *T, uint32_t *M, const RoundsArgs &a, int r, int mode,
                             hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (mode != 0 && (lanes <= 0 || !a.colc || !a.lenc)) return hipErrorInvalidValue;
-    if (mode == 1) {
+    if (a.live && (mode == 0 || lanes > kLiveLanes)) return hipErrorInvalidValue;
+    // Large graphs: the rounds with live bits, and with one lane a row the others
+    // too (flat_min).  The plain kernels need fewer registers: compacting rounds
+    // of an aggregation with one lane a row, plain and these, Chung-Lu with 5023
+    // vertices 107 and 115 us, 221 710 211 and 222, 1 065 829 592 and 604.
+    if (mode != 0 && (a.live || (a.gen0 && lanes == 1))) {
+        auto go = [&](auto kernel) {
+            if (e0)
+                hipExtLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, s, e0, e1, 0, row_ptr,
+                                      col, T, M, a, r);
+            else
+                hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, s, row_ptr, col, T, M, a,
+                                   r);
+        };
+        const bool first = mode == 1;
+        switch (lanes) {
+            case 1: first ? go(k_col_round_w_live<1>) : go(k_col_round_rw_live<1>); break;
+            case 2: first ? go(k_col_round_w_live<2>) : go(k_col_round_rw_live<2>); break;
+            case 4: first ? go(k_col_round_w_live<4>) : go(k_col_round_rw_live<4>); break;
+            case 8: first ? go(k_col_round_w_live<8>) : go(k_col_round_rw_live<8>); break;
+            default: return hipErrorInvalidValue;
+        }
+    } else if (mode == 1) {
         MIS2_LANE_DISPATCH_TIMED(lanes, k_col_round_w, dim3(blocks), dim3(kBlock), s, e0, e1,
                                  row_ptr, col, T, M, a, r);
     } else if (mode == 2) {
