@@ -644,17 +644,19 @@ __device__ __forceinline__ uint32_t sweep_column(const int64_t *__restrict__ row
 }
 
 // Decide Set over the wavefront's segment, with the next round's Refresh Row
-// for the vertices that stay undecided (loads as in sweep_column).
-template <int L, int U, int K>
+// for the vertices that stay undecided (loads as in sweep_column).  APPEND
+// false: only T is written, the vertices kept are left to the caller.
+template <int L, int U, int K, bool APPEND = true>
 __device__ __forceinline__ uint32_t sweep_decide(const int64_t *__restrict__ row_ptr,
                                                  const int32_t *__restrict__ col,
                                                  uint32_t *__restrict__ T,
                                                  const uint32_t *__restrict__ M,
                                                  const TupleParams &next, const SegIO &io,
-                                                 const Seg &sg, uint32_t kept = 0) {
+                                                 const Seg &sg) {
     constexpr int G = 64 / L;
     const int lane = (int)(threadIdx.x & 63u);
     const int sub = lane & (L - 1);
+    uint32_t kept = 0;
     unsigned long long dsum = 0;
     // The rows of step i + 1 are loaded while step i's gathers are in flight
     // (as in sweep_column).
@@ -777,7 +779,7 @@ __device__ __forceinline__ uint32_t sweep_decide(const int64_t *__restrict__ row
                 }
                 T[v[u]] = nt;
             }
-            seg_append(io, sg, keep, v[u], kept);
+            if (APPEND) seg_append(io, sg, keep, v[u], kept);
         }
         if (more) {
 #pragma unroll
@@ -1567,11 +1569,15 @@ __global__ __launch_bounds__(kBlock) void k_col_round_rw_live(const int64_t *__r
 // Decide Set where most rows are settled by their own M and T (round 0: a row
 // whose M differs from its tuple stays undecided): every lane looks at a vertex
 // of its own, kAhead of them at once, and only the rows that have to be read go,
-// through a list in LDS, to the sweep.  (The survivors of a segment are then in
-// no particular order.)  Staged rows, and rows of several lanes, each held a step
-// of the wavefront up: 27-point 100^3 24 us, elasticity 60^3 25 us, now 10 each.
-// With one lane a row the sweep looks at 64 rows a step anyhow (Chung-Lu 4M 75 us
-// either way, 512 subdomains 260).
+// through a list in LDS, to the sweep.  Staged rows, and rows of several lanes,
+// each held a step of the wavefront up: 27-point 100^3 with staged rows 22 us a
+// launch, elasticity 59^3 with four lanes 27, now 11 each.  With one lane a row
+// the sweep looks at 64 rows a step anyhow (Chung-Lu 4M 75 us either way, 512
+// subdomains 260).
+// The vertices that stay are listed in order, by a second look at their T, 0.5
+// us a launch: listed as they were settled, those that were read last, they
+// slowed the later Decide Sets (Chung-Lu 4M, staged rows, rounds 1 on of an
+// aggregation: 952 us, in order 860).
 constexpr int kAhead = 4, kToRead = 512;
 
 template <int L>
@@ -1585,15 +1591,19 @@ __device__ __forceinline__ uint32_t decide_few(const int64_t *__restrict__ row_p
     __shared__ int32_t to_read[kBlock / 64][kToRead + 64];
     int32_t *list = to_read[threadIdx.x >> 6];
     const int lane = (int)(threadIdx.x & 63u);
-    uint32_t kept = 0, count = 0;
-    for (int64_t i0 = 0; i0 < sg.count; i0 += 64 * kAhead) {
-        int32_t v[kAhead];
-        uint32_t t[kAhead], m[kAhead];
+    auto vertices = [&](int64_t i0, int32_t (&v)[kAhead]) {
 #pragma unroll
         for (int k = 0; k < kAhead; k++) {
             const int64_t i = min(i0 + 64 * k + lane, sg.count - 1);
             v[k] = io.wl_in ? io.wl_in[sg.base + i] : (int32_t)(sg.base + i);
         }
+    };
+    uint32_t kept = 0, count = 0;
+    int64_t listed = 0;
+    for (int64_t i0 = 0; i0 < sg.count; i0 += 64 * kAhead) {
+        int32_t v[kAhead];
+        uint32_t t[kAhead], m[kAhead];
+        vertices(i0, v);
 #pragma unroll
         for (int k = 0; k < kAhead; k++) {
             t[k] = T[v[k]];
@@ -1606,19 +1616,28 @@ __device__ __forceinline__ uint32_t decide_few(const int64_t *__restrict__ row_p
             const uint64_t mask = __ballot(read);
             if (read) list[count + (uint32_t)__popcll(mask & lanes_below(lane))] = v[k];
             count += (uint32_t)__popcll(mask);
-            const bool keep = ok && !read;
-            if (keep) T[v[k]] = make_tuple(next, (uint32_t)v[k]);
-            seg_append(io, sg, keep, v[k], kept);
+            if (ok && !read) T[v[k]] = make_tuple(next, (uint32_t)v[k]);
         }
-        if (count > kToRead - 64 * kAhead || i0 + 64 * kAhead >= sg.count) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int64_t end = min(i0 + 64 * kAhead, sg.count);
+        if (count > kToRead - 64 * kAhead || end == sg.count) {
+            wave_lds_sync();
             SegIO rows = io;
             rows.wl_in = list - sg.base;
-            kept = sweep_decide<L, kRows, kChunks<L>>(row_ptr, col, T, M, next, rows,
-                                                      Seg{sg.base, (int64_t)count}, kept);
+            sweep_decide<L, kRows, kChunks<L>, false>(row_ptr, col, T, M, next, rows,
+                                                      Seg{sg.base, (int64_t)count});
             count = 0;
+            // this wavefront's T is read back by other lanes
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            for (; listed < end; listed += 64 * kAhead) {
+                vertices(listed, v);
+#pragma unroll
+                for (int k = 0; k < kAhead; k++) t[k] = T[v[k]];
+#pragma unroll
+                for (int k = 0; k < kAhead; k++)
+                    seg_append(io, sg,
+                               listed + 64 * k + lane < end && t[k] != kOut && t[k] != kIn, v[k],
+                               kept);
+            }
         }
     }
     return kept;
@@ -2626,8 +2645,14 @@ hipError_t launch_col_round(int lanes, int blocks, const int64_t *row_ptr, const
 hipError_t launch_dec_round(int lanes, int blocks, const int64_t *row_ptr, const int32_t *col,
                             uint32_t *T, const uint32_t *M, const RoundsArgs &a, int r,
                             hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    // (k_dec_round0: not with one or two lanes a row, see decide_few)
-    if (r == 0 && !a.dsplit && !a.abl && lanes != 1 && lanes != 2) {
+    // k_dec_round0 not with one or two lanes a row (see decide_few), and with
+    // staged rows only where they are long or many: both kernels twice, here and
+    // there, 5-point 90 x 93 13.0 and 14.2 us, 7-point 40^3 13.3 and 14.1; 27-point
+    // 12^3 14.8 and 13.0, 30^3 15.6 and 12.5; Chung-Lu 221 710 33 and 30, 7-point
+    // 95^3 30 and 27
+    const bool staged_few = a.nnz >= 16 * a.n || a.n >= (int64_t)1 << 17;
+    if (r == 0 && !a.dsplit && !a.abl && lanes != 1 && lanes != 2 &&
+        (lanes != kStagedLanes || staged_few)) {
         const int few = lanes == kStagedLanes || lanes <= 0 ? 4 : std::min(lanes, 16);
         auto go = [&](auto kernel) {
             if (e0)
