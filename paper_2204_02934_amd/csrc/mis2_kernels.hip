@@ -1140,7 +1140,8 @@ __device__ __forceinline__ uint32_t sweep_decide_staged(const int64_t *__restric
 // first by the whole wavefront (coop_min_T / coop_decide) and leave the
 // flat range.
 // ---------------------------------------------------------------------------
-template <int U>
+// REPORT: round 0 may have to say what rows it met (io.long_flag).
+template <int U, bool REPORT>
 __device__ __forceinline__ uint32_t flat_column(const int64_t *__restrict__ row_ptr,
                                                 const int32_t *__restrict__ col,
                                                 const uint32_t *__restrict__ T,
@@ -1158,7 +1159,8 @@ __device__ __forceinline__ uint32_t flat_column(const int64_t *__restrict__ row_
         uint32_t m = T[v];
         const int64_t len = ok ? e - s : 0;
         dsum += (unsigned long long)len;
-        if (io.long_flag) report_rows(io, __ballot(len > 32), __ballot(len > kP3Wave));
+        if (REPORT && io.long_flag)
+            report_rows(io, __ballot(len > 32), __ballot(len > kP3Wave));
         // high-degree rows: the whole wavefront, one at a time
         uint64_t heavy = __ballot(len > kFlatHeavy);
         while (heavy) {
@@ -1336,7 +1338,7 @@ __device__ __forceinline__ uint32_t flat_decide(const int64_t *__restrict__ row_
 }
 
 // lanes == 0 in the plan selects the flat sweeps.
-template <int L, bool RD = false, bool WR = false>
+template <int L, bool RD = false, bool WR = false, bool GEN = false>
 __device__ __forceinline__ uint32_t any_column(const int64_t *__restrict__ row_ptr,
                                                const int32_t *__restrict__ col,
                                                const uint32_t *__restrict__ T,
@@ -1344,7 +1346,7 @@ __device__ __forceinline__ uint32_t any_column(const int64_t *__restrict__ row_p
                                                const Seg &sg) {
     if constexpr (L == 0) {
         __shared__ FlatLds sh[kBlock / 64];
-        return flat_column<kUnroll>(row_ptr, col, T, M, io, sg, sh[threadIdx.x >> 6]);
+        return flat_column<kUnroll, GEN>(row_ptr, col, T, M, io, sg, sh[threadIdx.x >> 6]);
     } else if constexpr (L == kStagedLanes) {
         __shared__ StagedLds<1> sh[kBlock / 64];
         return sweep_column_staged<1, RD, WR>(row_ptr, col, T, M, io, sg, sh[threadIdx.x >> 6]);
@@ -1446,9 +1448,13 @@ __device__ __forceinline__ void round_start(const RoundsArgs &a, int r) {
     if (blockIdx.x == 0 && threadIdx.x < 64) {
         uint32_t c1, c2;
         round_sizes(a, r, c1, c2);
-        const bool report = r >= 1 && !a.masked && a.lflag;
-        const uint32_t longs = report ? ctr_sum(a.lflag) : 0u;
-        const uint32_t past = report ? ctr_sum(a.lflag + 1) : 0u;
+        uint32_t longs = 0, past = 0;
+        if (r >= 1 && !a.masked && a.lflag) {
+            const uint32_t *flag = a.lflag + (threadIdx.x & 63u) * kCtrLine;
+            const uint32_t both = group_or<64>(flag[0] | flag[1] << 1);
+            longs = both & 1u;
+            past = both & 2u;
+        }
         if (threadIdx.x == 0) {
             a.rt[(size_t)r * kRoundStride] = c1;
             a.rt[(size_t)r * kRoundStride + 1] = c2;
@@ -1500,7 +1506,7 @@ __device__ __forceinline__ void col_round(const int64_t *__restrict__ row_ptr,
         kept = sweep_column<L, kRows, kChunks<L>, RD, WR>(row_ptr, col, T, M, io, sg,
                                                           &sh[threadIdx.x >> 6]);
     } else {
-        kept = any_column<L, RD, WR>(row_ptr, col, T, M, io, sg);
+        kept = any_column<L, RD, WR, GEN>(row_ptr, col, T, M, io, sg);
     }
     seg_finish(io, w, kept);
 }
@@ -1517,7 +1523,8 @@ __global__ __launch_bounds__(kBlock) void k_col_round(const int64_t *__restrict_
 // Rounds 0 and 1 where the neighbours' tuples are computed and that is exact
 // (unmasked, one graph; round 1 after k_push_in).  One lane per row: with
 // flat_min, Chung-Lu 4M vertices 304 -> 189 us a round.  The other runs' first
-// rounds take k_col_round, with fewer registers.
+// rounds take k_col_round, with fewer registers; but flat sweeps this one in any
+// run (elasticity 55^3, both runs' rounds 0, 181 us here, 198 there).
 template <int L>
 __global__ __launch_bounds__(kBlock) void k_col_round0(const int64_t *__restrict__ row_ptr,
                                                        const int32_t *__restrict__ col,
@@ -2628,7 +2635,8 @@ hipError_t launch_col_round(int lanes, int blocks, const int64_t *row_ptr, const
     } else if (mode == 2) {
         MIS2_LANE_DISPATCH_TIMED(lanes, k_col_round_rw, dim3(blocks), dim3(kBlock), s, e0, e1,
                                  row_ptr, col, T, M, a, r);
-    } else if (computes_tuples(a, r)) {
+    } else if (computes_tuples(a, r) || (r <= 1 && lanes == 0)) {
+        // (flat sweeps: the kernel that reports the rows it met)
         MIS2_LANE_DISPATCH_TIMED(lanes, k_col_round0, dim3(blocks), dim3(kBlock), s, e0, e1,
                                  row_ptr, col, T, M, a, r);
     } else {
