@@ -343,21 +343,22 @@ __global__ __launch_bounds__(kBlock) void k_scan_parts_u64(unsigned long long *_
 // threads' sums serves them all; the values pass through LDS, so that loads and
 // stores are coalesced (a wavefront's eight-byte stores 128 bytes apart kept one
 // workgroup at 10.2 us for 12 000 values, loads one after the other at 8.1; 5.4
-// so).  The sums of ITEMS values stay below
-// 2^32: no caller's total exceeds 2^31 where its values could.
-template <int THREADS, int ITEMS>
+// so).  Sum holds the sum of ITEMS values in a row: 32 bits where a value is
+// below 2^32 / ITEMS or all of them together below 2^32.
+template <int THREADS, int ITEMS, class Sum>
 struct ScanLds {
-    uint32_t x[THREADS * (ITEMS + 1)];  // one spare word after each thread's run
+    Sum x[THREADS * (ITEMS + 1)];  // one spare word after each thread's run
     unsigned long long base[THREADS];
     unsigned long long wsum[THREADS / 64];
 };
 
-template <int THREADS, int ITEMS, class First>
-__device__ __forceinline__ unsigned long long scan_block(ScanLds<THREADS, ITEMS> &S,
+template <int THREADS, int ITEMS, class Sum, class First>
+__device__ __forceinline__ unsigned long long scan_block(ScanLds<THREADS, ITEMS, Sum> &S,
                                                          const uint32_t *__restrict__ in, int n,
                                                          int64_t *__restrict__ out, First first) {
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t v[ITEMS], mine = 0;
+    uint32_t v[ITEMS];
+    Sum mine = 0;
 #pragma unroll
     for (int j = 0; j < ITEMS; j++) v[j] = in[min(tid + j * THREADS, n - 1)];
 #pragma unroll
@@ -367,7 +368,7 @@ __device__ __forceinline__ unsigned long long scan_block(ScanLds<THREADS, ITEMS>
     }
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < ITEMS; j++) v[j] = S.x[tid * (ITEMS + 1) + j];
+    for (int j = 0; j < ITEMS; j++) v[j] = (uint32_t)S.x[tid * (ITEMS + 1) + j];
 #pragma unroll
     for (int j = 0; j < ITEMS; j++) {
         S.x[tid * (ITEMS + 1) + j] = mine;
@@ -395,12 +396,12 @@ __device__ __forceinline__ unsigned long long scan_block(ScanLds<THREADS, ITEMS>
 
 // A tile from part[tile] on (SUM: from the sum of part[0 .. tile), the tiles' own
 // sums).
-template <bool SUM>
+template <bool SUM, class T>
 __global__ __launch_bounds__(kBlock) void k_tile_scan_u32(const uint32_t *__restrict__ in, int64_t n,
                                                           const unsigned long long *__restrict__ part,
                                                           int64_t *__restrict__ out, int64_t nb,
                                                           ScanHost host) {
-    __shared__ ScanLds<kBlock, kItems> S;
+    __shared__ ScanLds<kBlock, kItems, T> S;
     __shared__ unsigned long long psum[kWaves];
     const int64_t base = (int64_t)blockIdx.x * kTile;
     const unsigned long long end =
@@ -428,7 +429,7 @@ constexpr int64_t kOneScan = (int64_t)kOneScanItems * kOneScanThreads;
 __global__ __launch_bounds__(kOneScanThreads) void k_scan_one_u32(const uint32_t *__restrict__ in,
                                                                   int n, int64_t *__restrict__ out,
                                                                   ScanHost host) {
-    __shared__ ScanLds<kOneScanThreads, kOneScanItems> S;
+    __shared__ ScanLds<kOneScanThreads, kOneScanItems, uint32_t> S;
     unsigned long long end = 0;
     if (n > 0) end = scan_block(S, in, n, out, []() { return 0ull; });
     if (threadIdx.x == kOneScanThreads - 1) {
@@ -458,13 +459,20 @@ hipError_t exclusive_scan_u32_i64(const uint32_t *in, int64_t n, int64_t *out,
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_tile_sum_u32, dim3((unsigned)nb), dim3(kBlock), 0, s, in, n, part);
+    auto tiles = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kBlock), 0, s, in, n, part, out, nb, host);
+    };
+    // A value is at most n (the distinct coarse ids of a row), or part of a total
+    // below 2^32 (members, products of at most 2048 columns a row): eight of them
+    // pass 2^32 only past 2^29 values
     if (nb <= 4 * kBlock) {
-        hipLaunchKernelGGL(k_tile_scan_u32<true>, dim3((unsigned)nb), dim3(kBlock), 0, s, in, n,
-                           part, out, nb, host);
+        tiles(k_tile_scan_u32<true, uint32_t>);
     } else {
         hipLaunchKernelGGL(k_scan_parts_u64, dim3(1), dim3(kBlock), 0, s, part, nb);
-        hipLaunchKernelGGL(k_tile_scan_u32<false>, dim3((unsigned)nb), dim3(kBlock), 0, s, in, n,
-                           part, out, nb, host);
+        if (n <= (int64_t)1 << 29)
+            tiles(k_tile_scan_u32<false, uint32_t>);
+        else
+            tiles(k_tile_scan_u32<false, unsigned long long>);
     }
     return hipGetLastError();
 }
