@@ -64,9 +64,10 @@ extern "C" {
 #define MIS2_OPT_GRID_BLOCKS   2  /* 0 = automatic; else 1..8192 256-thread workgroups per sweep */
 #define MIS2_OPT_PROFILE       3  /* 1: time every sweep launch with HIP events on the call's stream */
 #define MIS2_OPT_ACCOUNT       4  /* 1: sweeps also sum the CSR row lengths they visit (extra atomics) */
-#define MIS2_OPT_PERSISTENT    5  /* 0 (default): two launches per round; 1: all rounds of a MIS-2
-                                     run in one cooperative launch (falls back to 0 when the
-                                     grid cannot be co-resident) */
+#define MIS2_OPT_PERSISTENT    5  /* 0 (default): two launches per round, or one for a small graph
+                                     (see below); 1: all rounds of a MIS-2 run in one
+                                     cooperative launch (falls back to 0 when the grid cannot
+                                     be co-resident) */
 #define MIS2_OPT_COMPACT       6  /* 1 (default): when the workspace has room (see
                                      mis2_workspace_bytes_csr) and the graph has rows longer
                                      than the cooperative threshold (32 entries per lane of
@@ -77,9 +78,10 @@ extern "C" {
 #define MIS2_OPT_TAIL          8  /* 1: once both worklists of a run hold fewer than 4096
                                      vertices (round 2 on), its remaining rounds run in one
                                      workgroup with the lists in LDS (one launch instead of
-                                     two per round, and no round issued past the end); 0
-                                     (default): every round is launched.  The plan tuner
-                                     tries both.  Results are the same either way. */
+                                     two per round, and no round issued past the end); 0:
+                                     every round is launched; -1 (default): as the plan tuner
+                                     finds, launched where it has not run.  Results are the
+                                     same either way. */
 #define MIS2_OPT_QUEUE_DEPTH   9  /* rounds the host keeps queued beyond the running one: 0
                                      (default) = 2; else 1..8.  Deeper queues issue more
                                      rounds past the end of a run (they find empty
@@ -96,6 +98,15 @@ extern "C" {
                                      process, never a tuning run (a class not seen yet takes
                                      the degree rule); 0: the fixed degree rule.  Plans never
                                      change results. */
+/*
+ * Small graphs: with every option above that plans or observes launches at its
+ * default (lanes, grid, PROFILE, ACCOUNT, PERSISTENT, COMPACT, TAIL and queue
+ * depth, and AUTOTUNE not 0), a graph of at most 4096 vertices and 32768
+ * entries runs mis2_run or mis2_aggregate whole in one workgroup and one
+ * launch; so does a level or a union of that size in the multilevel, batched
+ * and serving entry points.  Results and per-round sizes are the same.  Any of
+ * those options set otherwise (MIS2_OPT_TAIL 0, say) gives the launched form.
+ */
 
 typedef struct mis2_ctx mis2_ctx;
 
@@ -107,8 +118,9 @@ typedef struct mis2_graph {
     const int32_t *col;     /* device, [nnz] */
 } mis2_graph;
 
-/* Create a context bound to HIP device `device`.  Allocates only a small
- * pinned host buffer for scalar read-back.  *ctx receives the handle. */
+/* Create a context bound to HIP device `device`.  Allocates only pinned host
+ * memory, some 0.6 MiB: scalars and round sizes read back, and the tables of a
+ * batched level on their way.  *ctx receives the handle. */
 int mis2_create(mis2_ctx **ctx, int device);
 
 /* Destroy a context (NULL is ignored).  Does not free the workspace. */
@@ -249,7 +261,8 @@ typedef struct mis2_cgs_plan {
 int mis2_cgs_workspace_bytes(int64_t n, int64_t nnz, size_t *bytes);
 
 /* Fill a plan for graph g (the caller allocates its arrays, sizes above).
- * Synchronises the stream (the colouring reads a count back each round). */
+ * Synchronises the stream (the colouring reads a count back after every four
+ * of its launches). */
 int mis2_cgs_setup(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, int point,
                    mis2_cgs_plan *plan, void *stream);
 
@@ -284,14 +297,17 @@ typedef struct mis2_sweep_record {
                           2 = one persistent launch running every round of the phase
                           (then rows and edges are totals over its sweeps, rows_out is
                           the round count, and the per-sweep records carry ms = -1),
-                          3 = the one-workgroup tail launch (MIS2_OPT_TAIL) running the
-                          phase's rounds from `round` on (totals as for 2; its sweeps'
-                          records come before it, with ms = -1),
+                          3 = a one-workgroup launch running the phase's rounds from
+                          `round` on: the tail (MIS2_OPT_TAIL), or from round 0 a small
+                          graph's whole run (totals as for 2; its sweeps' records come
+                          before it, with ms = -1),
                           4 / 5 = a Refresh Column / Decide Set launch of a round issued
                           after the run had ended (it found empty worklists; rows 0) */
     int32_t phase;     /* 0 = MIS-2 of G; 1 = MIS-2 of the phase-2 induced subgraph */
     int32_t round;     /* round of Algorithm 1, from 0 (-1 for kind 2) */
-    int32_t lanes;     /* lanes per CSR row used by the launch */
+    int32_t lanes;     /* lanes per CSR row of the plan the launch follows (round 0's Decide
+                          Set reads the few rows it has to with 4, 8 or 16; a small graph's
+                          one workgroup has lanes of its own) */
     int64_t rows;      /* worklist entries processed */
     int64_t rows_out;  /* entries kept for the next round */
     int64_t edges;     /* sum of the processed CSR row lengths with MIS2_OPT_ACCOUNT, else -1 */
@@ -312,7 +328,9 @@ int mis2_last_sweeps(const mis2_ctx *ctx, mis2_sweep_record *out, int32_t cap, i
  * row (MIS2_LANES_STAGED for the staged sweeps), workgroups per sweep,
  * whether the last rounds ran in one workgroup (MIS2_OPT_TAIL), and
  * *source = 0 (set by options or the degree rule), 1 (tuned plan from the
- * cache) or 2 (tuned during this call).  Any pointer may be NULL. */
+ * cache) or 2 (tuned during this call).  A small graph that ran whole in one
+ * workgroup reports the plan it would have been launched with; its sweep
+ * records (kind 3 from round 0) tell.  Any pointer may be NULL. */
 int mis2_last_plan(const mis2_ctx *ctx, int32_t *lanes, int32_t *blocks, int32_t *tail,
                    int32_t *source);
 
@@ -402,6 +420,8 @@ int mis2_quotient(mis2_ctx *ctx, const mis2_graph *g, const int32_t *agg_id, int
  *                aggregates of i and its neighbours, ascending
  *   crow/ccol/cval  device out: A_c as an n_agg x n_agg CSR (diagonal
  *                included), c_cap entries of room, columns ascending
+ *                (pcol and pval are also scratch, up to p_cap entries: their
+ *                contents are lost where the call fails)
  *   p_nnz, c_nnz host out: entries of P and A_c (-1 when not reached)
  *   ws_need      host out (may be NULL): workspace bytes needed, when the
  *                context's is too small

@@ -368,6 +368,7 @@ FillSpans round_fills(const mis2_graph *g, const Workspace &ws, bool masked) {
 // LDS, which pays while rows are dense and costs 1-2 us per launch once they
 // are sparse.
 constexpr int kLateLanes = 4;
+constexpr uint64_t kLateShare = 4;
 
 // A compacting round of a graph whose T outgrows an XCD's L2 asks a bit per
 // vertex (n / 8 bytes, which stay in it) which neighbours are OUT before it
@@ -378,7 +379,6 @@ constexpr int kLateLanes = 4;
 // 204, 131, 82 us (with flat_min since, 469, 251, 175, 114, 65), the bits 5 us
 // each; with |worklist1| near n / 60 22 -> 29 us.
 constexpr uint64_t kLiveShare = 16;
-constexpr uint64_t kLateShare = 4;
 
 int run_rounds(mis2_ctx *ctx, const mis2_graph *g, uint64_t seed, const Workspace &ws,
                const Geometry &gm, bool masked, int phase, hipStream_t s, int32_t *iters_out,

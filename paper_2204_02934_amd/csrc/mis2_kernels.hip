@@ -377,8 +377,9 @@ __device__ __forceinline__ int flat_row(const FlatLds &sh, int nrows, uint32_t f
 // steps as the longest of 64 rows: with 9 entries on average and some rows of
 // 32, three of four steps were padding.)  4 at a time leave the compacting
 // sweeps 5 wavefronts per SIMD, 8 leave 4: Chung-Lu 4M vertices, all compacting
-// rounds, one lane per row 2.09, 8 at a time 1.89, 4 at a time 1.85 ms.  All lanes must call it.  any: J
-// readable column indices, for the lanes past the end.
+// rounds, one lane per row 2.09, 8 at a time 1.89, 4 at a time 1.85 ms.  (The
+// rule on sizes is launch_col_round's.)  All lanes must call it.  any: a readable
+// column index, for the lanes past the end.
 template <int J, class GET>
 __device__ __forceinline__ uint32_t flat_min(FlatLds &sh, const int32_t *any, const int32_t *row,
                                              int64_t len, GET get) {

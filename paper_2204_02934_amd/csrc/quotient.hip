@@ -45,9 +45,10 @@ constexpr int kWEdges = 8;                   // entries per lane loaded together
 
 // The spare buffer that rows are written to while they are counted.  Its first
 // part has `per` entries for every member of a row; its second part takes the
-// rows that need more, wherever there is room: kSpareParts regions with a cursor each (one address for the whole
-// chip would serialise its atomics); a row's place, an index into the buffer,
-// is kept in the row's unused slot of the first part.
+// rows that need more, wherever there is room: kSpareParts regions with a cursor
+// each (one address for the whole chip would serialise its atomics); a row's
+// place, an index into the buffer, is kept in the row's unused slot of the first
+// part.
 constexpr int kSpareParts = 32;
 constexpr int kSpareLine = 32;  // words per cursor (one cache line)
 struct Spare {
@@ -725,13 +726,12 @@ __global__ __launch_bounds__(kBlock) void k_coarse_rows(
 
 // Giant rows, one bitmap slot each (gmeta: rows [0, S), INT32_MAX less the
 // smallest ids [S, 2S), the largest ids plus one [2S, 3S), rows claimed [3S]; all
-// zero before a count pass).  Slots blockIdx.y,
-// blockIdx.y + gridDim.y, ...; the workgroups of a slot share its members in chunks of kBlock, kGiantParts
-// workgroups to a chunk (a chunk that holds hubs has a hundred times the
-// entries of another).  Where the
-// coarse ids fit an LDS bitmap (words > 0) a workgroup collects its share
-// there and adds its set words to the slot's once; else it sets every bit in
-// the slot (a plain read first skips bits it sees already set).  Most
+// zero before a count pass).  Slots blockIdx.y, blockIdx.y + gridDim.y, ...; the
+// workgroups of a slot share its members in chunks of kBlock, kGiantParts
+// workgroups to a chunk (a chunk that holds hubs has a hundred times the entries
+// of another).  Where the coarse ids fit an LDS bitmap (words > 0) a workgroup
+// collects its share there and adds its set words to the slot's once; else it sets
+// every bit in the slot (a plain read first skips bits it sees already set).  Most
 // candidates of a giant row repeat: a row of 2.3 million candidates held 6000
 // distinct ids, and setting each in global memory put every workgroup's
 // atomics on the same few lines.
