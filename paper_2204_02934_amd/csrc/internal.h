@@ -464,8 +464,8 @@ hipError_t launch_push_in(int64_t n, const int64_t *row_ptr, const int32_t *col,
 hipError_t launch_push_near(int64_t n, const int64_t *row_ptr, const int32_t *col,
                             const uint32_t *M, uint8_t *near, hipStream_t s);
 // Refresh Column asks live bits with at most this many lanes a row.  Aggregation
-// of Chung-Lu 2.5M without and with them (kernels, us): 1 lane 2978 and 2579, 2
-// 3035 and 2910, 4 3226 and 3051, 8 3679 and 3526; 16 4595 and 4731, staged 3074
+// of Chung-Lu 2.5M without and with them (kernels, us): 1 lane 2980 and 2523, 2
+// 3036 and 2888, 4 3232 and 2999, 8 3677 and 3466; 16 4595 and 4731, staged 3074
 // and 3108.
 constexpr int kLiveLanes = 8;
 // Bit v of live clear only where T[v] is OUT.  Writes ceil(n / 64) * 2 words.

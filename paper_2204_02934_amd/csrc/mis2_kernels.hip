@@ -1489,7 +1489,7 @@ __device__ __forceinline__ void col_round(const int64_t *__restrict__ row_ptr,
                                           const RoundsArgs &a, int r) {
     round_start(a, r);
     SegIO io = round_col_io(a, r);
-    if (!GEN) io.gen0 = 0;
+    if (!GEN || RD || WR) io.gen0 = 0;  // (no compacting round computes tuples)
     if (RD) {
         io.ccol_in = a.colc;
         io.lenc_in = a.lenc;
